@@ -60,6 +60,7 @@ struct Layout {
   size_t dec_lut, dec_tab, dec_F, D, row_off;
   size_t total;
   uint32_t A, nc_max, capw, n_blk;
+  uint32_t enc_spw;  // streams per encoder work-group: kWG, or 64 (k_encode_feed)
   uint32_t cnt_rep;  // partial histograms behind the histogram of D (CSR mode with an LDS-sized alphabet), else 0
   uint32_t n_pub;  // work-groups of the encoder when it also places its words (0: separate gather kernel)
   // the counters behind `chunk_words` (32-bit words; everything before tc_off is zeroed when a call starts, and so
@@ -96,6 +97,14 @@ int check_params(const rans_params *p, uint64_t n) {
   if (p->mode == RANS_MODE_CSR && p->cols + 1 > 65536) return RANS_ERR_ALPHABET;
   return RANS_OK;
 }
+
+// Coding waves (64 streams each) up to which the encoder runs them one to a work-group with three feeding waves
+// (k_encode_feed) instead of four to a work-group (k_encode).  Whole compress calls, us, four to a work-group against
+// fed, at 384 / 512 / 768 coding waves (64 streams to a chunk): 64 rows 28 / 30 / 34 against 26 / 29 / 42, 256 rows
+// 50 / 54 / 90 against 41 / 46 / 70; 1024 streams to a chunk: 64 rows 26 / 27 / 30 against 27 / 30 / 46, 256 rows
+// 50 / 53 / 59 against 43 / 49 / 78.  Two fed work-groups fit a compute unit, so from 512 on they come in turns.
+constexpr uint32_t kFeedMaxWaves = 384, kFeedMaxWavesLong = 512;
+constexpr uint32_t kFeedLongRows = 128;
 
 constexpr uint32_t kCntRep = 8;  // partial histograms the CSR kernels spread their same-address additions over
 constexpr uint32_t kCsrTile = kWG * 16;  // elements per tile in the CSR count / compact kernels
@@ -135,8 +144,13 @@ Layout make_layout(const rans_params &p, uint64_t n) {
   size_t n_sc = (size_t)L.nc_max * p.n_streams;
   L.st = take(n_sc * 4);
   L.nw = take(n_sc * 4);
+  // in CSR mode D is rarely longer than half of what the grid has to be sized for
+  const uint64_t coding_waves = (uint64_t)L.nc_max * ((p.n_streams + 63) / 64);
+  const bool csr = p.mode == RANS_MODE_CSR;
+  const uint32_t feed_max = !csr && per_stream >= kFeedLongRows ? kFeedMaxWavesLong : kFeedMaxWaves;
+  L.enc_spw = (csr ? (coding_waves + 1) / 2 : coding_waves) <= feed_max ? 64 : kWG;
   {
-    const uint64_t wgs = (uint64_t)L.nc_max * ((p.n_streams + kWG - 1) / kWG);
+    const uint64_t wgs = (uint64_t)L.nc_max * ((p.n_streams + L.enc_spw - 1) / L.enc_spw);
     L.n_pub = (wgs > 0 && wgs <= kFusedGatherMax) ? (uint32_t)wgs : 0;
   }
   if (p.mode != RANS_MODE_CSR) L.n_blk = 0;
@@ -144,8 +158,8 @@ Layout make_layout(const rans_params &p, uint64_t n) {
   L.acc_off = (L.nc_max + 1 + L.n_pub + 1) & ~1u;
   L.tc_off = L.acc_off + (L.n_pub ? 2 * L.nc_max : 0);
   L.chunk_words = take(((size_t)L.tc_off + 2 * (size_t)L.n_blk) * 4);
-  // word blocks of the encoder, per work-group (kWG streams, absent ones included): see k_encode
-  L.scratch = take((size_t)L.nc_max * ((p.n_streams + kWG - 1) / kWG) * kWG * L.capw * 2);
+  // word blocks of the encoder, per work-group (enc_spw streams, absent ones included): see k_encode
+  L.scratch = take((size_t)L.nc_max * ((p.n_streams + L.enc_spw - 1) / L.enc_spw) * L.enc_spw * L.capw * 2);
   size_t enc_end = o;
   o = overlay;
   L.dec_lut = take(((size_t)2 << p.freq_bits));

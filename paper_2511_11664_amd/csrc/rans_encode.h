@@ -142,6 +142,177 @@ __device__ __forceinline__ uint64_t wait_chunk(const unsigned long long *acc, ui
 // Sixteen bytes at an address that is only 2-byte aligned, moved to or from registers in one access.
 struct __attribute__((packed, aligned(2))) Block16 { uint32_t x, y, z, w; };
 
+// What every thread of an encoder work-group knows once the frequency table is in its LDS.
+struct EncTable {
+  uint32_t ok;     // 0: an error has been recorded
+  uint32_t exact;  // the table holds the division-free entries, else {floor(2^32/f), f, F, 2^M - f}
+  uint32_t n_chunks;
+  uint64_t len_d, dir_off, payload_off;
+};
+// Table build by a whole encoder work-group for itself: counts from the histogram, normalisation by the first wave
+// (meanwhile() is what the work-group does beside it), entries into l_tab (16 bytes a symbol).  sh: 16 words;
+// l_tmp: 12 A bytes that are free until the coding.  Alphabets up to kNormWaveA.
+template <class Meanwhile>
+__device__ __forceinline__ EncTable enc_build_table(const CtlRef &ctl, const NormArgs &na, uint32_t A, uint32_t totalM,
+                                                    uint32_t *l_tab, uint32_t *sh, uint2 *l_tmp, Meanwhile meanwhile) {
+  uint2 *const l_tab8 = l_tmp;  // {floor(2^32/f), f | F << 16}
+  uint32_t *const l_cnt = (uint32_t *)(l_tab8 + A);
+  {  // the counts, partial histograms summed, with all of a lane's loads in flight together
+    constexpr uint32_t kParts = kCntRep + 1;  // n_rep is 0 or kCntRep
+    for (uint32_t a = threadIdx.x; a < A; a += kWG) {
+      uint32_t c[kParts];
+#pragma unroll
+      for (uint32_t q = 0; q < kParts; q++) c[q] = q <= na.n_rep ? na.cnt[(size_t)q * A + a] : 0u;
+      uint32_t t = 0;
+#pragma unroll
+      for (uint32_t q = 0; q < kParts; q++) t += c[q];
+      l_cnt[a] = t;
+    }
+    __syncthreads();
+  }
+  meanwhile();
+  NormArgs nl = na;  // a copy in registers: the argument itself cannot be changed in place
+  nl.lds_cnt = l_cnt;
+  nl.enc_tab = l_tab8;
+  nl.enc_tab4 = (uint4 *)l_tab;
+  nl.quiet = blockIdx.x != 0;
+  nl.entry_checked = 1;
+  // Alphabets above 256 symbols (CSR): the wave would make five to eight symbols' entries per lane, so it stops at
+  // the frequencies and the whole work-group makes the entries, a lane per symbol (c2 as CSR: 2 us less).  With
+  // a byte alphabet the wave does it all: the second step's barriers and its instructions on all sixteen waves
+  // of a compute unit cost more than they save there (c5a: 0.8 us more).
+  const bool split = A > 256;
+  nl.fF = split ? (uint2 *)l_tab : nullptr;
+  if (threadIdx.x < 64) {  // frequencies and their running sums: one wave
+    const NormResult r = normalize_wave(ctl, nl);
+    if (threadIdx.x == 0) {
+      sh[0] = r.ok; sh[1] = split ? 0u : (r.exact ? 0u : 1u); sh[2] = r.n_chunks;
+      *(uint64_t *)(sh + 4) = r.len_d; *(uint64_t *)(sh + 6) = r.dir_off; *(uint64_t *)(sh + 8) = r.payload_off;
+    }
+  }
+  __syncthreads();
+  EncTable t;
+  t.ok = sh[0];
+  t.n_chunks = sh[2];
+  t.len_d = *(const uint64_t *)(sh + 4); t.dir_off = *(const uint64_t *)(sh + 6); t.payload_off = *(const uint64_t *)(sh + 8);
+  t.exact = 0;
+  if (!t.ok) return t;
+  if (split) {  // the table entries: every lane its symbol's (a division each), which overwrite {f, F} in the slot
+    int inexact = 0;
+    for (uint32_t a = threadIdx.x; a < A; a += kWG) {
+      const uint2 e = nl.fF[2 * a];
+      inexact |= emit_entries(nl, a, e.x, e.y, [](uint32_t kk, uint32_t d) { return div_pow2_by(kk, d); });
+    }
+    if (inexact) atomicOr(&sh[1], 1u);
+    __syncthreads();
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->enc_exact = sh[1] == 0;
+  }
+  t.exact = sh[1] == 0;
+  if (!t.exact) {
+    for (uint32_t a = threadIdx.x; a < A; a += kWG) {
+      const uint2 q = l_tab8[a];
+      ((uint4 *)l_tab)[a] = make_uint4(q.x, q.y & 0xffffu, q.y >> 16, totalM - (q.y & 0xffffu));
+    }
+  }
+  __syncthreads();  // the table is complete; sh and l_tmp may be written again
+  return t;
+}
+
+// Totals of what lies before a work-group's words: every earlier chunk (its size gives the chunk's byte offset) and
+// the earlier groups of this chunk (the position inside the chunk).  The first wave collects them - a lane's loads
+// are independent of each other - and hands the sums over through LDS.
+struct EncBefore {
+  uint64_t off, pre;  // bytes of the chunks before, words of the groups before
+  bool failed;        // a wait ran into its bound, or another work-group reported an error
+};
+__device__ __forceinline__ EncBefore enc_look_back(const CtlRef &ctl, uint32_t k, uint32_t g, uint32_t groups, uint32_t S,
+                                                   const unsigned long long *chunk_acc, const uint32_t *wg_pub, uint32_t *sh) {
+  uint64_t *sh64 = (uint64_t *)(sh + 4);  // [0] chunk offset, [1] words before this group, [2] a wait failed
+  const uint32_t lane = threadIdx.x & 63;
+  if (threadIdx.x < 64) {
+    uint64_t off_loc = 0, pre_loc = 0, failed = 0;
+    for (uint32_t c = lane; c < k; c += 64) {
+      const uint64_t words = wait_chunk(chunk_acc, c, groups, ctl);
+      failed |= words == ~0ull;
+      off_loc += (8ull * S + 2 * words + 3) & ~3ull;
+    }
+    for (uint32_t g2 = lane; g2 < g; g2 += 64) {
+      const uint32_t v = wait_published(wg_pub, k * groups + g2, ctl);
+      failed |= v == 0;
+      pre_loc += v - 1;
+    }
+    auto add64 = [](uint64_t x, uint64_t y) { return x + y; };
+    off_loc = lane63_64(wave_incl_scan64(off_loc, add64));
+    pre_loc = lane63_64(wave_incl_scan64(pre_loc, add64));
+    failed = lane63_64(wave_incl_scan64(failed, add64));
+    if (lane == 0) {
+      sh64[0] = off_loc;
+      sh64[1] = pre_loc;
+      sh64[2] = failed;
+    }
+  }
+  __syncthreads();
+  return EncBefore{sh64[0], sh64[1], sh64[2] != 0};
+}
+
+// Ends of the placement that every encoder shares: directory entry, total, capacity.  False if the words do not fit.
+struct EncPlace {
+  uint64_t off, pre, dir_off, payload_off, cap;
+  uint32_t k, g, groups, nc, S, tot;
+};
+__device__ __forceinline__ bool enc_directory(const CtlRef &ctl, const EncPlace &e, uint8_t *out, uint64_t *d_stream_bytes) {
+  uint8_t *dir = out + e.dir_off;
+  const uint64_t my_end = e.payload_off + e.off + 8ull * e.S + 2 * (e.pre + e.tot);  // end of this group's words
+  const bool last_group = e.g == e.groups - 1;
+  const uint64_t chunk_end = (my_end + 3) & ~3ull;  // meaningful for the chunk's last group
+  const bool fits = (last_group ? chunk_end : my_end) <= e.cap;
+  if (threadIdx.x == 0) {
+    if (e.g == 0) {
+      st32(dir + 8ull * e.k, (uint32_t)e.off);
+      st32(dir + 8ull * e.k + 4, (uint32_t)(e.off >> 32));
+    }
+    if (e.k == e.nc - 1 && last_group) {
+      const uint64_t pay = chunk_end - e.payload_off;
+      st32(dir + 8ull * e.nc, (uint32_t)pay);
+      st32(dir + 8ull * e.nc + 4, (uint32_t)(pay >> 32));
+      ctl->total_bytes = chunk_end;
+      if (d_stream_bytes) *d_stream_bytes = fits ? chunk_end : 0;
+    }
+    if (!fits) set_status(ctl, RANS_ERR_CAPACITY);
+  }
+  return fits;
+}
+
+// Eight lanes move a stream's words from its LDS area to the container, in pieces of 16 bytes whose both ends are
+// only 2-byte aligned: lane part sub of the eight, n words from LDS address src_w (in words) to dp.
+__device__ __forceinline__ void enc_copy_words(const uint16_t *lds, uint32_t src_w, uint16_t *dp0, uint32_t n, uint32_t sub) {
+  for (uint32_t w0 = 8 * sub; w0 < n; w0 += 64) {
+    const uint16_t *sp = lds + src_w + w0;
+    uint16_t *dp = dp0 + w0;
+    if (w0 + 8 <= n) {
+      uint4 q;
+      __builtin_memcpy(&q, sp, 16);
+      __builtin_memcpy(dp, &q, 16);
+    } else {  // the stream's last piece, 1 to 7 words: four, two, one
+      const uint32_t rem = n - w0;
+      uint32_t o = 0;
+      if (rem & 4) {
+        uint2 q;
+        __builtin_memcpy(&q, sp, 8);
+        __builtin_memcpy(dp, &q, 8);
+        o = 4;
+      }
+      if (rem & 2) {
+        uint32_t q;
+        __builtin_memcpy(&q, sp + o, 4);
+        __builtin_memcpy(dp + o, &q, 4);
+        o += 2;
+      }
+      if (rem & 1) dp[o] = sp[o];
+    }
+  }
+}
+
 template <class Src, int TAB, bool MUL24, bool FUSE>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k_encode(
     Src src, const uint2 *g_tab, const uint4 *g_tab4, uint32_t A, uint32_t M, uint32_t S, uint32_t cs, CtlRef ctl,
@@ -196,85 +367,35 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
   uint32_t nc, exact_tab;
   uint64_t len, dir_off, payload_off;
   if (TAB == 2 && build_tab) {
-    uint2 *const l_tab8 = (uint2 *)(sh + 16);  // {floor(2^32/f), f | F << 16}: in the stage, which is free until the coding
-    uint32_t *const l_cnt = (uint32_t *)(l_tab8 + A);
-    {  // the counts, partial histograms summed, with all of a lane's loads in flight together
-      constexpr uint32_t kParts = kCntRep + 1;  // n_rep is 0 or kCntRep
-      for (uint32_t a = threadIdx.x; a < A; a += kWG) {
-        uint32_t c[kParts];
+    auto touch = [&]() {
+      if constexpr (std::is_same<Src, SrcDense>::value) {
+        // While the first wave builds the table the others touch the lines that the coder asks for first (the
+        // last 32 rows of the chunk, which is coded from its end), so that they come from the cache by then.
+        // A wave's 64-byte column shares its 128-byte lines with the neighbouring wave's.
+        if (wide && threadIdx.x >= 64) {
+          const uint64_t cl = cs ? cs : na.n_elems, b0 = (uint64_t)k * cl;
+          if (b0 < na.n_elems) {
+            const uint64_t nh = na.n_elems - b0 < cl ? na.n_elems - b0 : cl, rows = nh / S;
+            const uint32_t ln = threadIdx.x & 63;
+            const uint8_t *colp = src.bytes() + b0 + (g * kWG + (threadIdx.x - ln)) + 16 * (ln & 3);
+            uint32_t acc = 0;
 #pragma unroll
-        for (uint32_t q = 0; q < kParts; q++) c[q] = q <= na.n_rep ? na.cnt[(size_t)q * A + a] : 0u;
-        uint32_t t = 0;
-#pragma unroll
-        for (uint32_t q = 0; q < kParts; q++) t += c[q];
-        l_cnt[a] = t;
-      }
-      __syncthreads();
-    }
-    if constexpr (std::is_same<Src, SrcDense>::value) {
-      // While the first wave builds the table the others touch the lines that the coder asks for first (the
-      // last 32 rows of the chunk, which is coded from its end), so that they come from the cache by then.
-      // A wave's 64-byte column shares its 128-byte lines with the neighbouring wave's.
-      if (wide && threadIdx.x >= 64) {
-        const uint64_t cl = cs ? cs : na.n_elems, b0 = (uint64_t)k * cl;
-        if (b0 < na.n_elems) {
-          const uint64_t nh = na.n_elems - b0 < cl ? na.n_elems - b0 : cl, rows = nh / S;
-          const uint32_t ln = threadIdx.x & 63;
-          const uint8_t *colp = src.bytes() + b0 + (g * kWG + (threadIdx.x - ln)) + 16 * (ln & 3);
-          uint32_t acc = 0;
-#pragma unroll
-          for (uint32_t u = 1; u <= 2; u++)
-            if (rows >= 16 * u) acc ^= *(const uint32_t *)(colp + (rows - 16 * u + (ln >> 2)) * S);
-          if (acc == 0x9e3779b9u && wide == 0x7fffffff) l_mem[1] = acc;  // never true: keeps the loads
+            for (uint32_t u = 1; u <= 2; u++)
+              if (rows >= 16 * u) acc ^= *(const uint32_t *)(colp + (rows - 16 * u + (ln >> 2)) * S);
+            if (acc == 0x9e3779b9u && wide == 0x7fffffff) l_mem[1] = acc;  // never true: keeps the loads
+          }
         }
       }
-    }
-    NormArgs nl = na;  // a copy in registers: the argument itself cannot be changed in place
-    nl.lds_cnt = l_cnt;
-    nl.enc_tab = l_tab8;
-    nl.enc_tab4 = (uint4 *)l_tab;
-    nl.quiet = blockIdx.x != 0;
-    nl.entry_checked = 1;
-    // Alphabets above 256 symbols (CSR): the wave would make five to eight symbols' entries per lane, so it stops at
-    // the frequencies and the whole work-group makes the entries, a lane per symbol (c2 as CSR: 2 us less).  With
-    // a byte alphabet the wave does it all: the second step's barriers and its instructions on all sixteen waves
-    // of a compute unit cost more than they save there (c5a: 0.8 us more).
-    const bool split = A > 256;
-    nl.fF = split ? (uint2 *)l_tab : nullptr;
-    if (threadIdx.x < 64) {  // frequencies and their running sums: one wave
-      const NormResult r = normalize_wave(ctl, nl);
-      if (threadIdx.x == 0) {
-        sh[0] = r.ok; sh[1] = split ? 0u : (r.exact ? 0u : 1u); sh[2] = r.n_chunks;
-        *(uint64_t *)(sh + 4) = r.len_d; *(uint64_t *)(sh + 6) = r.dir_off; *(uint64_t *)(sh + 8) = r.payload_off;
-      }
-    }
-    __syncthreads();
-    const uint32_t ok = sh[0];
-    nc = sh[2];
-    len = *(const uint64_t *)(sh + 4); dir_off = *(const uint64_t *)(sh + 6); payload_off = *(const uint64_t *)(sh + 8);
-    if (!ok) {
+    };
+    const EncTable t = enc_build_table(ctl, na, A, totalM, l_tab, sh, (uint2 *)(sh + 16), touch);
+    if (!t.ok) {
       if (FUSE && blockIdx.x == 0 && threadIdx.x == 0 && d_stream_bytes) *d_stream_bytes = 0;
       bail();
       return;
     }
-    if (split) {  // the table entries: every lane its symbol's (a division each), which overwrite {f, F} in the slot
-      int inexact = 0;
-      for (uint32_t a = threadIdx.x; a < A; a += kWG) {
-        const uint2 e = nl.fF[2 * a];
-        inexact |= emit_entries(nl, a, e.x, e.y, [](uint32_t kk, uint32_t d) { return div_pow2_by(kk, d); });
-      }
-      if (inexact) atomicOr(&sh[1], 1u);
-      __syncthreads();
-      if (blockIdx.x == 0 && threadIdx.x == 0) ctl->enc_exact = sh[1] == 0;
-    }
-    exact_tab = sh[1] == 0;
-    if (!exact_tab) {
-      for (uint32_t a = threadIdx.x; a < A; a += kWG) {
-        const uint2 q = l_tab8[a];
-        ((uint4 *)l_tab)[a] = make_uint4(q.x, q.y & 0xffffu, q.y >> 16, totalM - (q.y & 0xffffu));
-      }
-    }
-    __syncthreads();  // the table is complete; sh and the stage may be written again
+    nc = t.n_chunks;
+    len = t.len_d; dir_off = t.dir_off; payload_off = t.payload_off;
+    exact_tab = t.exact;
   } else {
     nc = ctl->n_chunks; len = ctl->len_d; dir_off = ctl->dir_off; payload_off = ctl->payload_off;
     exact_tab = TAB == 2 && ctl->enc_exact != 0;
@@ -699,62 +820,17 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
       const unsigned long long until = now + ((now - t_begin) * (n_classes - 1 - prio_class) * 12) / 100;
       while (wall_clock64() < until) __builtin_amdgcn_s_sleep(32);
     }
-    // Totals of what lies before this work-group's words: every earlier chunk (its size gives the chunk's
-    // byte offset) and the earlier groups of this chunk (the position inside the chunk).  The first wave
-    // collects them - a lane's loads are independent of each other - and hands the sums over through LDS.
-    uint64_t *sh64 = (uint64_t *)(sh + 4);  // [0] chunk offset, [1] words before this group, [2] a wait failed
-    const uint32_t lane = threadIdx.x & 63;
-    if (threadIdx.x < 64) {
-      uint64_t off_loc = 0, pre_loc = 0, failed = 0;
-      for (uint32_t c = lane; c < k; c += 64) {
-        const uint64_t words = wait_chunk(chunk_acc, c, groups, ctl);
-        failed |= words == ~0ull;
-        off_loc += (8ull * S + 2 * words + 3) & ~3ull;
-      }
-      for (uint32_t g2 = lane; g2 < g; g2 += 64) {
-        const uint32_t v = wait_published(wg_pub, k * groups + g2, ctl);
-        failed |= v == 0;
-        pre_loc += v - 1;
-      }
-      auto add64 = [](uint64_t x, uint64_t y) { return x + y; };
-      off_loc = lane63_64(wave_incl_scan64(off_loc, add64));
-      pre_loc = lane63_64(wave_incl_scan64(pre_loc, add64));
-      failed = lane63_64(wave_incl_scan64(failed, add64));
-      if (lane == 0) {
-        sh64[0] = off_loc;
-        sh64[1] = pre_loc;
-        sh64[2] = failed;
-      }
-    }
-    __syncthreads();
-    const uint64_t off = sh64[0], pre = sh64[1];
-    if (sh64[2]) {  // uniform: a wait ran into its bound, or another work-group reported an error
+    const EncBefore before = enc_look_back(ctl, k, g, groups, S, chunk_acc, wg_pub, sh);
+    const uint64_t off = before.off, pre = before.pre;
+    if (before.failed) {  // uniform
       if (threadIdx.x == 0) {
         if (get_status(ctl) == 0) set_status(ctl, RANS_ERR_HIP);
         if (k == nc - 1 && g == groups - 1 && d_stream_bytes) *d_stream_bytes = 0;
       }
       return;
     }
-    uint8_t *dir = out + dir_off;
-    const uint64_t my_end = payload_off + off + 8ull * S + 2 * (pre + tot);  // end of this group's words
     const bool last_group = g == groups - 1;
-    const uint64_t chunk_end = (my_end + 3) & ~3ull;  // meaningful for the chunk's last group
-    const bool fits = (last_group ? chunk_end : my_end) <= cap;
-    if (threadIdx.x == 0) {
-      if (g == 0) {
-        st32(dir + 8ull * k, (uint32_t)off);
-        st32(dir + 8ull * k + 4, (uint32_t)(off >> 32));
-      }
-      if (k == nc - 1 && last_group) {
-        const uint64_t pay = chunk_end - payload_off;
-        st32(dir + 8ull * nc, (uint32_t)pay);
-        st32(dir + 8ull * nc + 4, (uint32_t)(pay >> 32));
-        ctl->total_bytes = chunk_end;
-        if (d_stream_bytes) *d_stream_bytes = fits ? chunk_end : 0;
-      }
-      if (!fits) set_status(ctl, RANS_ERR_CAPACITY);
-    }
-    if (!fits) return;  // uniform
+    if (!enc_directory(ctl, EncPlace{off, pre, dir_off, payload_off, cap, k, g, groups, nc, S, tot}, out, d_stream_bytes)) return;
     uint8_t *ck = out + payload_off + off;
     if (live) {
       st32(ck + 4ull * j0, s);
@@ -765,35 +841,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
     // 64 words on, where an area holds that many) as one 16-byte piece - both ends are only 2-byte aligned, which the target allows - so a
     // wave moves eight streams per step and their pieces are adjacent in the container.
     uint16_t *dst = (uint16_t *)(ck + 8ull * S) + pre;  // first word of this group
+    const uint32_t lane = threadIdx.x & 63;
     for (uint32_t L0 = 0; L0 < 64; L0 += 8) {
       const int from = (int)(L0 + (lane >> 3));
       const uint32_t nL = (uint32_t)__shfl((int)n_lds, from), eL = (uint32_t)__shfl((int)ex, from);
       const uint32_t aL = (uint32_t)__shfl((int)wp, from) + 2;
-      for (uint32_t w0 = 8 * (lane & 7); w0 < nL; w0 += 64) {
-        const uint16_t *sp = (const uint16_t *)l_mem + (aL >> 1) + w0;
-        uint16_t *dp = dst + eL + w0;
-        if (w0 + 8 <= nL) {
-          uint4 q;
-          __builtin_memcpy(&q, sp, 16);
-          __builtin_memcpy(dp, &q, 16);
-        } else {  // the stream's last piece, 1 to 7 words: four, two, one
-          const uint32_t rem = nL - w0;
-          uint32_t o = 0;
-          if (rem & 4) {
-            uint2 q;
-            __builtin_memcpy(&q, sp, 8);
-            __builtin_memcpy(dp, &q, 8);
-            o = 4;
-          }
-          if (rem & 2) {
-            uint32_t q;
-            __builtin_memcpy(&q, sp + o, 4);
-            __builtin_memcpy(dp + o, &q, 4);
-            o += 2;
-          }
-          if (rem & 1) dp[o] = sp[o];
-        }
-      }
+      enc_copy_words((const uint16_t *)l_mem, aL >> 1, dst + eL, nL, lane & 7);
     }
     // a spilled block to its place: 16 bytes to a 2-byte aligned address
     auto put_block = [&](const uint4 &q, uint32_t dst_off) { *(Block16 *)(dst + dst_off) = Block16{q.x, q.y, q.z, q.w}; };

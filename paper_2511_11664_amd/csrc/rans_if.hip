@@ -34,6 +34,7 @@
 #include "rans_quant.h"
 #include "rans_csr.h"
 #include "rans_encode.h"
+#include "rans_encode_feed.h"
 #include "rans_decode.h"
 #include "rans_reshape.h"
 
@@ -271,7 +272,7 @@ int launch_encode_tail(const uint8_t *d_sym, uint64_t n, const rans_params &p, c
     PROF_LAUNCH(KID_NORMALIZE, k_normalize, dim3(1), dim3(kBig), 0, st, ctl, na_k);
     LAUNCH_CHECK();
   }
-  const uint32_t groups = (S + kWG - 1) / kWG;
+  const uint32_t groups = (S + L.enc_spw - 1) / L.enc_spw;
   const bool fused_gather = L.n_pub != 0;  // the encoder places its words itself: no k_chunk_scan / k_gather
   if (L.nc_max) {
     uint16_t *scratch = (uint16_t *)(ws + L.scratch);
@@ -327,7 +328,44 @@ int launch_encode_tail(const uint8_t *d_sym, uint64_t n, const rans_params &p, c
       else ENC_LAUNCH2(SRCT, TABV, false, false);                                                                   \
     }                                                                                                               \
   } while (0)
-    if (csr) {
+#define FEED_LAUNCH2(SRCT, LDSTAB, M24)                                                                             \
+  do {                                                                                                              \
+    auto kfn = k_encode_feed<SRCT, LDSTAB, M24>;                                                                    \
+    static const hipError_t attr_rc =                                                                               \
+        hipFuncSetAttribute((const void *)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);             \
+    if (lds_e > 64 * 1024 && attr_rc != hipSuccess) return RANS_ERR_HIP;                                            \
+    PROF_LAUNCH(KID_ENCODE, kfn, dim3(n_wg_e), dim3(kWG), lds_e, st, src, tab, tab4, A, p.freq_bits, S,             \
+                p.chunk_syms, ctl, scratch, L.capw, groups, cw + L.nc_max + 1, (unsigned long long *)(cw + L.acc_off), \
+                d_stream, (uint64_t)cap, d_stream_bytes, rw_e, enc_builds, na_k);                                   \
+  } while (0)
+#define FEED_LAUNCH(SRCT)                                                                                           \
+  do {                                                                                                              \
+    const bool tab_in_lds = A <= kFeedLdsTabMaxA;                                                                   \
+    const uint32_t n_wg_e = L.nc_max * groups;                                                                      \
+    const size_t rest_e = (tab_in_lds ? (size_t)A * 16 : 0) + 64 + 2 * kFeedTileBytes;                              \
+    /* word slots per stream: what it can need, as far as the LDS goes with up to two work-groups on a compute unit */ \
+    const size_t room_e = n_wg_e > compute_units() && rest_e < 64 * 1024 ? 80 * 1024 : 160 * 1024;                  \
+    uint32_t rw_e = L.capw < 16 ? 16 : (L.capw > 252 ? 252 : (L.capw + 3) & ~3u);                                   \
+    while (rw_e > 16 && kEncGuard + enc_area_stride(rw_e) * kFeedSpw + rest_e > room_e) rw_e -= 4;                  \
+    const size_t lds_e = kEncGuard + enc_area_stride(rw_e) * kFeedSpw + rest_e;                                     \
+    if (tab_in_lds) {                                                                                               \
+      if (mul24) FEED_LAUNCH2(SRCT, true, true);                                                                    \
+      else FEED_LAUNCH2(SRCT, true, false);                                                                         \
+    } else {                                                                                                        \
+      if (mul24) FEED_LAUNCH2(SRCT, false, true);                                                                   \
+      else FEED_LAUNCH2(SRCT, false, false);                                                                        \
+    }                                                                                                               \
+  } while (0)
+    const bool feed = L.enc_spw == kFeedSpw;
+    if (feed) {
+      if (csr) {
+        SrcCsr src{ws + L.v, (const uint16_t *)(ws + L.c), (const uint16_t *)(ws + L.r), 0};
+        FEED_LAUNCH(SrcCsr);
+      } else {
+        SrcDense src{d_sym};
+        FEED_LAUNCH(SrcDense);
+      }
+    } else if (csr) {
       SrcCsr src{ws + L.v, (const uint16_t *)(ws + L.c), (const uint16_t *)(ws + L.r), 0};
       if (A <= kEncTab16MaxA) ENC_LAUNCH(SrcCsr, 2);
       else if (lds_tab) ENC_LAUNCH(SrcCsr, 1);
@@ -336,6 +374,8 @@ int launch_encode_tail(const uint8_t *d_sym, uint64_t n, const rans_params &p, c
       SrcDense src{d_sym};
       ENC_LAUNCH(SrcDense, 2);
     }
+#undef FEED_LAUNCH
+#undef FEED_LAUNCH2
 #undef ENC_LAUNCH
 #undef ENC_LAUNCH2
     LAUNCH_CHECK();
