@@ -304,8 +304,10 @@ struct FSinkU16 {
   uint16_t *out;
   static constexpr bool kNarrow = true;
   __device__ __forceinline__ uint32_t bits(uint32_t x, float, float, float) const { return x; }
+  // an ordinary store: D is read again by the next two kernels, which find it in the caches (31 MB of D, decode and
+  // expand of a 64 x 512 x 28 x 28 tensor at 6 bits: 58.6 us with non-temporal stores here, 51.2 us with these)
   __device__ __forceinline__ static void put(uint16_t *base, uint32_t byte_off, uint32_t b) {
-    __builtin_nontemporal_store((uint16_t)b, (uint16_t *)((uint8_t *)base + byte_off));
+    *(uint16_t *)((uint8_t *)base + byte_off) = (uint16_t)b;
   }
 };
 // Inverse of Eq. 6 fused into the decoder: x = s * (xhat - z), one value per symbol.
