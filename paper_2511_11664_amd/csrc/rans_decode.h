@@ -336,6 +336,8 @@ __device__ __forceinline__ uint4 load_block16(const uint8_t *in, uint64_t bytes,
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
+constexpr uint32_t kLeanBlkWords = 32, kLeanLine = 144;  // see LEAN below
+
 // Interleaved rANS decoder (Eq. 3-4), one stream per lane.
 //
 // Every work-group rebuilds the tables in LDS from the stored frequencies: F by a
@@ -360,15 +362,26 @@ __device__ __forceinline__ uint4 load_block16(const uint8_t *in, uint64_t bytes,
 // saves the unpacking of f - (a 2^M x 8 B table): one LDS access on the state's dependency chain.
 // The byte-per-slot table, the per-symbol table and the scan scratch are then only needed while the tables
 // are built; they live at tmp_off, which may alias the window (not yet in use at that time).
-template <class Sink, typename LutT, bool MUL24, int NT, bool WIDE>
+//
+// LEAN: the form for launches that leave the SIMDs with one or two waves, where the time is one wave's chain of
+// dependent instructions and not the chip's throughput.  Such a wave issues an instruction about every 4 cycles, waits
+// 60 for an LDS read and another 28 if a second read has to arrive as well.  So nothing runs under a branch, the next
+// table entry is requested as soon as the state is known, and everything else (the store, the word pointer, the word
+// after next, read one step before it can be needed) happens while that request is on its way; blocks are 32 words
+// and looked after every 32 steps, which takes the refill's fifty instructions out of the steps.  The table is at LDS
+// address 0, the windows (144 bytes a stream: the same word of all streams in 16 different banks) at win_off.
+// One chunk of 32 streams and 6240 rows: 504 -> 385 us; 31 chunks of 64 x 64: 11.6 -> 10.6 us; a step is 133 cycles, of
+// which 60 wait for the entry and about 20 each go into issuing the word read and the store beside it.
+template <class Sink, typename LutT, bool MUL24, int NT, bool WIDE, bool LEAN>
 __global__ __launch_bounds__(NT) void k_decode_fast(const uint8_t *in, uint64_t bytes, CtlRef ctl, uint32_t A,
                                                      uint32_t M, uint32_t S, uint32_t cs, uint32_t groups,
                                                      uint64_t len, uint64_t dir_off, uint64_t payload_off,
                                                      float x_min, float x_max, uint32_t q_bits, uint32_t tmp_off,
-                                                     uint32_t misc_off, HdrImage img, rans_header hdr,
+                                                     uint32_t misc_off, uint32_t win_off, HdrImage img, rans_header hdr,
                                                      rans_qinfo *qout, Sink sink) {
   extern __shared__ __align__(16) uint32_t l_mem[];
-  constexpr uint32_t kWinBytes = 32 * NT;             // 16-word window per stream, one 32-byte line each
+  constexpr uint32_t kWinBytes = LEAN ? 0 : 32 * NT;  // what precedes the tables: a 16-word window per stream, one 32-byte line each
+  constexpr uint32_t kBlkWords = LEAN ? kLeanBlkWords : 8, kPieces = kBlkWords / 8;  // words of a block, its 16-byte pieces
   constexpr uint32_t NW = NT / 64;                    // waves per work-group
   // this is the first kernel of the call: no status to look at yet; work-group 0 checks the header
   if (blockIdx.x == 0 && threadIdx.x < 64) dec_check_header(in, bytes, ctl, img, hdr, qout);
@@ -436,18 +449,30 @@ __global__ __launch_bounds__(NT) void k_decode_fast(const uint8_t *in, uint64_t 
   const uint32_t end16 = (uint32_t)(B0 - blk_base) + 2 * nw;  // stream end, in bytes from blk_base
   // bytes of the container from blk_base on (saturated): loads stay below this
   const uint64_t room = bytes > blk_base ? bytes - blk_base : 0;
-  const uint32_t lim16 = room > 0xffffffffull ? 0xffffffffu : (uint32_t)room;
-  auto load_block = [&](uint32_t off16) -> uint4 {  // 16 bytes at sp + off16; bytes past the end read as zero
-    if (off16 <= lim16 && lim16 - off16 >= 16) return *(const uint4 *)(sp + off16);
-    uint32_t w[4] = {0, 0, 0, 0};
-    for (uint32_t q = 0; q < 8; q++)
-      if ((uint64_t)off16 + 2 * q + 2 <= lim16) w[q >> 1] |= (uint32_t) * (const uint16_t *)(sp + off16 + 2 * q) << (16 * (q & 1));
-    return make_uint4(w[0], w[1], w[2], w[3]);
+  const uint32_t lim16 = (room > 0xffffffffull ? 0xffffffffu : (uint32_t)room) & ~1u;  // whole words
+  // 16 bytes at sp + off16; bytes past the end read as zero: a block that reaches past it is taken from further back
+  // (the container's header lies before) and moved down
+  auto load_block = [&](uint32_t off16) -> uint4 {
+    if (off16 + 16 <= lim16) return *(const uint4 *)(sp + off16);  // off16 is below 2^23
+    const uint32_t back = off16 + 16 - lim16;
+    uint4 q = make_uint4(0, 0, 0, 0);
+    if (back < 16) {
+      __builtin_memcpy(&q, sp + off16 - back, 16);
+      uint64_t lo = (uint64_t)q.x | ((uint64_t)q.y << 32), hi = (uint64_t)q.z | ((uint64_t)q.w << 32);
+      const uint32_t by = 8 * back;  // 16 .. 112
+      lo = by >= 64 ? hi >> (by - 64) : (lo >> by) | (hi << (64 - by));
+      hi = by >= 64 ? 0 : hi >> by;
+      q = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+    }
+    return q;
   };
-  uint4 q_first[2] = {make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0)};
+  uint4 q_first[2 * kPieces];
+#pragma unroll
+  for (uint32_t i = 0; i < 2 * kPieces; i++) q_first[i] = make_uint4(0, 0, 0, 0);
   if (live) {
-    q_first[0] = load_block(0);
-    if (16 < end16) q_first[1] = load_block(16);
+#pragma unroll
+    for (uint32_t i = 0; i < 2 * kPieces; i++)
+      if (i == 0 || 16 * i < end16) q_first[i] = load_block(16 * i);
   }
 
   // ---- tables
@@ -539,28 +564,37 @@ __global__ __launch_bounds__(NT) void k_decode_fast(const uint8_t *in, uint64_t 
     // store (the refill code is issued for the whole wave whenever any lane needs it, so its length counts
     // on every call), single words are read at 2 (n mod 16) inside the line.  rd9 is twice the number of the
     // next unread word.  The window starts at LDS address 0 (this kernel has no static LDS).
-    constexpr uint32_t RB = 2, LOG_RB = 1;
+    constexpr uint32_t RB = LEAN ? 1 : 2, LOG_RB = LEAN ? 0 : 1;
     if ((uint32_t)(uintptr_t)(lds_u16 *)l_mem != 0) {  // cannot happen without static LDS; the slot arithmetic relies on it
       set_status(ctl, RANS_ERR_HIP);
       return;
     }
-    const uint32_t colb = 32 * ((uint32_t)wave * 64 + (uint32_t)lane);
+    const uint32_t colb = LEAN ? win_off + kLeanLine * threadIdx.x : 32 * ((uint32_t)wave * 64 + (uint32_t)lane);
     auto wread = [&](uint32_t rd_scaled) -> uint32_t {  // word whose number times 2 is rd_scaled
-      return *(lds_u16 *)(uintptr_t)((rd_scaled & 31u) | colb);
+      if constexpr (LEAN) return *(lds_u16 *)(uintptr_t)(((rd_scaled & (2 * kBlkWords - 1)) << 1) + colb);
+      else return *(lds_u16 *)(uintptr_t)((rd_scaled & 31u) | colb);
+    };
+    auto wread_next = [&](uint32_t rd) -> uint32_t {  // LEAN: the word after word rd; the line's first word follows its last one again
+      return *(lds_u16 *)(uintptr_t)(((rd & (2 * kBlkWords - 1)) << 1) + colb + 2);
     };
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) u32x4 lds_u128;
-    auto store_block = [&](uint32_t b, const uint4 &q) {  // block b -> words 8 (b & 1) .. 8 (b & 1) + 7 of the line
-      *(lds_u128 *)(uintptr_t)(((b & 1u) * 16) | colb) = u32x4{q.x, q.y, q.z, q.w};
+    auto store_block = [&](uint32_t b, const uint4 *q) {  // block b -> the (b & 1)-th half of the line
+#pragma unroll
+      for (uint32_t i = 0; i < kPieces; i++)
+        *(lds_u128 *)(uintptr_t)(((b & 1u) * 2 * kBlkWords + 16 * i) + colb) = u32x4{q[i].x, q[i].y, q[i].z, q[i].w};
+      if (LEAN && !(b & 1u)) *(lds_u16 *)(uintptr_t)(4 * kBlkWords + colb) = (uint16_t)q[0].x;
     };
     // the first two blocks, requested before the table build
-    store_block(0, q_first[0]);
-    if (16 < end16) store_block(1, q_first[1]);
+    store_block(0, q_first);
+    if (2 * kBlkWords < end16) store_block(1, q_first + kPieces);
     uint32_t ldb = 2;              // next block to request
     uint32_t rd9 = pos0 * RB;      // RB times the number of the next unread word (counted from blk_base)
     uint32_t pend_b = 0;
     bool pending = false;
-    uint4 pend_q = make_uint4(0, 0, 0, 0);
+    uint4 pend_q[kPieces];
+#pragma unroll
+    for (uint32_t i = 0; i < kPieces; i++) pend_q[i] = make_uint4(0, 0, 0, 0);
     uint32_t wnext = wread(rd9);
     uint32_t s = s_stored;
     // The state is at least 2^16 before every symbol if it is at the start: a step leaves f (s >> M) + (slot - F)
@@ -580,14 +614,23 @@ __global__ __launch_bounds__(NT) void k_decode_fast(const uint8_t *in, uint64_t 
     // window once the block whose rows it takes (two blocks back) is read up.  Reading a block takes at
     // least 8 steps, so each block sees a call while it is being read: block b is requested during
     // block b - 2 at the latest and stored during block b - 1.
+    // LEAN calls it every 32 steps, with blocks of 32 words; the word after next that was read before the call is
+    // read again, since it may be the first one of the block stored here.
     auto refill = [&]() {
-      const uint32_t cur = rd9 >> (LOG_RB + 3);
+      const uint32_t cur = rd9 / (RB * kBlkWords);
       if (pending && pend_b <= cur + 1) {
         store_block(pend_b, pend_q);
         pending = false;
       }
-      if (!pending && ldb <= cur + 2 && ldb * 16 < end16) {
-        pend_q = load_block(ldb * 16);
+      if (!pending && ldb <= cur + 2 && ldb * 2 * kBlkWords < end16) {
+        const uint32_t off = ldb * 2 * kBlkWords;
+        if (off + 16 * kPieces <= lim16) {
+#pragma unroll
+          for (uint32_t i = 0; i < kPieces; i++) pend_q[i] = *(const uint4 *)(sp + off + 16 * i);
+        } else {
+#pragma unroll
+          for (uint32_t i = 0; i < kPieces; i++) pend_q[i] = load_block(off + 16 * i);
+        }
         pend_b = ldb;
         pending = true;
         ldb++;
@@ -625,16 +668,60 @@ __global__ __launch_bounds__(NT) void k_decode_fast(const uint8_t *in, uint64_t 
         wnext = wread(rd9);
       }
     };
-    uint64_t t = 0;
-    for (; t + 8 <= rows_full; t += 8) {
+    auto slot_entry = [&](uint32_t state) -> uint64_t {  // LEAN: the table entry of a state
+      if constexpr (WIDE) {
+        return *(lds_u64 *)(uintptr_t)((state << 3) & (mask << 3));
+      } else {
+        const uint32_t x = *(lds_lut *)(uintptr_t)((state & mask) * (uint32_t)sizeof(LutT));
+        return *(lds_u64 *)(uintptr_t)(tab_off + x * 8);
+      }
+    };
+    uint64_t e_ahead = LEAN ? slot_entry(s) : 0;
+    uint32_t wnext2 = 0, s_top = s >> M;  // LEAN: the word after wnext, the state without its slot
+    auto lean_step = [&]() {
+      const uint32_t ex = (uint32_t)e_ahead, ey = (uint32_t)(e_ahead >> 32);
+      uint32_t fx, bias;
+      if constexpr (!WIDE) {
+        fx = ex & 0xffffu;
+        bias = (s & mask) - (ex >> 16);
+      } else if constexpr (Sink::kNarrow) {
+        fx = ex;
+        bias = ey >> 16;
+      } else {
+        fx = ex & 0xffffu;
+        bias = ex >> 16;
+      }
+      const uint32_t v = (MUL24 ? __umul24(fx, s_top) : fx * s_top) + bias;
+      const bool low = v < kL;
+      s = low ? (v << 16) | wnext : v;
+      e_ahead = slot_entry(s);
+      __builtin_amdgcn_sched_barrier(0);  // the request goes out before anything else
+      s_top = s >> M;
+      wnext = low ? wnext2 : wnext;
+      rd9 += low ? 1u : 0u;
+      wnext2 = wread_next(rd9);
+      sink.put(ob, oi, ey);
+      oi += oi_step;
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto one = [&]() {
+      if constexpr (LEAN) lean_step();
+      else step();
+    };
+    auto top_up = [&]() {
       refill();
-#pragma unroll
-      for (int u = 0; u < 8; u++) step();
+      if constexpr (LEAN) wnext2 = wread_next(rd9);
+    };
+    uint64_t t = 0;
+    for (; t + kBlkWords <= rows_full; t += kBlkWords) {
+      top_up();
+#pragma unroll 8
+      for (uint32_t u = 0; u < kBlkWords; u++) one();
     }
     if (t < rows_full || j < rem_row) {
-      refill();
-      for (; t < rows_full; t++) step();
-      if (j < rem_row) step();
+      top_up();
+      for (; t < rows_full; t++) one();
+      if (j < rem_row) one();
     }
     const uint32_t rd = rd9 >> LOG_RB;
     bad |= s_low || s != kL || rd - pos0 != nw;

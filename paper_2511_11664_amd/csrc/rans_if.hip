@@ -139,6 +139,7 @@ inline uint32_t compute_units() {
 }
 
 constexpr uint32_t kDecWideGroupMinChunks = 192;
+constexpr uint32_t kDecLeanMaxWaves = 1024;  // decoding waves (64 streams) up to which the decoder takes its LEAN form
 constexpr uint32_t kExpandOwnSumMaxTiles = 4096;
 constexpr uint32_t kShortRowCols = 32;  // rows up to this length: k_csr_compact derives its row ends from a mask
 
@@ -504,12 +505,36 @@ int decode_common(const uint8_t *d_stream, size_t stream_bytes, const rans_heade
   const bool tmp_alias = tmp_b <= win_b;
   const bool lut_alias = !tmp_alias && lut_b <= win_b;
   const size_t lds_wide = win_b + wide_b + (tmp_alias ? 0 : (lut_alias ? tmp_b - lut_b : tmp_b));
-  const uint32_t tmp_off = (uint32_t)((tmp_alias || lut_alias) ? 0 : win_b + wide_b);
-  const uint32_t misc_off = (uint32_t)(lut_alias ? win_b + wide_b : 0);
+  uint32_t tmp_off = (uint32_t)((tmp_alias || lut_alias) ? 0 : win_b + wide_b);
+  uint32_t misc_off = (uint32_t)(lut_alias ? win_b + wide_b : 0);
   const size_t kLdsMax = 160 * 1024;
   // worth it when the table is shared by enough lanes: always up to 2^13 slots, at 2^14 only for 1024-lane groups
-  const bool use_wide = lds_wide <= kLdsMax && (M <= 13 || nt >= 512);
-  const size_t lds_fast = use_wide ? lds_wide : lds_two;
+  bool use_wide = lds_wide <= kLdsMax && (M <= 13 || nt >= 512);
+  size_t lds_fast = use_wide ? lds_wide : lds_two;
+  // Few waves on the chip, every work-group of them resident: the form with the shortest chain (LEAN in the kernel),
+  // table first, windows behind it.  Whole decompress calls, us, without / with it at 64 streams a chunk, M = 12: 256
+  // chunks of 128 rows 16.0 / 13.2, 768 chunks 17.6 / 15.1, 1024 chunks, of which a quarter waits, 18.5 / 25.2.  At
+  // M = 14 the entry per slot needs 128 KB and a longer build, which pays from about 128 rows: 256 chunks of 64 / 128 /
+  // 512 rows 12.4 / 17.6 / 49.7 with the two look-ups, 13.0 / 16.8 / 39.6 with the one.
+  const uint64_t n_wg_f = (uint64_t)h.n_chunks * groups_f;
+  const uint32_t n_cu_f = compute_units();
+  bool lean = nt == 256 && (uint64_t)h.n_chunks * ((S + 63) / 64) <= kDecLeanMaxWaves;
+  uint32_t win_off = 0;
+  if (lean) {
+    const size_t win_lean = kLeanLine * (size_t)(S < nt ? S : nt);
+    const bool wide_lean = M <= 13 || (n_wg_f <= n_cu_f && L.capw >= 128 && wide_b + win_lean + tmp_b <= kLdsMax);
+    const size_t tab_lean = wide_lean ? wide_b : align_up(tmp_b, 16);
+    const bool alias = wide_lean && tmp_b <= win_lean;  // the build's tables under the windows
+    const size_t lds_lean = tab_lean + align_up(win_lean, 16) + (wide_lean && !alias ? tmp_b : 0);
+    lean = lds_lean <= kLdsMax && n_wg_f <= n_cu_f * (kLdsMax / lds_lean);
+    if (lean) {
+      use_wide = wide_lean;
+      lds_fast = lds_lean;
+      win_off = (uint32_t)tab_lean;
+      tmp_off = (uint32_t)(alias ? tab_lean : tab_lean + align_up(win_lean, 16));
+      misc_off = 0;
+    }
+  }
   // the fast decoder indexes a chunk's outputs and words with 32-bit offsets
   const bool small_chunk = L.chunk_len_max < (1ull << 29) && L.capw < (1u << 20);
   if (lds_fast <= kLdsMax && small_chunk) {
@@ -540,10 +565,10 @@ int decode_common(const uint8_t *d_stream, size_t stream_bytes, const rans_heade
       const uint64_t dir_off = kHdrBytes + align_up((size_t)A * 2, 8);
 #define FDEC_ARGS                                                                                            \
   d_stream, (uint64_t)stream_bytes, ctl, A, M, S, h.p.chunk_syms, groups_f, h.len_d, dir_off, payload_off, h.x_min, \
-      h.x_max, h.p.q_bits, tmp_off, misc_off, img, h, d_qinfo
-#define FDEC_ONE(SINKT, LUTT, MULV, NTV, WIDEV, sinkv)                                                              \
+      h.x_max, h.p.q_bits, tmp_off, misc_off, win_off, img, h, d_qinfo
+#define FDEC_ONE(SINKT, LUTT, MULV, NTV, WIDEV, LEANV, sinkv)                                                      \
   do {                                                                                                             \
-    auto kfn = k_decode_fast<SINKT, LUTT, MULV, NTV, WIDEV>;                                                       \
+    auto kfn = k_decode_fast<SINKT, LUTT, MULV, NTV, WIDEV, LEANV>;                                                 \
     /* once per instantiation: allow dynamic LDS beyond the default 64 KB */                                       \
     static const hipError_t attr_rc =                                                                              \
         hipFuncSetAttribute((const void *)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);          \
@@ -552,9 +577,10 @@ int decode_common(const uint8_t *d_stream, size_t stream_bytes, const rans_heade
   } while (0)
 #define FDEC_NT(SINKT, LUTT, MULV, WIDEV, sinkv)                                                                   \
   do {                                                                                                             \
-    if (nt == 1024) FDEC_ONE(SINKT, LUTT, MULV, 1024, WIDEV, sinkv);                                               \
-    else if (nt == 512) FDEC_ONE(SINKT, LUTT, MULV, 512, WIDEV, sinkv);                                            \
-    else FDEC_ONE(SINKT, LUTT, MULV, 256, WIDEV, sinkv);                                                           \
+    if (nt == 1024) FDEC_ONE(SINKT, LUTT, MULV, 1024, WIDEV, false, sinkv);                                        \
+    else if (nt == 512) FDEC_ONE(SINKT, LUTT, MULV, 512, WIDEV, false, sinkv);                                     \
+    else if (lean) FDEC_ONE(SINKT, LUTT, MULV, 256, WIDEV, true, sinkv);                                           \
+    else FDEC_ONE(SINKT, LUTT, MULV, 256, WIDEV, false, sinkv);                                                    \
   } while (0)
 #define FDEC_LAUNCH(SINKT, LUTT, sinkv)                                                                            \
   do {                                                                                                             \
