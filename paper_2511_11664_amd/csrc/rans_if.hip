@@ -53,12 +53,12 @@ namespace {
 enum KernelId {
   KID_MINMAX = 0, KID_QINFO, KID_QUANT_HIST, KID_SCAN, KID_CSR_COMPACT, KID_CSR_ROWS,
   KID_NORMALIZE, KID_ENCODE, KID_CHUNK_SCAN, KID_GATHER, KID_DEC_PREPARE, KID_DECODE, KID_ROW_SCAN,
-  KID_CSR_EXPAND, KID_DEQUANT, KID_RS_MASK, KID_RS_COLS, KID_RS_ROWS, KID_RS_COST, KID_RS_ROWS_POW2, KID_COUNT
+  KID_CSR_EXPAND, KID_DEQUANT, KID_RS_MASK, KID_RS_COUNT, KID_RS_COST, KID_COUNT
 };
 const char *const kKernelNames[KID_COUNT] = {
     "k_minmax", "k_qinfo", "k_quant_hist", "k_scan_u32", "k_csr_compact", "k_csr_rows",
     "k_normalize", "k_encode", "k_chunk_scan", "k_gather", "k_dec_prepare", "k_decode", "k_row_part",
-    "k_csr_to_dense", "k_dequant", "k_rs_mask", "k_rs_cols", "k_rs_rows", "k_rs_cost", "k_rs_rows_pow2"};
+    "k_csr_to_dense", "k_dequant", "k_rs_mask", "k_rs_count", "k_rs_cost"};
 
 struct ProfRecord {
   int kid;
@@ -786,10 +786,9 @@ struct RsPlan {
   RsCands cands;
   RsOffsets offs;
   RsGroups grps;
-  RsPow2 pow2;    // candidates whose row counts k_rs_rows_pow2 takes from the mask
-  bool any_pow2;
-  uint32_t n_entries, n_tiles;
-  size_t mask16, lp, tile_cnt, zero0, hv, hl, hr, bad, costs, ticket, total;  // byte offsets in the workspace
+  RsGrid grid;
+  uint32_t n_tiles;
+  size_t mask, hv_part, zero0, hv, hl, hr, costs, ticket, total;  // byte offsets in the workspace
   uint32_t zero_words;
   bool too_many;
 };
@@ -822,30 +821,6 @@ RsPlan rs_plan(uint64_t n, uint32_t q_bits) {
     orr += P.cands.K[k] + 1u;
   }
   P.offs.hr[P.cands.n] = orr;
-  {  // work-groups of k_rs_rows: about kRowsGrid in all, shared out by the number of rows (K = 1 needs one)
-    constexpr uint64_t kRowsGrid = 4096;
-    // K = 1 has a closed form and K = 2, 4, 8, 16 a kernel of their own: no rows for k_rs_rows
-    auto rows_of = [&](uint32_t K) -> uint64_t { return (K == 1 || K == 2 || K == 4 || K == 8 || K == 16) ? 0 : n / K; };
-    for (uint32_t i = 0; i < 4; i++) P.pow2.hr_at[i] = ~0u;
-    for (uint32_t k = 0; k < P.cands.n; k++)
-      for (uint32_t i = 0; i < 4; i++)
-        if (P.cands.K[k] == (2u << i)) {
-          P.pow2.hr_at[i] = P.offs.hr[k];
-          P.any_pow2 = true;
-        }
-    uint64_t rows_all = 0;
-    for (uint32_t k = 0; k < P.cands.n; k++) rows_all += rows_of(P.cands.K[k]);
-    uint32_t w = 0;
-    for (uint32_t k = 0; k < P.cands.n; k++) {
-      P.offs.wg0[k] = w;
-      const uint64_t rows = rows_of(P.cands.K[k]);
-      const uint64_t need = (rows + 4 * 63 - 1) / (4 * 63);  // work-groups that have a row at all
-      uint64_t share = rows_all ? (rows * kRowsGrid + rows_all - 1) / rows_all : 1;
-      share = share > need ? need : share;
-      w += (uint32_t)((share < 1 && (rows || P.cands.K[k] == 1)) ? 1 : share);  // K = 1 keeps one work-group for its closed form
-    }
-    P.offs.wg0[P.cands.n] = w;
-  }
   // groups of consecutive candidates with a common multiple of at most kRsLcmMax (see RsGroups)
   uint32_t ol = 0;
   {
@@ -871,78 +846,81 @@ RsPlan rs_plan(uint64_t n, uint32_t q_bits) {
       P.grps.L[P.grps.n] = cur;
     }
     if (cur) P.grps.n++;
+    // a column count takes windows of 32 residues and works on up to 32 of them side by side: short periods are
+    // repeated until they fill that many windows, for small tensors fewer
+    const uint32_t want = n >= 1024 * 512 ? 1024u : n <= 32 * 512 ? 32u : (uint32_t)(n / 512);
+    uint32_t wg = 0;
     for (uint32_t g = 0; g < P.grps.n; g++) {
       uint32_t &L = P.grps.L[g];
-      if (L < 32) L *= (32 + L - 1) / L;  // the kernel's wrap-around assumes at least 32 residues
+      if (L < want) L *= (want + L - 1) / L;
       P.grps.off[g] = ol;
       ol += L;
+      P.grps.wg0[g] = wg;
+      wg += (L + 1023) / 1024 * (uint32_t)(((n + L - 1) / L + kRsColBlock - 1) / kRsColBlock);
     }
     P.grps.off[P.grps.n] = ol;
+    P.grps.wg0[P.grps.n] = P.grid.n_cols = wg;
   }
-  P.n_entries = (uint32_t)((n + 15) / 16);
+  const uint32_t n_words = (uint32_t)((n + 31) / 32);
   P.n_tiles = (uint32_t)((n + kRsTile - 1) / kRsTile);
+  // k_rs_mask: a work-group has two tiles at least, as zeroing and storing its counters cost about as much as a tile
+  P.grid.n_part = P.n_tiles * 13 / 32;
+  P.grid.n_part = P.grid.n_part < 1 ? 1 : P.grid.n_part > kRsMaskBlocks ? kRsMaskBlocks : P.grid.n_part;
+  P.grid.n_sum = (P.grid.n_part + 63) / 64;
+  // row counts: 128 words or more for a work-group, 256 work-groups at most
+  uint32_t rows = n_words / 128;
+  rows = rows < 1 ? 1 : rows > 256 ? 256 : rows;
+  P.grid.wg_words = ((n_words + rows - 1) / rows + 3) & ~3u;
+  P.grid.n_rows = P.cands.n ? (n_words + P.grid.wg_words - 1) / P.grid.wg_words : 0;
+  const uint32_t pieces = (P.grid.wg_words + kRsPiece - 1) / kRsPiece;
+  P.grid.piece = ((P.grid.wg_words + pieces - 1) / pieces + 3) & ~3u;
+  // LDS histograms: a counter per lane and bin while they fit 24 KB, then up to eight per bin in 16 KB
+  while (P.grid.n_wide < P.cands.n && P.offs.hr[P.grid.n_wide + 1] <= 24 * 4) P.grid.n_wide++;
+  while (P.grid.rep_log2 < 3 && (orr - P.offs.hr[P.grid.n_wide]) << (P.grid.rep_log2 + 3) <= 16 * 1024) P.grid.rep_log2++;
+  // copies of the row-count histograms, so that no address gets more than a few dozen additions; as many as fit
+  // beside hv_part in an eighth of a byte per symbol
+  P.offs.rep_stride = orr;
+  P.offs.n_rep = n >= 1ull << 22 ? 8 : 1;
+  while (P.offs.n_rep > 1 && (size_t)orr * P.offs.n_rep * 4 + P.grid.n_part * 1024 > n / 8) P.offs.n_rep /= 2;
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
     o = align_up(o + bytes, 256);
     return at;
   };
-  P.mask16 = take((size_t)P.n_entries * 2);
-  P.lp = take((size_t)P.n_entries * 2);
-  P.tile_cnt = take(((size_t)P.n_tiles + 1) * 4);
+  P.mask = take((size_t)n_words * 4);
+  P.hv_part = take((size_t)P.grid.n_part * 1024);
   P.zero0 = o;
   P.hv = take(256 * 4);
   P.hl = take((size_t)ol * 4 + 4);
-  P.hr = take((size_t)orr * 4 + 4);
-  P.bad = take(4);
-  P.costs = take(RANS_RESHAPE_MAX_CAND * 8);
-  P.ticket = take(4);
+  P.ticket = P.hl + (size_t)ol * 4;
+  P.hr = take((size_t)P.offs.rep_stride * P.offs.n_rep * 4);
   P.zero_words = (uint32_t)((o - P.zero0) / 4);
+  P.costs = take(RANS_RESHAPE_MAX_CAND * 8);
   P.total = o;
   return P;
 }
 
 int launch_search_reshape(const uint8_t *d_sym, uint64_t n, uint32_t q_bits, rans_reshape_result *d_res, uint8_t *ws,
                           const RsPlan &P, hipStream_t st) {
-  uint16_t *mask16 = (uint16_t *)(ws + P.mask16), *lp = (uint16_t *)(ws + P.lp);
-  uint32_t *tile_cnt = (uint32_t *)(ws + P.tile_cnt);
+  uint32_t *mask = (uint32_t *)(ws + P.mask), *hv_part = (uint32_t *)(ws + P.hv_part);
   uint32_t *hv = (uint32_t *)(ws + P.hv), *hl = (uint32_t *)(ws + P.hl), *hr = (uint32_t *)(ws + P.hr);
-  uint32_t *bad = (uint32_t *)(ws + P.bad);
-  hipLaunchKernelGGL(k_rs_zero, dim3(8), dim3(256), 0, st, (uint32_t *)(ws + P.zero0), P.zero_words);
+  PROF_LAUNCH(KID_RS_MASK, k_rs_mask, dim3(P.grid.n_part), dim3(kWG), 0, st, d_sym, (uint32_t)n, (int)aligned_to(d_sym, 16),
+              P.n_tiles, (uint16_t *)mask, hv_part, (uint32_t *)(ws + P.zero0), P.zero_words);
   LAUNCH_CHECK();
-  PROF_LAUNCH(KID_RS_MASK, k_rs_mask, dim3(P.n_tiles < 512 ? P.n_tiles : 512), dim3(kWG), 0, st, d_sym, (uint32_t)n,
-              (int)aligned_to(d_sym, 16), P.n_tiles, mask16, lp, tile_cnt, hv, q_bits, bad);
+  static const hipError_t attr_rc =
+      hipFuncSetAttribute((const void *)k_rs_count, hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024);
+  const size_t wide = P.offs.hr[P.grid.n_wide], bins = P.offs.hr[P.cands.n];
+  const size_t lds = 4 * kRsWG * sizeof(uint2) + ((wide << 6) + ((bins - wide) << P.grid.rep_log2)) * 4;
+  if (lds > 64 * 1024 && attr_rc != hipSuccess) return RANS_ERR_HIP;
+  PROF_LAUNCH(KID_RS_COUNT, k_rs_count, dim3(P.grid.n_rows + P.grid.n_cols + P.grid.n_sum), dim3(kRsWG), lds, st,
+              mask, (uint32_t)n, P.cands, P.offs, P.grps, P.grid, hv_part, hv, hl, hr);
   LAUNCH_CHECK();
-  PROF_LAUNCH(KID_SCAN, k_scan_u32, dim3(1), dim3(kBig), 0, st, tile_cnt, P.n_tiles);
-  LAUNCH_CHECK();
-  {
-    static const hipError_t attr_rc = hipFuncSetAttribute((const void *)k_rs_cols, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                          kRsLcmMax * 4);
-    if (attr_rc != hipSuccess) return RANS_ERR_HIP;
-    const uint32_t n_cu = compute_units();
-    const uint32_t g_e = grid_for((P.n_entries + 7) / 8, kWG, n_cu ? n_cu : 256);  // one work-group per compute unit
-    for (uint32_t g = 0; g < P.grps.n; g++) {
-      PROF_LAUNCH(KID_RS_COLS, k_rs_cols, dim3(g_e), dim3(kWG), P.grps.L[g] * 4, st, mask16, P.n_entries, P.grps.L[g],
-                  hl + P.grps.off[g]);
-      LAUNCH_CHECK();
-    }
-  }
-  if (P.any_pow2) {
-    const uint32_t n_cu = compute_units();
-    PROF_LAUNCH(KID_RS_ROWS_POW2, k_rs_rows_pow2, dim3(grid_for((P.n_entries + 7) / 8, kWG, n_cu ? n_cu : 256)), dim3(kWG), 0, st,
-                mask16, P.n_entries, (uint32_t)n, P.pow2, hr);
-    LAUNCH_CHECK();
-  }
-  if (P.cands.n && P.offs.wg0[P.cands.n]) {
-    PROF_LAUNCH(KID_RS_ROWS, k_rs_rows, dim3(P.offs.wg0[P.cands.n]), dim3(kWG), 0, st, mask16, lp, tile_cnt,
-                (uint32_t)n, P.n_tiles, P.cands, P.offs, hr);
-    LAUNCH_CHECK();
-  }
   if (P.cands.n)
-    PROF_LAUNCH(KID_RS_COST, k_rs_cost, dim3(P.cands.n), dim3(kWG), 0, st, P.cands, (uint32_t)n, P.n_tiles, q_bits, tile_cnt, hv, hl,
-                hr, P.offs, P.grps, bad, (double *)(ws + P.costs), (uint32_t *)(ws + P.ticket), d_res);
+    PROF_LAUNCH(KID_RS_COST, k_rs_cost, dim3(P.cands.n), dim3(kRsWG), 0, st, P.cands, (uint32_t)n, q_bits, hv, hl, hr, P.offs,
+                P.grps, (double *)(ws + P.costs), (uint32_t *)(ws + P.ticket), d_res);
   else
-    hipLaunchKernelGGL(k_rs_empty, dim3(1), dim3(1), 0, st, (uint32_t)n, bad, d_res);
+    hipLaunchKernelGGL(k_rs_empty, dim3(1), dim3(kWG), 0, st, (uint32_t)n, q_bits, hv, d_res);
   LAUNCH_CHECK();
   return RANS_OK;
 }

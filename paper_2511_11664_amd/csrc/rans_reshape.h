@@ -9,170 +9,216 @@ namespace {
 
 // ------------------------------------------------------------------ kernels: reshape search (Sec. 3.2)
 
-// The quantised tensor is fixed over all reshapes [N, K]: so are the nonzero values v and their
-// number.  Only the histograms of the column indices (position mod K) and of the row counts change.
-// One pass turns the tensor into a zero mask (16 positions per entry), the number of nonzeros
-// before each entry inside its tile, the tile totals and the histogram of v; everything else is
-// computed from those.
-constexpr uint32_t kRsTile = kWG * 16;
+// The quantised tensor is fixed over all reshapes [N, K]: so are the nonzero values v and their number.  Only the
+// histograms of the column indices (position mod K) and of the row counts change, and both follow from the zero mask
+// alone.  Three launches: k_rs_mask reads the tensor once (mask, histogram of v), k_rs_count makes every histogram
+// from the mask, an eighth of the tensor, and k_rs_cost sums the entropies and walks the candidates.
+// Measured, the former seven launches (mask, scan of its tile counts, columns by an LDS addition per nonzero, rows by
+// look-ups in a prefix array, costs) against these: 25.7 M symbols with 18 candidates 142 -> 38 us of kernels
+// (10 + 19 + 9), 100 352 symbols with 12 candidates 37 -> 25 us.
+constexpr uint32_t kRsTile = kWG * 16;       // symbols of a step of k_rs_mask
+constexpr uint32_t kRsMaskBlocks = 1024;    // its work-groups at most: 16 waves on a compute unit
+constexpr uint32_t kRsWG = 1024;             // threads of k_rs_count and k_rs_cost
+constexpr uint32_t kRsColRows = 16;          // rows a thread of the column counts adds up bit by bit (5 planes)
+constexpr uint32_t kRsColBlock = (kRsWG / 32) * kRsColRows;  // rows of a work-group of the column counts
+constexpr uint32_t kRsHalo = 9;              // words behind a piece: a row that starts in it ends at most 255 positions on
+constexpr uint32_t kRsPiece = 4 * kRsWG - 12;  // mask words of a piece of the row counts (a multiple of 4)
+static_assert(kRsPiece + kRsHalo <= 4 * kRsWG && kRsPiece % 4 == 0, "four words a thread");
 struct RsCands {
   uint32_t n;
   uint16_t K[RANS_RESHAPE_MAX_CAND];
 };
 struct RsOffsets {  // first bin of each candidate's row-count histogram; entry n = total
   uint32_t hr[RANS_RESHAPE_MAX_CAND + 1];
-  // first work-group of each candidate in the grid of k_rs_rows (shares in proportion to the number of rows, so
-  // that the candidates with the shortest rows do not run on alone at the end); entry n = the grid
-  uint32_t wg0[RANS_RESHAPE_MAX_CAND + 1];
+  uint32_t rep_stride, n_rep;  // partial histograms: work-group b of the row counts adds to copy b % n_rep
 };
 // Candidates are grouped so that the members of a group have a common multiple L of at most kRsLcmMax: one
 // histogram of the nonzero positions modulo L then serves every member, whose own column histogram
 // (positions modulo K) is that one folded K-periodically.
-constexpr uint32_t kRsLcmMax = 32768;  // LDS words of k_rs_cols
+constexpr uint32_t kRsLcmMax = 32768;
 struct RsGroups {
   uint32_t n;
-  uint32_t L[RANS_RESHAPE_MAX_CAND];        // residues of group g: a multiple of every K in it, at least 16
+  uint32_t L[RANS_RESHAPE_MAX_CAND];        // residues of group g: a multiple of every K in it
   uint32_t off[RANS_RESHAPE_MAX_CAND + 1];  // first word of its histogram in hl; entry n = total
+  uint32_t wg0[RANS_RESHAPE_MAX_CAND + 1];  // its first work-group among the column counts' ones; entry n = their number
   uint8_t of[RANS_RESHAPE_MAX_CAND];        // group of candidate k
 };
+struct RsGrid {  // shares of the grid of k_rs_count, in this order: row counts, column counts, sums of hv_part
+  uint32_t n_rows, n_cols, n_sum;
+  uint32_t n_part;      // partial histograms of v
+  uint32_t wg_words;    // mask words of a work-group of the row counts (a multiple of 4), its pieces' size below
+  uint32_t piece;
+  // copies of a bin in the row counts' LDS histogram: one per lane for the first n_wide candidates, the ones with the
+  // most rows and the fewest bins, 1 << rep_log2 for the others
+  uint32_t n_wide, rep_log2;
+};
 
+// Zero mask and histogram of v.  Bound by the LDS additions of the nonzeros (one each), so the grid fills the chip with
+// waves.  A work-group stores its histogram whole: a thousand work-groups' additions to the same 256
+// addresses take 12 us at the end of the kernel.  25.7 M symbols, 30 % nonzeros: 31 us with 512 work-groups, a branch
+// per symbol and a scan per tile, now 10 us (2.8 TB/s).
 __global__ __launch_bounds__(kWG) void k_rs_mask(const uint8_t *sym, uint32_t n, int aligned, uint32_t n_tiles,
-                                                 uint16_t *mask16, uint16_t *lp, uint32_t *tile_cnt, uint32_t *hv,
-                                                 uint32_t q_bits, uint32_t *bad_flag) {
-  __shared__ uint32_t sh[kWG / 64];
+                                                 uint16_t *mask16, uint32_t *hv_part, uint32_t *zero, uint32_t zero_words) {
   // eight counters per value, one per lane residue: activations have a few very frequent values, and a wave's
   // additions to one LDS address are performed one after the other
   __shared__ uint32_t h[256 * 8];
   for (uint32_t i = threadIdx.x; i < 256 * 8; i += kWG) h[i] = 0;
+  // what the next kernel adds to
+  for (uint32_t i = blockIdx.x * kWG + threadIdx.x; i < zero_words; i += gridDim.x * kWG) zero[i] = 0;
   const uint32_t rep = threadIdx.x & 7u;
   __syncthreads();
-  uint8_t b[16];
-  if (blockIdx.x < n_tiles) load16(sym, (uint64_t)blockIdx.x * kRsTile + threadIdx.x * 16, n, aligned, b);
+  const uint32_t n_entries = 2 * ((n + 31) / 32);  // whole words
+  uint32_t w[4];
+  load16w(sym, (uint64_t)blockIdx.x * kRsTile + threadIdx.x * 16, n, aligned, w);  // the grid has at most n_tiles work-groups
   for (uint32_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
     const uint64_t e0 = (uint64_t)tile * kRsTile + threadIdx.x * 16;
-    uint8_t nb[16];  // the next tile's symbols are on their way while this one is looked at
-    const bool more = tile + gridDim.x < n_tiles;
-    if (more) load16(sym, e0 + (uint64_t)gridDim.x * kRsTile, n, aligned, nb);
-    uint32_t m = 0;
+    uint32_t nw[4] = {0, 0, 0, 0};  // the next tile's symbols are on their way while this one is looked at
+    if (tile + gridDim.x < n_tiles) load16w(sym, e0 + (uint64_t)gridDim.x * kRsTile, n, aligned, nw);
+    if ((e0 >> 4) < n_entries) mask16[e0 >> 4] = (uint16_t)nonzero_mask16(w);
 #pragma unroll
     for (int k = 0; k < 16; k++) {
-      if (b[k]) {
-        m |= 1u << k;
-        if (b[k] >> q_bits) atomicOr(bad_flag, 1u);  // not a symbol of this bit width
-        atomicAdd(&h[b[k] * 8u + rep], 1u);
-      }
+      const uint32_t b = (w[k >> 2] >> (8 * (k & 3))) & 0xffu;
+      if (b) atomicAdd(&h[b * 8u + rep], 1u);
     }
-    uint32_t tot;
-    const uint32_t ex = block_excl_scan<kWG>(__popc(m), sh, &tot);
-    if (e0 < n) {
-      mask16[e0 >> 4] = (uint16_t)m;
-      lp[e0 >> 4] = (uint16_t)ex;
-    }
-    if (threadIdx.x == 0) tile_cnt[tile] = tot;
-    if (more) {
 #pragma unroll
-      for (int k = 0; k < 16; k++) b[k] = nb[k];
-    }
-    __syncthreads();
+    for (int j = 0; j < 4; j++) w[j] = nw[j];
   }
+  __syncthreads();
   uint32_t t = 0;  // kWG == 256: a thread per value
 #pragma unroll
   for (int r = 0; r < 8; r++) t += h[threadIdx.x * 8 + r];
-  if (t) atomicAdd(&hv[threadIdx.x], t);
+  hv_part[(size_t)blockIdx.x * 256 + threadIdx.x] = t;
 }
 
-// zeroes the histograms of a call (runs before k_rs_mask, which adds to hv)
-__global__ void k_rs_zero(uint32_t *p, uint32_t words) {
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < words; i += gridDim.x * blockDim.x) p[i] = 0;
-}
-
-// Histogram of the nonzero positions modulo L (one group of candidates; see RsGroups), in LDS and then added
-// to hl.  A thread takes eight consecutive mask entries (128 positions) with one load and walks their set bits.
-__global__ __launch_bounds__(kWG) void k_rs_cols(const uint16_t *mask16, uint32_t n_entries, uint32_t L, uint32_t *hl) {
-  extern __shared__ uint32_t h_l[];
-  for (uint32_t i = threadIdx.x; i < L; i += kWG) h_l[i] = 0;
+// Histogram of the nonzero positions modulo L (one group of candidates; see RsGroups), bit-sliced: a thread takes the
+// 32 residues 32 w .. 32 w + 31, reads their bits in one row of L positions after the other - a 32-bit window at any
+// bit position - and adds them up in 32 vertical counters, five bit planes for up to kRsColRows rows: about 20
+// instructions per 32 positions whatever the density, where a walk over the set bits with an LDS addition each took
+// 25 us on 25.7 M symbols with 30 % nonzeros.  A work-group is 32 windows by 32 interleaved rows.
+__device__ __forceinline__ void rs_count_cols(const uint32_t *mask, uint32_t n, uint32_t L, uint32_t bx, uint32_t *hl,
+                                              uint32_t *s_c /* 32 * 33 words */) {
+  const uint32_t n_words = (n + 31) / 32;
+  const uint32_t W = (L + 31) / 32, n_wb = (W + 31) / 32, R = (n + L - 1) / L;
+  const uint32_t wx = bx % n_wb, rb = bx / n_wb;
+  const uint32_t wl = threadIdx.x & 31u, w = wx * 32 + wl;
+  const uint32_t r0 = rb * kRsColBlock + (threadIdx.x >> 5);
+  for (uint32_t i = threadIdx.x; i < 32 * 33; i += kRsWG) s_c[i] = 0;
   __syncthreads();
-  const uint32_t n_oct = (n_entries + 7) / 8;
-  const uint32_t stride = gridDim.x * kWG;
-  const uint32_t step = (uint32_t)(((uint64_t)stride * 128) % L);  // positions between a thread's octets, modulo L
-  uint32_t c = (uint32_t)(((uint64_t)(blockIdx.x * kWG + threadIdx.x) * 128) % L);
-  for (uint32_t o = blockIdx.x * kWG + threadIdx.x; o < n_oct; o += stride) {
-    uint32_t w[4];
-    if (8 * o + 8 <= n_entries) {  // the mask array starts 256-byte aligned
-      const uint4 q = *(const uint4 *)(mask16 + 8 * (size_t)o);
-      w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
-    } else {
+  if (w < W && r0 < R) {
+    const uint32_t keep = L - 32 * w >= 32 ? ~0u : (1u << (L - 32 * w)) - 1u;  // the next row's bits are not this window's
+    uint32_t p[5] = {0, 0, 0, 0, 0};
+    // two rounds of eight rows, the loads of a round in flight together (n <= 2^30: no overflow)
+#pragma unroll 1
+    for (uint32_t r1 = r0; r1 < r0 + kRsColRows * (kRsWG / 32) && r1 < R; r1 += 8 * (kRsWG / 32)) {
+      uint32_t lo[8], hi[8];
 #pragma unroll
-      for (int j = 0; j < 4; j++) {
-        const uint32_t e = 8 * o + 2 * j;
-        w[j] = (e < n_entries ? mask16[e] : 0u) | ((e + 1 < n_entries ? (uint32_t)mask16[e + 1] : 0u) << 16);
+      for (uint32_t u = 0; u < 8; u++) {
+        const uint32_t r = r1 + u * (kRsWG / 32), at = (r * L + 32 * w) >> 5;
+        const bool a = r < R && at < n_words, b = r < R && at + 1 < n_words;
+        lo[u] = mask[a ? at : 0];  // always a load, so that none hides behind a branch
+        hi[u] = mask[b ? at + 1 : 0];
+        lo[u] = a ? lo[u] : 0u;
+        hi[u] = b ? hi[u] : 0u;
       }
-    }
-    uint32_t cj = c;  // residue of the first position of the word at hand
 #pragma unroll
-    for (int j = 0; j < 4; j++) {
-      uint32_t m = w[j];
-      while (m) {
-        const uint32_t bit = (uint32_t)__ffs((int)m) - 1u;
-        m &= m - 1u;
-        uint32_t pos = cj + bit;  // < 2 L as L >= 32
-        pos = pos >= L ? pos - L : pos;
-        atomicAdd(&h_l[pos], 1u);
-      }
-      cj += 32;
-      cj = cj >= L ? cj - L : cj;
-    }
-    c += step;
-    c = c >= L ? c - L : c;
-  }
-  __syncthreads();
-  for (uint32_t i = threadIdx.x; i < L; i += kWG) {
-    const uint32_t t = h_l[i];
-    if (t) atomicAdd(&hl[i], t);
-  }
-}
-
-// Row-count histograms of the candidates K = 2, 4, 8, 16 (those of them in the domain: hr_at[i] is the first bin of
-// K = 2 << i, ~0 for none), straight from the zero mask: such rows are K-bit fields of a mask word, and their
-// counts are population counts of the fields - taken for all fields of a 32-position word at once, with word
-// operations for K = 2 and 4 (how many fields hold 1, 2, ... set bits) and per field for K = 8 and 16.  These
-// candidates have the most rows; k_rs_rows, which looks up two prefix counts per row, is left with the others.
-struct RsPow2 {
-  uint32_t hr_at[4];
-};
-__global__ __launch_bounds__(kWG) void k_rs_rows_pow2(const uint16_t *mask16, uint32_t n_entries, uint32_t n, RsPow2 at,
-                                                      uint32_t *hr) {
-  __shared__ uint32_t s_h[4][17 * 8];  // eight counters per value, one per lane residue
-  for (uint32_t i = threadIdx.x; i < 4 * 17 * 8; i += kWG) (&s_h[0][0])[i] = 0;
-  __syncthreads();
-  const uint32_t rp = threadIdx.x & 7u;
-  const uint32_t n_oct = (n_entries + 7) / 8;
-  uint32_t c2[3] = {0, 0, 0}, c4[5] = {0, 0, 0, 0, 0};
-  for (uint32_t o = blockIdx.x * kWG + threadIdx.x; o < n_oct; o += gridDim.x * kWG) {
-    uint32_t w[4];
-    if (8 * o + 8 <= n_entries) {
-      const uint4 q = *(const uint4 *)(mask16 + 8 * (size_t)o);
-      w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
-    } else {
+      for (uint32_t u = 0; u < 8; u++) {
+        uint32_t x = __builtin_amdgcn_alignbit(hi[u], lo[u], ((r1 + u * (kRsWG / 32)) * L) & 31u) & keep;
 #pragma unroll
-      for (int j = 0; j < 4; j++) {
-        const uint32_t e = 8 * o + 2 * j;
-        w[j] = (e < n_entries ? mask16[e] : 0u) | ((e + 1 < n_entries ? (uint32_t)mask16[e + 1] : 0u) << 16);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const uint64_t p0 = ((uint64_t)o * 4 + j) * 32;  // first position of the word
-      const uint32_t m = w[j];
-      if (p0 + 32 <= n) {  // all of the word's rows exist (n is a multiple of every K here)
-        if (at.hr_at[0] != ~0u) {
-          const uint32_t x = m & 0x55555555u, y = (m >> 1) & 0x55555555u;
-          const uint32_t two = (uint32_t)__popc(x & y), one = (uint32_t)__popc(x ^ y);
-          c2[2] += two; c2[1] += one; c2[0] += 16u - two - one;
+        for (int j = 0; j < 5; j++) {
+          const uint32_t c = p[j] & x;
+          p[j] ^= x;
+          x = c;
         }
+      }
+    }
+#pragma unroll 2  // short code: straight-line code that runs once is waited for line by line
+    for (uint32_t b = 0; b < 32; b++) {
+      uint32_t c = 0;
+#pragma unroll
+      for (int j = 0; j < 5; j++) c |= ((p[j] >> b) & 1u) << j;
+      atomicAdd(&s_c[b * 33 + wl], c);
+    }
+  }
+  __syncthreads();
+  {
+    const uint32_t i = threadIdx.x;  // kRsWG == 32 * 32
+    const uint32_t t = s_c[(i & 31u) * 33 + (i >> 5)], at = wx * 1024 + i;
+    if (t && at < L) atomicAdd(&hl[at], t);
+  }
+}
+
+// Row-count histograms of all candidates over one range of mask words, every row counted where it starts.  The range
+// is taken in pieces of up to kRsPiece words, which go to LDS with the number of nonzeros before each word, so a row's
+// count is a population count of one window (K <= 32) or the difference of two look-ups: no pass over memory per
+// candidate, no prefix array, no scan over the tensor.  K = 2 and 4 - the most rows - are counted for the whole word at
+// a time in registers, 8 and 16 as fields of a word.  K = 1 is left out: its row counts are the zero mask itself.
+// One work-group per compute unit: every work-group ends with additions to some hundred addresses, and they cost more
+// than the counting when there are a thousand work-groups.  A short row's count takes few values, so the
+// additions of a wave meet in one bin: the candidates with short rows have a counter per lane, summed by a wave scan
+// before neighbouring bins leave together (a lone lane's addition per bin instead: 14 us more on 25.7 M symbols).
+__device__ __forceinline__ void rs_count_rows(const uint32_t *mask, uint32_t n, const RsCands &cands, const RsOffsets &offs,
+                                              const RsGrid &gr, uint32_t bx, uint32_t *hr, uint2 *s_wp /* 4 kRsWG */,
+                                              uint32_t *s_h, uint32_t *sh, uint4 *s_cand) {
+  const uint32_t n_words = (n + 31) / 32;
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const uint32_t bins = offs.hr[cands.n], wide = offs.hr[gr.n_wide], rl = gr.rep_log2;
+  uint32_t *s_n = s_h + (wide << 6) - (wide << rl);  // bin b >= wide has its copies at s_n[b << rl]
+  for (uint32_t i = threadIdx.x; i < (wide << 6) + ((bins - wide) << rl); i += kRsWG) s_h[i] = 0;
+  uint32_t at2 = ~0u, at4 = ~0u, at8 = ~0u, at16 = ~0u;  // first bins of K = 2, 4, 8, 16 where they are candidates
+  for (uint32_t k = 0; k < cands.n && cands.K[k] <= 16; k++) {
+    const uint32_t K = cands.K[k];
+    if (K == 2) at2 = offs.hr[k];
+    if (K == 4) at4 = offs.hr[k];
+    if (K == 8) at8 = offs.hr[k];
+    if (K == 16) at16 = offs.hr[k];
+  }
+  auto slot = [&](uint32_t bin) {  // uniform choice: `bin` is any bin of one candidate
+    return bin < wide ? s_h + (bin << 6) + lane : s_n + (bin << rl) + (lane & ((1u << rl) - 1u));
+  };
+  uint32_t *const s8 = slot(at8 == ~0u ? 0 : at8), *const s16 = slot(at16 == ~0u ? 0 : at16);
+  const uint32_t l8 = at8 < wide ? 6 : rl, l16 = at16 < wide ? 6 : rl;
+  uint32_t c2[3] = {0, 0, 0}, c4[5] = {0, 0, 0, 0, 0};
+  const uint32_t g0 = bx * gr.wg_words, g1 = g0 + gr.wg_words < n_words ? g0 + gr.wg_words : n_words;
+  for (uint32_t w0 = g0; w0 < g1; w0 += gr.piece) {
+    const uint32_t w1 = w0 + gr.piece < g1 ? w0 + gr.piece : g1;
+    const uint32_t at = w0 + 4 * threadIdx.x;
+    uint32_t w[4] = {0, 0, 0, 0};
+    if (at < w1 + kRsHalo) {
+      if (at + 4 <= n_words) {  // the mask starts 256-byte aligned, `at` is a multiple of 4
+        const uint4 q = *(const uint4 *)(mask + at);
+        w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
+      } else {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; j++) w[j] = at + j < n_words ? mask[at + j] : 0u;
+      }
+    }
+    // every candidate's rows of this piece - their number, the first one's position, K, the first bin - by a thread each:
+    // the two divisions, made by every wave for every candidate, were half of the kernel's instructions
+    if (threadIdx.x < cands.n) {
+      const uint32_t K = cands.K[threadIdx.x], s = w0 * 32, e = w1 * 32 < n ? w1 * 32 : n;
+      const uint32_t i0 = (s + K - 1) / K, i1 = (e + K - 1) / K;
+      const bool other = K <= 16 && (K & (K - 1)) == 0;  // K = 1, 2, 4, 8, 16
+      s_cand[threadIdx.x] = make_uint4(other ? 0u : i1 - i0, i0 * K - s, K, offs.hr[threadIdx.x]);
+    }
+    uint32_t tot;
+    uint32_t ex = block_excl_scan<kRsWG>(__popc(w[0]) + __popc(w[1]) + __popc(w[2]) + __popc(w[3]), sh, &tot);
+#pragma unroll
+    for (uint32_t j = 0; j < 4; j++) {
+      s_wp[4 * threadIdx.x + j] = make_uint2(w[j], ex);
+      ex += __popc(w[j]);
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t j = 0; j < 4; j++) {
+      if (at + j >= w1) continue;
+      const uint32_t p0 = (at + j) * 32, m = s_wp[4 * threadIdx.x + j].x;
+      if (p0 + 32 <= n) {  // all of the word's rows exist (n is a multiple of every K here)
+        const uint32_t x = m & 0x55555555u, y = (m >> 1) & 0x55555555u;
+        const uint32_t two = (uint32_t)__popc(x & y), one = (uint32_t)__popc(x ^ y);
+        c2[2] += two; c2[1] += one; c2[0] += 16u - two - one;
         uint32_t t = m - ((m >> 1) & 0x55555555u);
         t = (t & 0x33333333u) + ((t >> 2) & 0x33333333u);  // eight fields of four bits: their population counts (0 .. 4)
-        if (at.hr_at[1] != ~0u) {
+        if (at4 != ~0u) {
           uint32_t rest = 8;
 #pragma unroll
           for (uint32_t v = 1; v <= 4; v++) {
@@ -184,178 +230,178 @@ __global__ __launch_bounds__(kWG) void k_rs_rows_pow2(const uint16_t *mask16, ui
           }
           c4[0] += rest;
         }
-        if (at.hr_at[2] != ~0u) {
+        if (at8 != ~0u) {
           const uint32_t b = (t + (t >> 4)) & 0x0f0f0f0fu;  // four fields of eight bits
 #pragma unroll
-          for (int f = 0; f < 4; f++) atomicAdd(&s_h[2][((b >> (8 * f)) & 0xffu) * 8 + rp], 1u);
+          for (int f = 0; f < 4; f++) atomicAdd(s8 + (((b >> (8 * f)) & 0xffu) << l8), 1u);
         }
-        if (at.hr_at[3] != ~0u) {
-          atomicAdd(&s_h[3][(uint32_t)__popc(m & 0xffffu) * 8 + rp], 1u);
-          atomicAdd(&s_h[3][(uint32_t)__popc(m >> 16) * 8 + rp], 1u);
+        if (at16 != ~0u) {
+          atomicAdd(s16 + ((uint32_t)__popc(m & 0xffffu) << l16), 1u);
+          atomicAdd(s16 + ((uint32_t)__popc(m >> 16) << l16), 1u);
         }
-      } else if (p0 < n) {  // the word with the end of the tensor: row by row
-#pragma unroll
+      } else {  // the word with the end of the tensor: row by row
+#pragma unroll 1
         for (uint32_t i = 0; i < 4; i++) {
-          if (at.hr_at[i] == ~0u) continue;
-          const uint32_t K = 2u << i;
+          const uint32_t first = i == 0 ? at2 : i == 1 ? at4 : i == 2 ? at8 : at16, K = 2u << i;
+          if (first == ~0u) continue;
           for (uint32_t q = 0; q < 32 && p0 + q < n; q += K)
-            atomicAdd(&s_h[i][(uint32_t)__popc((m >> q) & ((1u << K) - 1u)) * 8 + rp], 1u);
+            atomicAdd(slot(first + (uint32_t)__popc((m >> q) & ((1u << K) - 1u))), 1u);
         }
       }
     }
-  }
-#pragma unroll
-  for (uint32_t v = 0; v < 3; v++)
-    if (c2[v]) atomicAdd(&s_h[0][v * 8 + rp], c2[v]);
-#pragma unroll
-  for (uint32_t v = 0; v < 5; v++)
-    if (c4[v]) atomicAdd(&s_h[1][v * 8 + rp], c4[v]);
-  __syncthreads();
-  if (threadIdx.x < 4 * 17) {
-    const uint32_t i = threadIdx.x / 17, v = threadIdx.x % 17;
-    if (at.hr_at[i] != ~0u && v <= (2u << i)) {
-      uint32_t t = 0;
-#pragma unroll
-      for (int q = 0; q < 8; q++) t += s_h[i][v * 8 + q];
-      if (t) atomicAdd(&hr[at.hr_at[i] + v], t);
-    }
-  }
-}
-
-// nonzeros before position g (g <= n)
-__device__ __forceinline__ uint32_t rs_prefix(uint32_t g, uint32_t n, uint32_t nnz, const uint16_t *mask16,
-                                              const uint16_t *lp, const uint32_t *tile_off) {
-  if (g >= n) return nnz;
-  const uint32_t e = g >> 4;
-  return tile_off[g / kRsTile] + lp[e] + __popc((uint32_t)mask16[e] & ((1u << (g & 15)) - 1u));
-}
-
-// Histogram of the row counts r of one candidate (the work-group's, see RsOffsets): r[i] = prefix((i + 1) K) - prefix(i K).  A wave
-// takes 63 consecutive rows: lane l looks up the prefix at the start of row l of them (lane 63: the end of the
-// last), and a row's count is the neighbouring lane's prefix minus the lane's own - one look-up per row.
-__global__ __launch_bounds__(kWG) void k_rs_rows(const uint16_t *mask16, const uint16_t *lp, const uint32_t *tile_off,
-                                                 uint32_t n, uint32_t n_tiles, RsCands cands, RsOffsets offs,
-                                                 uint32_t *hr) {
-  __shared__ uint32_t h[257];
-  const uint32_t *hr_off = offs.hr;
-  uint32_t k = 0;
-  while (k + 1 < cands.n && offs.wg0[k + 1] <= blockIdx.x) k++;  // uniform; at most a hundred steps
-  const uint32_t K = cands.K[k];
-  const uint32_t bx = blockIdx.x - offs.wg0[k], gx = offs.wg0[k + 1] - offs.wg0[k];
-  const uint32_t nnz = tile_off[n_tiles];
-  uint32_t *out = hr + hr_off[k];
-  if (K == 1) {  // the row counts are the zero mask itself
-    if (bx == 0 && threadIdx.x == 0) {
-      out[0] = n - nnz;
-      out[1] = nnz;
-    }
-    return;
-  }
-  for (uint32_t i = threadIdx.x; i <= K; i += kWG) h[i] = 0;
-  __syncthreads();
-  const uint32_t N = n / K;
-  const uint32_t lane = threadIdx.x & 63;
-  if (K < 16) {
-    // Short rows that are not aligned fields of a mask word (K = 7, 14, ...): a row's count is the population
-    // count of K bits of a 32-bit window over two mask entries.  A wave's additions to the few bins of such a
-    // histogram are performed one after the other in LDS, so every lane counts in registers instead - one byte
-    // per value in two 64-bit words - and the wave adds its lanes' bytes up every 255 rows at the latest.
-    uint64_t pk0 = 0, pk1 = 0;
-    auto flush = [&]() {
-      for (uint32_t v = 0; v <= K; v++) {  // uniform
-        const uint32_t mine = (uint32_t)((v < 8 ? pk0 : pk1) >> (8 * (v & 7u))) & 0xffu;
-        const uint32_t tot = wave_incl_sum_scan(mine);
-        if (lane == 63 && tot) atomicAdd(&h[v], tot);
+    for (uint32_t k = 0; k < cands.n; k++) {
+      const uint4 c = s_cand[k];
+      const uint32_t cnt = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.x), first = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.y);
+      const uint32_t K = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.z), bin = (uint32_t)__builtin_amdgcn_readfirstlane((int)c.w);
+      // many rows: the work-group takes them together; few: one wave, while the others take other candidates
+      const bool all = cnt >= kRsWG / 2;
+      if (!all && wave != k % (kRsWG / 64)) continue;
+      const uint32_t step = all ? kRsWG : 64;
+      uint32_t *const h = slot(bin);
+      const uint32_t hs = bin < wide ? 6 : rl;
+      if (K <= 32) {
+        const uint32_t keep = K == 32 ? ~0u : (1u << K) - 1u;
+        for (uint32_t i = all ? threadIdx.x : lane; i < cnt; i += step) {
+          const uint32_t g = first + __umul24(i, K);
+          const uint32_t r = (uint32_t)__popc(__builtin_amdgcn_alignbit(s_wp[(g >> 5) + 1].x, s_wp[g >> 5].x, g & 31u) & keep);
+          atomicAdd(h + (r << hs), 1u);
+        }
+      } else {
+        for (uint32_t i = all ? threadIdx.x : lane; i < cnt; i += step) {
+          const uint32_t g = first + __umul24(i, K), f = g + K;
+          const uint2 a = s_wp[g >> 5], b = s_wp[f >> 5];
+          const uint32_t r = (b.y + (uint32_t)__popc(b.x & ((1u << (f & 31u)) - 1u))) -
+                             (a.y + (uint32_t)__popc(a.x & ((1u << (g & 31u)) - 1u)));
+          atomicAdd(h + (r << hs), 1u);
+        }
       }
-      pk0 = pk1 = 0;
-    };
-    const uint32_t n_entries = (n + 15) / 16;
-    const uint32_t stride = gx * kWG;
-    const uint32_t n_it = (N + stride - 1) / stride;  // the same for every thread
-    for (uint32_t it = 0; it < n_it; it++) {
-      const uint32_t i = bx * kWG + threadIdx.x + it * stride;
-      if (i < N) {
-        const uint32_t g = i * K, e = g >> 4;  // i K < n <= 2^30
-        const uint32_t win = (uint32_t)mask16[e] | (e + 1 < n_entries ? (uint32_t)mask16[e + 1] << 16 : 0u);
-        const uint32_t r = (uint32_t)__popc((win >> (g & 15u)) & ((1u << K) - 1u));
-        if (r < 8) pk0 += 1ull << (8 * r);
-        else pk1 += 1ull << (8 * (r - 8));
-      }
-      if ((it & 255u) == 254u) flush();
     }
-    flush();
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i <= K; i += kWG) {
-      const uint32_t t = h[i];
-      if (t) atomicAdd(&out[i], t);
-    }
-    return;
+    __syncthreads();  // the words make room for the next piece
   }
-  const uint32_t waves = gx * (kWG / 64);
-  // four groups of 63 rows per step, their look-ups in flight together
-  constexpr uint32_t kU = 4;
-  for (uint32_t i0 = (bx * (kWG / 64) + (threadIdx.x >> 6)) * 63; i0 < N; i0 += kU * waves * 63) {
-    uint32_t a[kU];
+  // the register counts: one addition per wave and value
 #pragma unroll
-    for (uint32_t u = 0; u < kU; u++) {
-      const uint32_t i = i0 + u * waves * 63 + lane;  // i K stays below 2^32 (n <= 2^30, K <= 2^8) when i <= N
-      a[u] = rs_prefix(i <= N ? i * K : n, n, nnz, mask16, lp, tile_off);
-    }
+  for (uint32_t v = 0; v < 3; v++) {
+    const uint32_t t = wave_incl_sum_scan(c2[v]);
+    if (lane == 63 && at2 != ~0u) atomicAdd(slot(at2 + v), t);
+  }
 #pragma unroll
-    for (uint32_t u = 0; u < kU; u++) {
-      const uint32_t i = i0 + u * waves * 63 + lane;
-      const uint32_t b = (uint32_t)__shfl_down((int)a[u], 1);
-      if (lane < 63 && i < N) atomicAdd(&h[b - a[u]], 1u);
-    }
+  for (uint32_t v = 0; v < 5; v++) {
+    const uint32_t t = wave_incl_sum_scan(c4[v]);
+    if (lane == 63 && at4 != ~0u) atomicAdd(slot(at4 + v), t);
   }
   __syncthreads();
-  for (uint32_t i = threadIdx.x; i <= K; i += kWG) {
-    const uint32_t t = h[i];
+  for (uint32_t i = wave; i < wide; i += kRsWG / 64) {
+    const uint32_t t = wave_incl_sum_scan(s_h[(i << 6) + lane]);
+    if (lane == 63) s_h[i << 6] = t;
+  }
+  __syncthreads();
+  uint32_t *out = hr + (size_t)(bx % offs.n_rep) * offs.rep_stride;
+  for (uint32_t i = threadIdx.x; i < bins; i += kRsWG) {  // neighbours together: a lone lane's addition costs as much as a wave's
+    uint32_t t = 0;
+    if (i < wide) t = s_h[i << 6];
+    else
+      for (uint32_t r = 0; r < 1u << rl; r++) t += s_n[(i << rl) + r];
     if (t) atomicAdd(&out[i], t);
   }
+}
+
+// All histograms that depend on the reshape, and the sum of the partial histograms of v, side by side in one grid:
+// none of the three fills the chip for long.
+__global__ __launch_bounds__(kRsWG) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_rs_count(const uint32_t *mask, uint32_t n, RsCands cands, RsOffsets offs,
+                                                  RsGroups grps, RsGrid gr, const uint32_t *hv_part, uint32_t *hv,
+                                                  uint32_t *hl, uint32_t *hr) {
+  extern __shared__ uint32_t s_dyn[];
+  __shared__ uint32_t sh[kRsWG / 64];
+  __shared__ uint4 s_cand[RANS_RESHAPE_MAX_CAND];
+  uint32_t b = blockIdx.x;
+  if (b < gr.n_rows) {
+    rs_count_rows(mask, n, cands, offs, gr, b, hr, (uint2 *)s_dyn, s_dyn + 8 * kRsWG, sh, s_cand);
+    return;
+  }
+  b -= gr.n_rows;
+  if (b < gr.n_cols) {
+    uint32_t g = 0;
+    while (grps.wg0[g + 1] <= b) g++;  // uniform; entry n is n_cols
+    rs_count_cols(mask, n, grps.L[g], b - grps.wg0[g], hl + grps.off[g], s_dyn);
+    return;
+  }
+  b -= gr.n_cols;  // up to 64 of the partial histograms, a quarter of the threads each
+  if (threadIdx.x < 256) s_dyn[threadIdx.x] = 0;
+  __syncthreads();
+  const uint32_t v = threadIdx.x & 255u;
+  uint32_t t = 0;
+#pragma unroll 8
+  for (uint32_t u = 0; u < 16; u++) {
+    const uint32_t i = b * 64 + u * 4 + (threadIdx.x >> 8);
+    const uint32_t x = hv_part[(size_t)(i < gr.n_part ? i : 0) * 256 + v];
+    t += i < gr.n_part ? x : 0u;
+  }
+  atomicAdd(&s_dyn[v], t);
+  __syncthreads();
+  if (threadIdx.x < 256 && s_dyn[v]) atomicAdd(&hv[v], s_dyn[v]);
 }
 
 // Costs and the walk of Algorithm 1.  One work-group per candidate sums its entropy terms in binary64
 // (a fixed tree: lanes, then waves); the work-group that finishes last walks the candidates from the
 // largest N down.  costs[] and the ticket live in the zeroed part of the workspace.
-__global__ __launch_bounds__(kWG) void k_rs_cost(RsCands cands, uint32_t n, uint32_t n_tiles, uint32_t q_bits,
-                                                 const uint32_t *tile_off, const uint32_t *hv, const uint32_t *hl,
-                                                 const uint32_t *hr, RsOffsets offs, RsGroups grps,
-                                                 const uint32_t *bad_flag, double *costs, uint32_t *ticket,
-                                                 rans_reshape_result *res) {
+__global__ __launch_bounds__(kRsWG) void k_rs_cost(RsCands cands, uint32_t n, uint32_t q_bits, const uint32_t *hv,
+                                                 const uint32_t *hl, const uint32_t *hr, RsOffsets offs, RsGroups grps,
+                                                 double *costs, uint32_t *ticket, rans_reshape_result *res) {
   __shared__ double s_part[kWG / 64];
+  __shared__ uint64_t s_sum[kRsWG / 64];
   __shared__ uint32_t s_ticket;
-  __shared__ uint32_t s_col[256];  // this candidate's column histogram (K <= 2^8)
-  const uint32_t *hr_off = offs.hr;
-  const uint32_t k = blockIdx.x;
-  const uint32_t nnz = tile_off[n_tiles];
+  __shared__ uint32_t s_cnt[257];  // the candidate's histogram of c and r (K <= 2^8)
+  __shared__ uint32_t s_v[256];
+  __shared__ double s_cost[RANS_RESHAPE_MAX_CAND];
+  const uint32_t k = blockIdx.x, two_q = 1u << q_bits;
+  const uint32_t K = cands.K[k], N = n / K;
+  // every load of the work-group is under way before the first is waited for: hv, the row counts' copies (K = 1 has
+  // none: its row counts are the zero mask itself) and the group's histogram of positions modulo L.  That one is
+  // folded K-periodically (K divides L): a thread stays on one column, as the threads' stride is a multiple of K
+  const uint32_t my_v = threadIdx.x < 256 ? hv[threadIdx.x] : 0u;
+  const uint32_t n_r = K == 1 ? 0u : (K + 1) * offs.n_rep;
+  // i / d = i (2^21 / d + 1) >> 21 for the i < 2056 and d <= 257 here (i d < 2^21): two divisions in all instead of one per index
+  const uint32_t inv_r = (1u << 21) / (K + 1) + 1u, inv_c = (1u << 21) / K + 1u;
+  const uint32_t col = threadIdx.x - ((threadIdx.x * inv_c) >> 21) * K;  // threadIdx.x % K
+  uint32_t my_r[3], my_a[3];
+  static_assert(257 * 8 <= 3 * kRsWG, "eight copies at most");
+#pragma unroll
+  for (uint32_t u = 0; u < 3; u++) {
+    const uint32_t i = threadIdx.x + u * kRsWG, q = (i * inv_r) >> 21;
+    my_a[u] = i - q * (K + 1);
+    my_r[u] = u * kRsWG < n_r && i < n_r ? hr[(size_t)q * offs.rep_stride + offs.hr[k] + my_a[u]] : 0u;
+  }
+  if (threadIdx.x < 257) s_cnt[threadIdx.x] = 0;
+  uint32_t my_c = 0;
   {
-    const uint32_t K = cands.K[k], N = n / K;
-    // the group's histogram of positions modulo L, folded K-periodically (K divides L)
-    s_col[threadIdx.x] = 0;  // kWG == 256
-    __syncthreads();
-    {
-      const uint32_t g = grps.of[k], L = grps.L[g];
-      const uint32_t *hg = hl + grps.off[g];
-      for (uint32_t i0 = threadIdx.x; i0 < L; i0 += 8 * kWG) {  // a thread's eight loads in flight together
-        uint32_t t[8];
+    const uint32_t g = grps.of[k], L = grps.L[g], step = ((kRsWG * inv_c) >> 21) * K;
+    const uint32_t *hg = hl + grps.off[g];
+    if (threadIdx.x < step)
+      for (uint32_t i0 = threadIdx.x; i0 < L; i0 += 16 * step) {
+        uint32_t t[16];
 #pragma unroll
-        for (int u = 0; u < 8; u++) t[u] = i0 + u * kWG < L ? hg[i0 + u * kWG] : 0u;
+        for (uint32_t u = 0; u < 16; u++) t[u] = hg[i0 + u * step < L ? i0 + u * step : 0];
 #pragma unroll
-        for (int u = 0; u < 8; u++)
-          if (t[u]) atomicAdd(&s_col[(i0 + u * kWG) % K], t[u]);
+        for (uint32_t u = 0; u < 16; u++) my_c += i0 + u * step < L ? t[u] : 0u;
       }
-    }
+  }
+  const uint32_t nnz = (uint32_t)block_sum64<kRsWG>(threadIdx.x ? my_v : 0u, s_sum);
+  const bool bad = __syncthreads_or(threadIdx.x < 256 && threadIdx.x >= two_q && my_v != 0) != 0;  // not symbols of this bit width
+  {
+    if (threadIdx.x < 256) s_v[threadIdx.x] = threadIdx.x ? my_v : 0u;
+    if (my_c) atomicAdd(&s_cnt[col], my_c);
+#pragma unroll
+    for (uint32_t u = 0; u < 3; u++)
+      if (my_r[u]) atomicAdd(&s_cnt[my_a[u]], my_r[u]);
     __syncthreads();
-    const uint32_t two_q = 1u << q_bits;
     const uint32_t A = K + 1 > two_q ? K + 1 : two_q;
     const uint64_t len = 2ull * nnz + N;
     double h = 0.0;
-    for (uint32_t a = threadIdx.x; a < A; a += kWG) {
+    for (uint32_t a = threadIdx.x; a < A && threadIdx.x < kWG; a += kWG) {
       uint64_t c = 0;
-      if (a < two_q) c += hv[a];
-      if (a < K) c += s_col[a];
-      if (a <= K) c += hr[hr_off[k] + a];
+      if (a < two_q) c += s_v[a];
+      if (a <= K) c += s_cnt[a];
+      if (K == 1 && a <= 1) c += a ? nnz : n - nnz;
       if (c) {
         const double p = (double)c / (double)len;
         h -= p * log2(p);
@@ -364,7 +410,7 @@ __global__ __launch_bounds__(kWG) void k_rs_cost(RsCands cands, uint32_t n, uint
     const uint64_t bits = wave_incl_scan64((uint64_t)__double_as_longlong(h), [](uint64_t x, uint64_t y) {
       return (uint64_t)__double_as_longlong(__longlong_as_double((long long)x) + __longlong_as_double((long long)y));
     });
-    if ((threadIdx.x & 63) == 63) s_part[threadIdx.x >> 6] = __longlong_as_double((long long)bits);
+    if ((threadIdx.x & 63) == 63 && threadIdx.x < kWG) s_part[threadIdx.x >> 6] = __longlong_as_double((long long)bits);
     __syncthreads();
     if (threadIdx.x == 0) {
       double H = 0.0;
@@ -375,27 +421,32 @@ __global__ __launch_bounds__(kWG) void k_rs_cost(RsCands cands, uint32_t n, uint
     }
     __syncthreads();
   }
-  if (s_ticket != gridDim.x - 1 || threadIdx.x != 0) return;
+  if (s_ticket != gridDim.x - 1) return;
   __atomic_thread_fence(__ATOMIC_ACQUIRE);
+  // a thread per candidate, then the walk: one trip to memory for all costs
+  static_assert(RANS_RESHAPE_MAX_CAND <= kRsWG, "a thread per candidate");
+  if (threadIdx.x < cands.n) {
+    const double cost = __hip_atomic_load(costs + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_cost[threadIdx.x] = cost;
+    res->cand_rows[threadIdx.x] = n / cands.K[threadIdx.x];
+    res->cand_cost[threadIdx.x] = cost;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
   double best = INFINITY, prev = INFINITY;
   uint64_t n_tilde = n;
   uint32_t evaluated = 0;
-  bool walking = true;
   for (uint32_t i = 0; i < cands.n; i++) {
-    const double cost = __hip_atomic_load(costs + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    res->cand_rows[i] = n / cands.K[i];
-    res->cand_cost[i] = cost;
-    if (walking) {
-      evaluated++;
-      if (cost < best) {
-        best = cost;
-        n_tilde = n / cands.K[i];
-      }
-      if (cost > prev) walking = false;  // stop after this one
-      prev = cost;
+    const double cost = s_cost[i];
+    evaluated++;
+    if (cost < best) {
+      best = cost;
+      n_tilde = n / cands.K[i];
     }
+    if (cost > prev) break;  // the walk stops after this one
+    prev = cost;
   }
-  if (*bad_flag) {  // a symbol outside {0 .. 2^Q - 1}: no meaningful result
+  if (bad) {  // a symbol outside {0 .. 2^Q - 1}: no meaningful result
     best = __longlong_as_double(0x7ff8000000000000ll);
     n_tilde = n;
     evaluated = 0;
@@ -408,10 +459,12 @@ __global__ __launch_bounds__(kWG) void k_rs_cost(RsCands cands, uint32_t n, uint
 }
 
 // an empty domain: rows = T, cols = 1, cost +inf
-__global__ void k_rs_empty(uint32_t n, const uint32_t *bad_flag, rans_reshape_result *res) {
+__global__ __launch_bounds__(kWG) void k_rs_empty(uint32_t n, uint32_t q_bits, const uint32_t *hv, rans_reshape_result *res) {
+  const bool bad = __syncthreads_or((threadIdx.x >> q_bits) != 0 && hv[threadIdx.x] != 0) != 0;
+  if (threadIdx.x != 0) return;
   res->rows = n;
   res->cols = 1;
-  res->cost_bits = *bad_flag ? __longlong_as_double(0x7ff8000000000000ll) : INFINITY;
+  res->cost_bits = bad ? __longlong_as_double(0x7ff8000000000000ll) : INFINITY;
   res->n_evaluated = 0;
   res->n_candidates = 0;
 }
