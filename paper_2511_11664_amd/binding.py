@@ -228,12 +228,20 @@ def search_reshape(d_sym, q_bits: int) -> ReshapeResult:
     ws = torch.empty(ws_bytes + 256, dtype=torch.uint8, device=d_sym.device)
     off = (-ws.data_ptr()) % 256
     ws = ws[off:off + ws_bytes]
-    res = torch.zeros(C.sizeof(ReshapeResult), dtype=torch.uint8, device=d_sym.device)
+    res = _host_words(C.sizeof(ReshapeResult) // 8)
     rc = rans_search_reshape(d_sym, n, q_bits, res, ws)
+    torch.cuda.current_stream().synchronize()
     if rc:
         raise RansError(rc)
-    host = res.cpu().numpy().tobytes()
-    return ReshapeResult.from_buffer_copy(host)
+    return ReshapeResult.from_buffer_copy(res.numpy())
+
+
+def _host_words(n: int) -> torch.Tensor:
+    """n zeroed 64-bit words of pinned host memory, which a kernel can write and the host reads after the stream's
+    synchronisation: no fill, no copy and no second wait for a result of a few bytes."""
+    t = torch.empty(n, dtype=torch.int64, pin_memory=True)
+    C.memset(t.data_ptr(), 0, 8 * n)
+    return t
 
 
 def rans_strerror(code: int) -> str:
@@ -339,12 +347,26 @@ def compress_with_search(x: torch.Tensor, q_bits: int, freq_bits: int, n_streams
     in_dtype = F16 if x.dtype == torch.float16 else F32
     # any valid reshape serves for the quantise step (Eq. 6 does not depend on it)
     pq = make_params(q_bits, freq_bits, n, 1, MODE_DENSE, n_streams, chunk_syms, in_dtype)
-    cq = Codec(pq, n, x.device)
+    rc, ws_bytes, _ = rans_workspace_bytes(pq, n)
+    if rc:
+        raise RansError(rc)
     sym = torch.empty(n, dtype=torch.uint8, device=x.device)
-    cq.quantize(x.reshape(-1), sym)
+    qinfo = torch.empty(4, dtype=torch.float32, device=x.device)
+    ws = torch.empty(ws_bytes + 256, dtype=torch.uint8, device=x.device)
+    rc = rans_quantize(x.reshape(-1), n, pq, sym, qinfo, ws)
+    if rc:
+        raise RansError(rc)
+    # a non-finite tensor is reported by the encoder, which gets the same extrema: no wait for the status here
     res = search_reshape(sym, q_bits)
     p = make_params(q_bits, freq_bits, res.rows, res.cols, MODE_CSR, n_streams, chunk_syms, in_dtype)
-    ce = Codec(p, n, x.device)
-    ce.qinfo.copy_(cq.qinfo)
-    nbytes = ce.encode(sym)
-    return ce.stream[:nbytes], p, res
+    rc, ws_bytes, max_bytes = rans_workspace_bytes(p, n)
+    if rc:
+        raise RansError(rc)
+    ws = torch.empty(ws_bytes + 256, dtype=torch.uint8, device=x.device)
+    stream = torch.empty(max_bytes + 16, dtype=torch.uint8, device=x.device)
+    size = _host_words(1)
+    rc = rans_encode(sym, n, p, qinfo, stream, size, ws)
+    st = rans_last_status(ws)  # synchronises
+    if rc or st:
+        raise RansError(rc or st)
+    return stream[:int(size[0])], p, res
