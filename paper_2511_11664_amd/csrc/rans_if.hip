@@ -149,6 +149,14 @@ inline uint32_t grid_for(uint64_t n, uint32_t per_block, uint32_t cap) {
   return (uint32_t)(g > cap ? cap : g);
 }
 
+// Vectors of V elements a lane of k_quant_hist takes in a step of its work-group.  A dense tensor that 128 work-groups can
+// take in one step gets as few as that needs: more work-groups end with more additions to the same addresses, 12 ns
+// each, fewer leave the chip idle.  CSR mode's tile counts rely on kQIter.
+inline uint32_t quant_vectors(uint64_t n, uint32_t V, bool csr) {
+  const uint64_t it = (n + (uint64_t)QNT * V * 128 - 1) / ((uint64_t)QNT * V * 128);
+  return csr || it > kQIter ? kQIter : it < 1 ? 1u : (uint32_t)it;
+}
+
 // Index of the last of the counters behind L.chunk_words that a call starts from zero, and the tile counts among them.
 inline uint32_t counter_words(const Layout &L) { return L.tc_off + L.n_blk - 1; }
 inline uint32_t *tile_counts_of(const Layout &L, uint8_t *ws) {
@@ -195,15 +203,16 @@ int launch_quantize(const void *d_x, uint64_t n, const rans_params &p, const Lay
   }
   if (n) {
     int skip0 = p.mode == RANS_MODE_CSR;
-    uint32_t g = grid_for(n, QNT * V * kQIter, skip0 ? kQuantBlocksCsr : kQuantBlocks);
+    const uint32_t n_it = quant_vectors(n, V, skip0);
+    uint32_t g = grid_for(n, QNT * V * n_it, skip0 ? kQuantBlocksCsr : kQuantBlocks);
     auto launch_qh = [&](auto csr_tag) {
       constexpr bool CSRV = decltype(csr_tag)::value;
       if (f16) {
-        if (vec) PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<__half, true, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const __half *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws));
-        else PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<__half, false, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const __half *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws));
+        if (vec) PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<__half, true, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const __half *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws), n_it);
+        else PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<__half, false, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const __half *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws), n_it);
       } else {
-        if (vec) PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<float, true, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const float *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws));
-        else PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<float, false, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const float *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws));
+        if (vec) PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<float, true, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const float *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws), n_it);
+        else PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<float, false, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const float *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws), n_it);
       }
     };
     if (skip0) launch_qh(std::true_type{});
@@ -971,13 +980,14 @@ int rans_encode(const uint8_t *d_sym, uint64_t n_elems, const rans_params *p, co
   if (n_elems) {
     const bool vec = aligned_to(d_sym, 16);
     const int skip0 = p->mode == RANS_MODE_CSR;
-    const uint32_t g = grid_for(n_elems, QNT * (vec ? 16 : 1) * kQIter, skip0 ? kQuantBlocksCsr : kQuantBlocks);
+    const uint32_t n_it = quant_vectors(n_elems, vec ? 16 : 1, skip0);
+    const uint32_t g = grid_for(n_elems, QNT * (vec ? 16 : 1) * n_it, skip0 ? kQuantBlocksCsr : kQuantBlocks);
     auto launch_qh = [&](auto csr_tag) {
       constexpr bool CSRV = decltype(csr_tag)::value;
       if (vec)
-        PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<uint8_t, true, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, d_sym, (uint32_t)n_elems, ctl, p->q_bits, (uint8_t *)nullptr, (uint32_t *)(ws + L.cnt), skip0, (const MinMaxPart *)nullptr, 0u, (rans_qinfo *)nullptr, tile_counts_of(L, ws), grp_counts_of(L, ws));
+        PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<uint8_t, true, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, d_sym, (uint32_t)n_elems, ctl, p->q_bits, (uint8_t *)nullptr, (uint32_t *)(ws + L.cnt), skip0, (const MinMaxPart *)nullptr, 0u, (rans_qinfo *)nullptr, tile_counts_of(L, ws), grp_counts_of(L, ws), n_it);
       else
-        PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<uint8_t, false, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, d_sym, (uint32_t)n_elems, ctl, p->q_bits, (uint8_t *)nullptr, (uint32_t *)(ws + L.cnt), skip0, (const MinMaxPart *)nullptr, 0u, (rans_qinfo *)nullptr, tile_counts_of(L, ws), grp_counts_of(L, ws));
+        PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<uint8_t, false, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, d_sym, (uint32_t)n_elems, ctl, p->q_bits, (uint8_t *)nullptr, (uint32_t *)(ws + L.cnt), skip0, (const MinMaxPart *)nullptr, 0u, (rans_qinfo *)nullptr, tile_counts_of(L, ws), grp_counts_of(L, ws), n_it);
     };
     if (skip0) launch_qh(std::true_type{});
     else launch_qh(std::false_type{});

@@ -760,7 +760,7 @@ __global__ __launch_bounds__(kBig) void k_normalize(CtlRef ctl, NormArgs na) {
 // few hot symbols of an activation tensor do not serialise the whole wave on one
 // LDS address.
 constexpr int kHistRep = 8;
-constexpr int kQIter = 4;
+constexpr int kQIter = 4;                // vectors a lane takes in a step of its work-group
 constexpr int QNT = 1024;                // lanes per work-group of the quantise / histogram kernel
 constexpr uint32_t kQuantBlocks = 256;   // its work-groups (persistent over tiles): few of them, because each one ends
                                          // with a burst of same-address atomics on the global histogram
@@ -768,11 +768,27 @@ constexpr uint32_t kQuantBlocksCsr = 512;  // CSR mode, where every tile ends wi
                                            // two work-groups per compute unit overlap them (c2: 30.4 -> 28.3 us; the
                                            // dense kernel is 4 us slower on c5a with 512)
 
+// What bounds it on large tensors is the instructions of a symbol, before the traffic (requesting the next step's vectors
+// while this one is worked on made it 10 % slower, by its registers).  Symbols come in one of three ways, chosen per call:
+//   kDivAny    x / s as the compiler divides
+//   kDivFast   FastDiv, the same quotient in five operations
+//   kDivRound  u = fma(x, 1 / s, z), rounded: no quotient and no clamp, where the result is certain.
+// The last needs |x| <= 256 s for all x, as whenever the tensor's range holds a 0.  With r1 = (1 / s)(1 + e), |e| <= 2^-23,
+// u is off x / s + z by 256 * 2^-23 and its own rounding, 2^-16 for |u| < 512; Eq. 6 as defined - the rounded quotient,
+// plus z, rounded - is off by 256 * 2^-24 and 2^-16.  Together below 8 * 10^-5, so u and Eq. 6's sum round to the same integer
+// unless u is within kRoundDoubt = 2^-13 of a half; and that integer is in 0 .. 2^Q - 1, as the exact value is at most
+// 1/2 + 6 * 10^-5 outside (z and s are rounded).  A lane with a doubtful value takes all of its vector by FastDiv: about 2^-12
+// of the values of a continuous distribution, one wave step of 256 values in 16.
+// Measured, FastDiv throughout and always four vectors a step against this: 16384 x 4096 fp16 36.7 -> 34.9 us (5.8 TB/s of
+// tensor and symbols), 8192 x 3136 fp32 in CSR mode 28.4 -> 27.8 us, 395 x 4096 fp16 8.8 -> 7.5 us, 128 x 784 fp32
+// 6.3 -> 4.8 us, 3.3 M symbols counted only 7.7 -> 5.9 us.
+constexpr int kDivAny = 0, kDivFast = 1, kDivRound = 2;
+constexpr float kRoundDoubt = 0x1p-13f;
 template <typename T, bool VEC, int NT, bool CSR>
 __global__ __launch_bounds__(NT) void k_quant_hist(const T *x, uint32_t n, CtlRef ctl, uint32_t q_bits,
                                                     uint8_t *sym, uint32_t *cnt, int skip_zero_bin,
                                                     const MinMaxPart *part, uint32_t n_part, rans_qinfo *qout,
-                                                    uint32_t *blk_nnz, uint32_t *grp_nnz) {
+                                                    uint32_t *blk_nnz, uint32_t *grp_nnz, uint32_t n_it) {
   constexpr bool IS_SYM = sizeof(T) == 1;
   constexpr int V = VEC ? (int)(16 / sizeof(T)) : 1;
   __shared__ uint32_t h[256 * kHistRep];
@@ -798,7 +814,8 @@ __global__ __launch_bounds__(NT) void k_quant_hist(const T *x, uint32_t n, CtlRe
   FastDiv fd;
   fd.init(s);
   const uint32_t rep = threadIdx.x & (kHistRep - 1);
-  const uint32_t tile = NT * V * kQIter;
+  const bool round_only = fast && !degenerate && amax <= 256.0f * s;
+  const uint32_t tile = NT * V * (CSR ? (uint32_t)kQIter : n_it);
   // CSR: the nonzeros of each tile of kCsrTile symbols are counted on the way.  A work-group's tile of
   // NT * V * kQIter elements is V such tiles and a wave's symbols of one step lie in one of them: the lanes'
   // counts are summed with a wave scan, the last lane adds the sum to the tile's LDS counter, and after the
@@ -811,17 +828,33 @@ __global__ __launch_bounds__(NT) void k_quant_hist(const T *x, uint32_t n, CtlRe
     atomicAdd(&h[a * kHistRep + rep], 1u);
     if constexpr (CSR) lane_nz += a != 0;
   };
-  auto run = [&](auto fast_tag) {
-  constexpr bool FAST = decltype(fast_tag)::value;
+  auto run = [&](auto div_tag) {
+  constexpr int DIV = decltype(div_tag)::value;
   auto q = [&](float v) -> uint32_t {
-    const float t = FAST ? fd.div(v) : v / s;
+    const float t = DIV != kDivAny ? fd.div(v) : v / s;
     const float r = rintf(t + zf);
     return (uint32_t)__builtin_amdgcn_fmed3f(r, 0.0f, levels);
+  };
+  auto q_all = [&](const auto &v, auto &a) {  // a lane's vector
+    constexpr int NV = sizeof(v) / sizeof(v[0]);
+    if constexpr (DIV == kDivRound) {
+      float far = 0.0f;
+#pragma unroll
+      for (int k = 0; k < NV; k++) {
+        const float u = __builtin_fmaf(v[k], fd.r1, zf), r = rintf(u);
+        far = fmaxf(far, fabsf(u - r));
+        a[k] = (uint32_t)r;
+      }
+      if (!(far > 0.5f - kRoundDoubt)) return;
+    }
+#pragma unroll
+    for (int k = 0; k < NV; k++) a[k] = q(v[k]);
   };
   // a work-group walks tiles blockIdx.x, blockIdx.x + gridDim.x, ... and flushes its histogram once
   for (uint64_t base = (uint64_t)blockIdx.x * tile; base < n; base += (uint64_t)gridDim.x * tile) {
 #pragma unroll
   for (int it = 0; it < kQIter; it++) {
+    if (!CSR && (uint32_t)it >= n_it) break;
     uint64_t e0 = base + ((uint64_t)it * NT + threadIdx.x) * V;
     if (!CSR && e0 >= n) break;
     if (e0 < n) {
@@ -835,18 +868,22 @@ __global__ __launch_bounds__(NT) void k_quant_hist(const T *x, uint32_t n, CtlRe
         }
       } else if constexpr (sizeof(T) == 4) {
         float4 f = *(const float4 *)((const float *)x + e0);
-        uint32_t a0 = q(f.x), a1 = q(f.y), a2 = q(f.z), a3 = q(f.w);
-        bump(a0); bump(a1); bump(a2); bump(a3);
-        *(uint32_t *)(sym + e0) = a0 | (a1 << 8) | (a2 << 16) | (a3 << 24);
+        const float v[4] = {f.x, f.y, f.z, f.w};
+        uint32_t a[4];
+        q_all(v, a);
+        bump(a[0]); bump(a[1]); bump(a[2]); bump(a[3]);
+        *(uint32_t *)(sym + e0) = a[0] | (a[1] << 8) | (a[2] << 16) | (a[3] << 24);
       } else {
         uint4 w = *(const uint4 *)((const uint16_t *)x + e0);
         uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+        float v[8];
         uint32_t a[8];
 #pragma unroll
         for (int k = 0; k < 4; k++) {
-          a[2 * k] = q(half_bits_to_float((uint16_t)(ww[k] & 0xffffu)));
-          a[2 * k + 1] = q(half_bits_to_float((uint16_t)(ww[k] >> 16)));
+          v[2 * k] = half_bits_to_float((uint16_t)(ww[k] & 0xffffu));
+          v[2 * k + 1] = half_bits_to_float((uint16_t)(ww[k] >> 16));
         }
+        q_all(v, a);
 #pragma unroll
         for (int k = 0; k < 8; k++) bump(a[k]);
         uint2 o;
@@ -890,8 +927,10 @@ __global__ __launch_bounds__(NT) void k_quant_hist(const T *x, uint32_t n, CtlRe
   }
   }
   };  // run
-  if (fast) run(std::true_type{});
-  else run(std::false_type{});
+  if constexpr (IS_SYM) run(std::integral_constant<int, kDivAny>{});
+  else if (round_only) run(std::integral_constant<int, kDivRound>{});
+  else if (fast) run(std::integral_constant<int, kDivFast>{});
+  else run(std::integral_constant<int, kDivAny>{});
   __syncthreads();
   // The counts go to the global histogram with additions that return nothing: the kernel that reads them
   // starts after this one has ended, which is all the ordering the histogram needs.
