@@ -1064,15 +1064,19 @@ __global__ __launch_bounds__(kWG) void k_dequant(const uint8_t *sym, uint64_t n,
   uint64_t done = 0;
   if constexpr (VEC) {
     struct alignas(4 * sizeof(OutT)) Quad { OutT a, b, c, d; };
-    const uint64_t nv = n / 16;
-    for (uint64_t i = tid; i < nv; i += stride) {
-      const uint4 w = ((const uint4 *)sym)[i];
-      const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+    // four symbols a lane and store, neighbouring lanes side by side: a wave's store is one stretch of memory.  (With
+    // sixteen consecutive symbols a lane its stores hit 64 pieces of 16 bytes: 3.3 M symbols to fp32 8.2 us, now 5.7.)
+    const uint64_t nv = n / 4;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * (4 * kWG) + threadIdx.x; i0 < nv; i0 += 4 * stride) {
+      uint32_t w[4];
+#pragma unroll
+      for (int k = 0; k < 4; k++) w[k] = ((const uint32_t *)sym)[i0 + k * kWG < nv ? i0 + k * kWG : i0];
 #pragma unroll
       for (int k = 0; k < 4; k++)
-        ((Quad *)out)[4 * i + k] = Quad{conv(ww[k] & 0xffu), conv((ww[k] >> 8) & 0xffu), conv((ww[k] >> 16) & 0xffu), conv(ww[k] >> 24)};
+        if (i0 + k * kWG < nv)
+          ((Quad *)out)[i0 + k * kWG] = Quad{conv(w[k] & 0xffu), conv((w[k] >> 8) & 0xffu), conv((w[k] >> 16) & 0xffu), conv(w[k] >> 24)};
     }
-    done = nv * 16;
+    done = nv * 4;
   }
   for (uint64_t i = done + tid; i < n; i += stride) out[i] = conv(sym[i]);
 }
