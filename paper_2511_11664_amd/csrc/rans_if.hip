@@ -141,6 +141,10 @@ inline uint32_t compute_units() {
 constexpr uint32_t kDecWideGroupMinChunks = 192;
 constexpr uint32_t kDecLeanMaxWaves = 1024;  // decoding waves (64 streams) up to which the decoder takes its LEAN form
 constexpr uint32_t kExpandOwnSumMaxTiles = 4096;
+// Up to so many rows and tiles k_csr_to_dense does without tile sums: two rounds of 16-byte loads a lane, and no more
+// work-groups than compute units read them.
+constexpr uint32_t kExpandAllRows = 32768, kExpandAllTiles = 256;
+static_assert(kExpandAllRows <= 8 * 8 * kWG * 2, "two rounds of eight loads of eight counts");
 constexpr uint32_t kShortRowCols = 32;  // rows up to this length: k_csr_compact derives its row ends from a mask
 
 inline uint32_t grid_for(uint64_t n, uint32_t per_block, uint32_t cap) {
@@ -711,9 +715,13 @@ int decode_common(const uint8_t *d_stream, size_t stream_bytes, const rans_heade
     }
     const uint32_t n_tiles = (N + tile_rows - 1) / tile_rows;
     uint32_t *part = (uint32_t *)(ws + L.row_off);  // n_tiles + 1 entries (n_tiles <= N)
-    PROF_LAUNCH(KID_ROW_SCAN, k_row_part, dim3((n_tiles + kWG / 64 - 1) / (kWG / 64)), dim3(kWG), 0, st, D + 2 * nnz, N, K, tile_rows,
-                n_tiles, part, ctl);
-    LAUNCH_CHECK();
+    // few rows in few tiles: the expand kernel's work-groups add up all counts before their tile themselves
+    if (N <= kExpandAllRows && n_tiles <= kExpandAllTiles) part = nullptr;
+    if (part) {
+      PROF_LAUNCH(KID_ROW_SCAN, k_row_part, dim3((n_tiles + kWG / 64 - 1) / (kWG / 64)), dim3(kWG), 0, st, D + 2 * nnz, N, K, tile_rows,
+                  n_tiles, part, ctl);
+      LAUNCH_CHECK();
+    }
     // up to a few thousand tiles every work-group of the expand kernel adds up the sums before its own
     const int scanned = n_tiles > kExpandOwnSumMaxTiles;
     if (scanned) {
