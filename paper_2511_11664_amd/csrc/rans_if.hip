@@ -153,6 +153,12 @@ inline uint32_t grid_for(uint64_t n, uint32_t per_block, uint32_t cap) {
   return (uint32_t)(g > cap ? cap : g);
 }
 
+// CSR mode: k_quant_hist counts nonzeros per tile of kCsrTile symbols, and with 16-byte vectors a work-group has to take a
+// tile per element of the vector.  Small tensors are faster with element loads and a work-group per tile.  Whole calls
+// with vectors / with elements, us: encode from bytes 29.7 / 24.3 at 100 352 symbols, 31.5 / 26.9 at 401 408, 32.7 / 31.3
+// at 2^20; compress of fp16 30.0 / 27.2, 32.2 / 29.9, 33.1 / 34.4; of fp32 27.9 / 27.1, 29.6 / 29.8, 31.7 / 33.9.
+inline bool csr_by_element(uint64_t n, size_t elem_bytes) { return n <= (1u << 20) / elem_bytes; }
+
 // Vectors of V elements a lane of k_quant_hist takes in a step of its work-group.  A dense tensor that 128 work-groups can
 // take in one step gets as few as that needs: more work-groups end with more additions to the same addresses, 12 ns
 // each, fewer leave the chip idle.  CSR mode's tile counts rely on kQIter.
@@ -185,13 +191,15 @@ int launch_quantize(const void *d_x, uint64_t n, const rans_params &p, const Lay
   const uint32_t ncz_ = counter_words(L);
   const bool f16 = p.in_dtype == RANS_F16;
   const bool vec = aligned_to(d_x, 16) && aligned_to(d_sym, 8);
-  const uint32_t V = vec ? (f16 ? 8 : 4) : 1;
+  const uint32_t Vm = vec ? (f16 ? 8 : 4) : 1;  // of k_minmax
+  const bool vec_q = vec && !(p.mode == RANS_MODE_CSR && csr_by_element(n, f16 ? 2 : 4));
+  const uint32_t V = vec_q ? Vm : 1;
   static_assert(QNT * kQIter == kCsrTile, "a work-group step of k_quant_hist is V tiles of the CSR kernels");
   if (tiles_per_grp) *tiles_per_grp = V;
   MinMaxPart *part = (MinMaxPart *)(ws + L.mm_part);
   uint32_t n_part = 0;
   if (n) {
-    uint32_t g = n_part = grid_for(n, kWG * V * 4, kMaxParts);
+    uint32_t g = n_part = grid_for(n, kWG * Vm * 4, kMaxParts);
     if (f16) {
       if (vec) PROF_LAUNCH(KID_MINMAX, (k_minmax<__half, true>), dim3(g), dim3(kWG), 0, st, (const __half *)d_x, (uint32_t)n, part, ctl, cnt, L.A * (1 + L.cnt_rep), cw_, ncz_);
       else PROF_LAUNCH(KID_MINMAX, (k_minmax<__half, false>), dim3(g), dim3(kWG), 0, st, (const __half *)d_x, (uint32_t)n, part, ctl, cnt, L.A * (1 + L.cnt_rep), cw_, ncz_);
@@ -212,10 +220,10 @@ int launch_quantize(const void *d_x, uint64_t n, const rans_params &p, const Lay
     auto launch_qh = [&](auto csr_tag) {
       constexpr bool CSRV = decltype(csr_tag)::value;
       if (f16) {
-        if (vec) PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<__half, true, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const __half *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws), n_it);
+        if (vec_q) PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<__half, true, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const __half *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws), n_it);
         else PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<__half, false, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const __half *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws), n_it);
       } else {
-        if (vec) PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<float, true, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const float *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws), n_it);
+        if (vec_q) PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<float, true, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const float *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws), n_it);
         else PROF_LAUNCH(KID_QUANT_HIST, (k_quant_hist<float, false, QNT, CSRV>), dim3(g), dim3(QNT), 0, st, (const float *)d_x, (uint32_t)n, ctl, p.q_bits, d_sym, cnt, skip0, part, n_part, d_qinfo, tile_counts_of(L, ws), grp_counts_of(L, ws), n_it);
       }
     };
@@ -985,9 +993,11 @@ int rans_encode(const uint8_t *d_sym, uint64_t n_elems, const rans_params *p, co
   PROF_LAUNCH(KID_QINFO, k_qinfo_from_user, dim3(1), dim3(kBig), 0, st, ctl, d_qinfo, p->q_bits,
               (uint32_t *)(ws + L.cnt), L.A * (1 + L.cnt_rep), (uint32_t *)(ws + L.chunk_words), counter_words(L));
   LAUNCH_CHECK();
+  const uint32_t tiles_per_grp =
+      aligned_to(d_sym, 16) && !(p->mode == RANS_MODE_CSR && csr_by_element(n_elems, 1)) ? 16u : 1u;
   if (n_elems) {
-    const bool vec = aligned_to(d_sym, 16);
     const int skip0 = p->mode == RANS_MODE_CSR;
+    const bool vec = tiles_per_grp == 16;
     const uint32_t n_it = quant_vectors(n_elems, vec ? 16 : 1, skip0);
     const uint32_t g = grid_for(n_elems, QNT * (vec ? 16 : 1) * n_it, skip0 ? kQuantBlocksCsr : kQuantBlocks);
     auto launch_qh = [&](auto csr_tag) {
@@ -1002,7 +1012,7 @@ int rans_encode(const uint8_t *d_sym, uint64_t n_elems, const rans_params *p, co
     LAUNCH_CHECK();
   }
   return launch_encode_tail(d_sym, n_elems, *p, L, ws, d_stream, stream_cap, d_stream_bytes, st, seq,
-                            aligned_to(d_sym, 16) ? 16u : 1u);
+                            tiles_per_grp);
 }
 
 int rans_compress(const void *d_x, uint64_t n_elems, const rans_params *p, uint8_t *d_stream, size_t stream_cap,

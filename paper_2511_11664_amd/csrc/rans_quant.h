@@ -772,7 +772,8 @@ constexpr uint32_t kQuantBlocksCsr = 512;  // CSR mode, where every tile ends wi
 // while this one is worked on made it 10 % slower, by its registers).  Symbols come in one of three ways, chosen per call:
 //   kDivAny    x / s as the compiler divides
 //   kDivFast   FastDiv, the same quotient in five operations
-//   kDivRound  u = fma(x, 1 / s, z), rounded: no quotient and no clamp, where the result is certain.
+//   kDivRound  u = fma(x, 1 / s, z), rounded: no quotient and no clamp, where the result is certain (dense mode: in CSR mode,
+//              bound by its barriers, it gives 0.6 us of 28 and costs 4 us of longer code on a first pass).
 // The last needs |x| <= 256 s for all x, as whenever the tensor's range holds a 0.  With r1 = (1 / s)(1 + e), |e| <= 2^-23,
 // u is off x / s + z by 256 * 2^-23 and its own rounding, 2^-16 for |u| < 512; Eq. 6 as defined - the rounded quotient,
 // plus z, rounded - is off by 256 * 2^-24 and 2^-16.  Together below 8 * 10^-5, so u and Eq. 6's sum round to the same integer
@@ -780,7 +781,7 @@ constexpr uint32_t kQuantBlocksCsr = 512;  // CSR mode, where every tile ends wi
 // 1/2 + 6 * 10^-5 outside (z and s are rounded).  A lane with a doubtful value takes all of its vector by FastDiv: about 2^-12
 // of the values of a continuous distribution, one wave step of 256 values in 16.
 // Measured, FastDiv throughout and always four vectors a step against this: 16384 x 4096 fp16 36.7 -> 34.9 us (5.8 TB/s of
-// tensor and symbols), 8192 x 3136 fp32 in CSR mode 28.4 -> 27.8 us, 395 x 4096 fp16 8.8 -> 7.5 us, 128 x 784 fp32
+// tensor and symbols), 395 x 4096 fp16 8.8 -> 7.5 us, 128 x 784 fp32
 // 6.3 -> 4.8 us, 3.3 M symbols counted only 7.7 -> 5.9 us.
 constexpr int kDivAny = 0, kDivFast = 1, kDivRound = 2;
 constexpr float kRoundDoubt = 0x1p-13f;
@@ -814,7 +815,7 @@ __global__ __launch_bounds__(NT) void k_quant_hist(const T *x, uint32_t n, CtlRe
   FastDiv fd;
   fd.init(s);
   const uint32_t rep = threadIdx.x & (kHistRep - 1);
-  const bool round_only = fast && !degenerate && amax <= 256.0f * s;
+  const bool round_only = !CSR && fast && !degenerate && amax <= 256.0f * s;
   const uint32_t tile = NT * V * (CSR ? (uint32_t)kQIter : n_it);
   // CSR: the nonzeros of each tile of kCsrTile symbols are counted on the way.  A work-group's tile of
   // NT * V * kQIter elements is V such tiles and a wave's symbols of one step lie in one of them: the lanes'
@@ -852,7 +853,9 @@ __global__ __launch_bounds__(NT) void k_quant_hist(const T *x, uint32_t n, CtlRe
   };
   // a work-group walks tiles blockIdx.x, blockIdx.x + gridDim.x, ... and flushes its histogram once
   for (uint64_t base = (uint64_t)blockIdx.x * tile; base < n; base += (uint64_t)gridDim.x * tile) {
-#pragma unroll
+  // dense: the symbol stores keep the next vector's load behind them anyway, and short code is fetched sooner (a first pass
+  // over 16384 x 4096 fp16 149 -> 145 us); CSR, whose step ends with a wave scan, is 1 us slower without the unrolling
+#pragma unroll(CSR ? kQIter : 1)
   for (int it = 0; it < kQIter; it++) {
     if (!CSR && (uint32_t)it >= n_it) break;
     uint64_t e0 = base + ((uint64_t)it * NT + threadIdx.x) * V;
