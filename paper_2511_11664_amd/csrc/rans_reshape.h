@@ -193,7 +193,7 @@ __device__ __forceinline__ void rs_count_rows(const uint32_t *mask, uint32_t n, 
       }
     }
     // every candidate's rows of this piece - their number, the first one's position, K, the first bin - by a thread each:
-    // the two divisions, made by every wave for every candidate, were half of the kernel's instructions
+    // with the two divisions made by every wave for every candidate the kernel took 4 us more (25.7 M symbols)
     if (threadIdx.x < cands.n) {
       const uint32_t K = cands.K[threadIdx.x], s = w0 * 32, e = w1 * 32 < n ? w1 * 32 : n;
       const uint32_t i0 = (s + K - 1) / K, i1 = (e + K - 1) / K;
