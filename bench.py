@@ -269,7 +269,7 @@ def main():
         coding = {"bits_per_symbol": round(8 * nbytes / n, 4), "entropy_H": round(H, 4), "cross_entropy_CE": round(CE, 4)}
     b_enc, b_dec = _alg_bytes(w, nbytes, int(hdr.len_d))
     # algorithmic bytes per launch of the kernels that can dominate (per-unit figure x units of one launch)
-    alg = {"k_encode": n + nbytes, "k_decode": nbytes + e * n, "k_quant_hist": e * n + n, "k_minmax": e * n,
+    alg = {"k_encode": n + nbytes, "k_encode_feed": n + nbytes, "k_decode": nbytes + e * n, "k_decode_lean": nbytes + e * n, "k_quant_hist": e * n + n, "k_minmax": e * n,
            "k_gather": 2 * nbytes}
     # HBM-side bytes per launch of the dominant kernel: NOT measured by this run (counters need rocprofv3); the figure
     # is the one recorded by the rocprofv3 --pmc runs of this same command whose summary is committed under profiles/
@@ -280,7 +280,8 @@ def main():
         # the summary has one line per template instantiation; the timed loop runs the fused encoder and the
         # decoder that writes the caller's dtype, the other instantiations belong to the unfused entry points
         want = {"k_encode": f"k_encode<{'SrcCsr' if w.mode else 'SrcDense'},2,{'true' if w.freq_bits >= 8 else 'false'},true>",
-                "k_decode": "k_decode_fast<FSink" + ("U16" if w.mode else "Float")}.get(dom, dom + "<")
+                "k_decode": "k_decode_fast<FSink" + ("U16" if w.mode else "Float"),
+                "k_decode_lean": "k_decode_fast<FSink" + ("U16" if w.mode else "Float")}.get(dom, dom + "<")
         hits = [line.split() for line in open(tfile) if line.startswith(want)]
         if len(hits) == 1:
             traffic = int(hits[0][-1])

@@ -98,13 +98,50 @@ int check_params(const rans_params *p, uint64_t n) {
   return RANS_OK;
 }
 
-// Coding waves (64 streams each) up to which the encoder runs them one to a work-group with three feeding waves
-// (k_encode_feed) instead of four to a work-group (k_encode).  Whole compress calls, us, four to a work-group against
-// fed, at 384 / 512 / 768 coding waves (64 streams to a chunk): 64 rows 28 / 30 / 34 against 26 / 29 / 42, 256 rows
-// 50 / 54 / 90 against 41 / 46 / 70; 1024 streams to a chunk: 64 rows 26 / 27 / 30 against 27 / 30 / 46, 256 rows
-// 50 / 53 / 59 against 43 / 49 / 78.  Two fed work-groups fit a compute unit, so from 512 on they come in turns.
-constexpr uint32_t kFeedMaxWaves = 384, kFeedMaxWavesLong = 512;
-constexpr uint32_t kFeedLongRows = 128;
+// Which of the two encoders a tensor takes: one coding wave per work-group with three waves that feed it
+// (k_encode_feed), or four coding waves (k_encode).  The fed form has the shorter row and the longer start, and its
+// tiles leave a compute unit room for two work-groups (one, where the table of a large alphabet fills the LDS), so what
+// decides is the symbols per stream (`rows`) and the coding waves (64 streams each) the grid is sized for.  Whole
+// compress calls, time fed over time with k_encode, the slowest of 1 to 16384 streams a chunk and M = 12, 14:
+//   rows                        16    24    32    48    64    96   128   192   256   512
+//   dense, up to 192 waves    1.04  1.01  1.03  0.97  0.97  0.93  0.94  0.86  0.84  0.78
+//   dense, 256 waves          1.07  1.05  1.06  1.00  1.00  0.91  0.91  0.85  0.83  0.77
+//   dense, 512: 64 streams    1.03  0.99  0.98  0.96  0.95  0.91  0.91  0.86  0.86  0.76
+//          512: 256           1.05  1.02  1.07  1.01  1.04  0.96  0.98  0.93  0.92  0.88
+//          512: 1024          1.09  1.06  1.11  1.07  1.09  1.00  1.01  0.95  0.95  0.87
+//          512: 4096          1.28  1.23  1.24  1.16  1.21  1.17  1.17  1.09  1.03  0.93
+//   dense, 640 waves          1.70  1.61  1.63  1.60  1.53  1.52  1.51  1.38  1.35  1.28
+// CSR tensors are placed as if D were as long as it can be: at 640 and 768 waves a tensor without zeros takes up to 1.7
+// times as long fed and one with 70 % nonzeros 1.5 times, while 30 % nonzeros gain 5 to 10 %.  What a stream gets at
+// least is taken from a D with an eighth of the tensor nonzero: the longer start shows in tensors that do not fill a chunk.
+// Alphabets of 1021 to 5120 symbols (one work-group on a unit) at 288 to 512 waves: 1.11 at 128 rows, 0.95 at 512.
+constexpr uint32_t kFeedSpw = 64;           // streams per work-group of the fed encoder
+constexpr uint32_t kFeedTwoMaxA = 1020;     // alphabets up to this size leave room for a second work-group
+constexpr uint32_t kFeedLdsTabMaxA = 5120;  // and up to this one their 16-byte entries fit the LDS beside two tiles
+inline bool encoder_is_fed(const rans_params &p, uint64_t n, uint32_t A, uint32_t nc_max, uint64_t chunk_len_max) {
+  const uint32_t groups = (p.n_streams + kFeedSpw - 1) / kFeedSpw;
+  const uint64_t waves = (uint64_t)nc_max * groups;
+  const uint64_t len = p.mode == RANS_MODE_CSR ? p.rows + n / 4 : n;
+  const uint64_t rows = (len < chunk_len_max ? len : chunk_len_max) / p.n_streams;
+  if (waves <= 192) return rows >= 24;
+  if (waves <= 256) return rows >= 48;
+  if (waves > 512) return false;
+  if (A > kFeedTwoMaxA && A <= kFeedLdsTabMaxA) return rows >= 512;
+  const uint32_t least = groups <= 1 ? 48 : groups <= 4 ? 96 : groups <= 16 ? 192 : 384;
+  return rows >= (waves > 384 && least < 128 ? 128 : least);
+}
+
+// Scratch for the encoder's spilled word blocks, whichever form it takes: each chunk has this many columns of capw
+// words, a column per stream; those of one work-group are stored block by block (see k_encode).
+__host__ __device__ inline uint32_t enc_columns(uint32_t n_streams) { return (n_streams + 63u) & ~63u; }
+struct EncScratch {
+  uint16_t *base;    // the work-group's part
+  uint32_t columns;  // its columns: word blocks of eight of one stream are columns * 8 words apart
+};
+__device__ __forceinline__ EncScratch enc_scratch(uint16_t *scratch, uint32_t S, uint32_t capw, uint32_t k, uint32_t first) {
+  const uint32_t all = enc_columns(S), rest = all - first;
+  return EncScratch{scratch + ((uint64_t)k * all + first) * capw, rest < (uint32_t)kWG ? rest : (uint32_t)kWG};
+}
 
 constexpr uint32_t kCntRep = 8;  // partial histograms the CSR kernels spread their same-address additions over
 constexpr uint32_t kCsrTile = kWG * 16;  // elements per tile in the CSR count / compact kernels
@@ -144,11 +181,7 @@ Layout make_layout(const rans_params &p, uint64_t n) {
   size_t n_sc = (size_t)L.nc_max * p.n_streams;
   L.st = take(n_sc * 4);
   L.nw = take(n_sc * 4);
-  // in CSR mode D is rarely longer than half of what the grid has to be sized for
-  const uint64_t coding_waves = (uint64_t)L.nc_max * ((p.n_streams + 63) / 64);
-  const bool csr = p.mode == RANS_MODE_CSR;
-  const uint32_t feed_max = !csr && per_stream >= kFeedLongRows ? kFeedMaxWavesLong : kFeedMaxWaves;
-  L.enc_spw = (csr ? (coding_waves + 1) / 2 : coding_waves) <= feed_max ? 64 : kWG;
+  L.enc_spw = encoder_is_fed(p, n, L.A, L.nc_max, L.chunk_len_max) ? kFeedSpw : kWG;
   {
     const uint64_t wgs = (uint64_t)L.nc_max * ((p.n_streams + L.enc_spw - 1) / L.enc_spw);
     L.n_pub = (wgs > 0 && wgs <= kFusedGatherMax) ? (uint32_t)wgs : 0;
@@ -158,8 +191,7 @@ Layout make_layout(const rans_params &p, uint64_t n) {
   L.acc_off = (L.nc_max + 1 + L.n_pub + 1) & ~1u;
   L.tc_off = L.acc_off + (L.n_pub ? 2 * L.nc_max : 0);
   L.chunk_words = take(((size_t)L.tc_off + 2 * (size_t)L.n_blk) * 4);
-  // word blocks of the encoder, per work-group (enc_spw streams, absent ones included): see k_encode
-  L.scratch = take((size_t)L.nc_max * ((p.n_streams + L.enc_spw - 1) / L.enc_spw) * L.enc_spw * L.capw * 2);
+  L.scratch = take((size_t)L.nc_max * enc_columns(p.n_streams) * L.capw * 2);
   size_t enc_end = o;
   o = overlay;
   L.dec_lut = take(((size_t)2 << p.freq_bits));

@@ -446,8 +446,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
   const uint32_t top = colb + 2 * rw;
   uint32_t wp = top - 2;                                   // LDS address of the slot of the next word
   // Scratch holds the work-group's spilled 16-byte blocks block-major: block b of the stream in column c at
-  // ((b * kWG + c) * 8) words from the work-group's base.
-  uint16_t *const g0 = scratch + (uint64_t)blockIdx.x * kWG * capw + threadIdx.x * 8;
+  // ((b * columns + c) * 8) words from the work-group's base.  Only lanes with a stream spill.
+  const EncScratch spilled = enc_scratch(scratch, S, capw, k, g * kWG);
+  uint16_t *const g0 = spilled.base + threadIdx.x * 8;
   uint16_t *gp = g0;  // where the stream's next spilled block goes
   auto words_in_area = [&]() { return (top - 2 - wp) >> 1; };
   // Moves the area's complete 8-word blocks (oldest first: from the top) to scratch and what is left, fewer
@@ -459,7 +460,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
     for (uint32_t b = 0; b < nblk; b++) {
       const lds_u32 *q = (const lds_u32 *)(uintptr_t)(top - 16 * (b + 1));
       *(uint4 *)gp = make_uint4(q[0], q[1], q[2], q[3]);
-      gp += kWG * 8;
+      gp += spilled.columns * 8;
     }
     if (r && nblk) {  // the remaining words sit at the bottom end of what was used: up to the top
       for (uint32_t i = 0; i < r; i++)
@@ -469,7 +470,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
     if (all && r) {
       const lds_u32 *q = (const lds_u32 *)(uintptr_t)(top - 16);
       *(uint4 *)gp = make_uint4(q[0], q[1], q[2], q[3]);
-      gp += kWG * 8;
+      gp += spilled.columns * 8;
     }
   };
   // after every batch: a stream with fewer than kEncAhead free slots left makes room
@@ -761,7 +762,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
   if (prio_rotate) __builtin_amdgcn_s_setprio(0);
   if (!FUSE && live) spill(true);  // k_gather finds every word in scratch
   const uint32_t n_lds = (FUSE && live) ? words_in_area() : 0;                     // words still in the area
-  const uint32_t nbg = live ? (uint32_t)((gp - g0) / (kWG * 8)) : 0;               // blocks in scratch
+  const uint32_t nbg = live ? (uint32_t)((gp - g0) / (spilled.columns * 8)) : 0;   // blocks in scratch
   // without FUSE the last block may be partial: spill(true) has left wp at the top minus the r words it holds
   const uint32_t nw = !live ? 0 : (FUSE ? 8 * nbg + n_lds : ((top - 2 - wp) >> 1 ? 8 * (nbg - 1) + ((top - 2 - wp) >> 1) : 8 * nbg));
   if (!FUSE && live) {
@@ -801,7 +802,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
     auto block_src = [&](uint32_t i, uint32_t *dst_off) -> const uint4 * {
       const uint32_t o = owner_of(i), bi = i - t_bex[o];
       *dst_off = t_dst[o] + 8 * bi;
-      return (const uint4 *)(scratch + (uint64_t)blockIdx.x * kWG * capw + ((uint64_t)(t_nbg[o] - 1 - bi) * kWG + o) * 8);
+      return (const uint4 *)(spilled.base + ((uint64_t)(t_nbg[o] - 1 - bi) * spilled.columns + o) * 8);
     };
     if (n_spilled) {  // uniform
       t_bex[threadIdx.x] = bex;
@@ -935,7 +936,7 @@ __global__ __launch_bounds__(kBig) void k_chunk_scan(CtlRef ctl, uint32_t *chunk
 constexpr uint32_t kGatherTile = 8192;     // words per LDS tile
 constexpr uint32_t kFusedScanMax = 4096;   // chunks up to which the gather kernel scans the sizes itself
 template <bool FUSED_SCAN>
-__global__ __launch_bounds__(kWG) void k_gather(CtlRef ctl, const uint16_t *scratch, uint32_t capw, const uint32_t *st,
+__global__ __launch_bounds__(kWG) void k_gather(CtlRef ctl, uint16_t *scratch, uint32_t capw, const uint32_t *st,
                                                 const uint32_t *nw_arr, const uint32_t *chunk_words, uint32_t S,
                                                 uint32_t groups, uint8_t *out, uint64_t cap,
                                                 uint64_t *d_stream_bytes) {
@@ -1000,7 +1001,8 @@ __global__ __launch_bounds__(kWG) void k_gather(CtlRef ctl, const uint16_t *scra
     st32(ck + 4ull * S + 4ull * j, nw);
   }
   // block bi of the stream in read order (bi = 0: the newest, partial one) is block nb - 1 - bi as written
-  const uint16_t *g0 = scratch + (uint64_t)blockIdx.x * kWG * capw + threadIdx.x * 8;
+  const EncScratch spilled = enc_scratch(scratch, S, capw, k, g * kWG);
+  const uint16_t *g0 = spilled.base + threadIdx.x * 8;
   const uint32_t nb = (nw + 7) / 8;                                    // aligned 8-word blocks that hold the words
   const uint32_t skip = nb * 8 - nw;                                   // words of the lowest block before the first one
   uint16_t *dst = (uint16_t *)(ck + 8ull * S) + pre;                   // first word of this group
@@ -1011,7 +1013,7 @@ __global__ __launch_bounds__(kWG) void k_gather(CtlRef ctl, const uint16_t *scra
     if (lo < hi) {
       const uint32_t b_lo = (lo - ex + skip) / 8, b_hi = (hi - 1 - ex + skip) / 8;
       for (uint32_t bi = b_lo; bi <= b_hi; bi++) {
-        const uint4 q = *(const uint4 *)(g0 + (uint64_t)(nb - 1 - bi) * (kWG * 8));
+        const uint4 q = *(const uint4 *)(g0 + (uint64_t)(nb - 1 - bi) * (spilled.columns * 8));
         const uint32_t ww[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
         for (int i = 0; i < 8; i++) {

@@ -26,16 +26,14 @@ namespace {
 //
 // Measured, k_encode before against this: one chunk of 32 streams and 6272 rows 946 -> 281 us (45 ns a row; the coder's
 // eleven instructions are about 72 cycles, 30 ns, of which the two LDS accesses are 32), 25 chunks of 64 x 64 symbols
-// 15.0 -> 12.0 us, 198 chunks of 64 x 128 symbols 20.4 -> 16.3 us; where the line to k_encode lies: kFeedMaxWaves.
+// 15.0 -> 12.0 us, 198 chunks of 64 x 128 symbols 20.4 -> 16.3 us; where the line to k_encode lies: encoder_is_fed.
 //
 // When a stream's word area runs full, all streams of the wave move their complete blocks to scratch: a spill costs
 // the wave the same whether one lane or all of them take part, and streams of one tensor fill up at about the same rate.
-constexpr uint32_t kFeedSpw = 64;                  // streams per work-group
 constexpr uint32_t kFeedWaves = kWG / 64 - 1;      // feeding waves
 constexpr uint32_t kFeedPer = 8;                   // rows of a tile per feeding wave
 constexpr uint32_t kFeedRows = kFeedWaves * kFeedPer;
 constexpr uint32_t kFeedTileBytes = kFeedRows * kFeedSpw * 16;
-constexpr uint32_t kFeedLdsTabMaxA = 5120;         // 16-byte entries of alphabets up to this size fit beside two tiles
 
 // LDS_TAB: the 16-byte entries are staged in LDS (built there when build_tab), else read from global memory.
 template <class Src, bool LDS_TAB, bool MUL24>

@@ -53,12 +53,14 @@ namespace {
 enum KernelId {
   KID_MINMAX = 0, KID_QINFO, KID_QUANT_HIST, KID_SCAN, KID_CSR_COMPACT, KID_CSR_ROWS,
   KID_NORMALIZE, KID_ENCODE, KID_CHUNK_SCAN, KID_GATHER, KID_DEC_PREPARE, KID_DECODE, KID_ROW_SCAN,
-  KID_CSR_EXPAND, KID_DEQUANT, KID_RS_MASK, KID_RS_COUNT, KID_RS_COST, KID_COUNT
+  KID_CSR_EXPAND, KID_DEQUANT, KID_RS_MASK, KID_RS_COUNT, KID_RS_COST,
+  KID_ENCODE_FEED, KID_DECODE_LEAN, KID_COUNT
 };
 const char *const kKernelNames[KID_COUNT] = {
     "k_minmax", "k_qinfo", "k_quant_hist", "k_scan_u32", "k_csr_compact", "k_csr_rows",
     "k_normalize", "k_encode", "k_chunk_scan", "k_gather", "k_dec_prepare", "k_decode", "k_row_part",
-    "k_csr_to_dense", "k_dequant", "k_rs_mask", "k_rs_count", "k_rs_cost"};
+    "k_csr_to_dense", "k_dequant", "k_rs_mask", "k_rs_count", "k_rs_cost",
+    "k_encode_feed", "k_decode_lean"};
 
 struct ProfRecord {
   int kid;
@@ -356,7 +358,7 @@ int launch_encode_tail(const uint8_t *d_sym, uint64_t n, const rans_params &p, c
     static const hipError_t attr_rc =                                                                               \
         hipFuncSetAttribute((const void *)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);             \
     if (lds_e > 64 * 1024 && attr_rc != hipSuccess) return RANS_ERR_HIP;                                            \
-    PROF_LAUNCH(KID_ENCODE, kfn, dim3(n_wg_e), dim3(kWG), lds_e, st, src, tab, tab4, A, p.freq_bits, S,             \
+    PROF_LAUNCH(KID_ENCODE_FEED, kfn, dim3(n_wg_e), dim3(kWG), lds_e, st, src, tab, tab4, A, p.freq_bits, S,        \
                 p.chunk_syms, ctl, scratch, L.capw, groups, cw + L.nc_max + 1, (unsigned long long *)(cw + L.acc_off), \
                 d_stream, (uint64_t)cap, d_stream_bytes, rw_e, enc_builds, na_k);                                   \
   } while (0)
@@ -412,11 +414,11 @@ int launch_encode_tail(const uint8_t *d_sym, uint64_t n, const rans_params &p, c
   {
     const uint32_t gg = L.nc_max ? L.nc_max * groups : 1;  // an empty D still needs its one directory entry
     if (fused_scan)
-      PROF_LAUNCH(KID_GATHER, (k_gather<true>), dim3(gg), dim3(kWG), 0, st, ctl, (const uint16_t *)(ws + L.scratch),
+      PROF_LAUNCH(KID_GATHER, (k_gather<true>), dim3(gg), dim3(kWG), 0, st, ctl, (uint16_t *)(ws + L.scratch),
                   L.capw, (const uint32_t *)(ws + L.st), (const uint32_t *)(ws + L.nw),
                   (const uint32_t *)(ws + L.chunk_words), S, groups, d_stream, (uint64_t)cap, d_stream_bytes);
     else
-      PROF_LAUNCH(KID_GATHER, (k_gather<false>), dim3(gg), dim3(kWG), 0, st, ctl, (const uint16_t *)(ws + L.scratch),
+      PROF_LAUNCH(KID_GATHER, (k_gather<false>), dim3(gg), dim3(kWG), 0, st, ctl, (uint16_t *)(ws + L.scratch),
                   L.capw, (const uint32_t *)(ws + L.st), (const uint32_t *)(ws + L.nw),
                   (const uint32_t *)(ws + L.chunk_words), S, groups, d_stream, (uint64_t)cap, d_stream_bytes);
     LAUNCH_CHECK();
@@ -594,7 +596,7 @@ int decode_common(const uint8_t *d_stream, size_t stream_bytes, const rans_heade
     static const hipError_t attr_rc =                                                                              \
         hipFuncSetAttribute((const void *)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax);          \
     if (lds_fast > 64 * 1024 && attr_rc != hipSuccess) return RANS_ERR_HIP;                                        \
-    PROF_LAUNCH(KID_DECODE, kfn, grid, blk, lds_fast, st, FDEC_ARGS, sinkv);                                       \
+    PROF_LAUNCH(LEANV ? KID_DECODE_LEAN : KID_DECODE, kfn, grid, blk, lds_fast, st, FDEC_ARGS, sinkv);             \
   } while (0)
 #define FDEC_NT(SINKT, LUTT, MULV, WIDEV, sinkv)                                                                   \
   do {                                                                                                             \

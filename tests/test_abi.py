@@ -48,6 +48,19 @@ def test_workspace_bytes_and_argument_errors(lib):
     assert B.rans_workspace_bytes(B.make_params(8, 12, 1, (1 << 30) + 1, 0, 4, 0, 0), (1 << 30) + 1)[0] == B.ERR_ARG
 
 
+def test_workspace_holds_the_streams_there_are():
+    """The spilled words' scratch goes by the streams rounded up to 64, whichever coder runs: a call that changes the
+    coder needs no larger workspace."""
+    def ws(s, rows, chunks):
+        n = s * rows * chunks
+        return B.rans_workspace_bytes(B.make_params(8, 12, n, 1, B.MODE_DENSE, s, s * rows, B.F32), n)[1]
+    for s, chunks in ((64, 600), (64, 64), (320, 100), (1, 700)):
+        rows = 256
+        n_sc = s * chunks
+        words = -(-s // 64) * 64 * rows * chunks * 2
+        assert words < ws(s, rows, chunks) < words + s * rows * chunks + 8 * n_sc + 8 * chunks * (-(-s // 64) + 4) + (64 << 10)
+
+
 def test_peek_header_agrees_with_oracle_container(lib, oracle):
     import numpy as np
     x = np.maximum(np.random.default_rng(0).standard_normal(600), 0).astype(np.float32)

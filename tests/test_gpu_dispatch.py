@@ -1,0 +1,68 @@
+"""Which form of a kernel a call takes on the two sides of the lines between them, from the launches the library
+records, and the containers at those sizes byte by byte against the CPU oracle.  Needs an MI355X (-m gpu)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2511_11664_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _launched(call):
+    """Names of the kernels `call` launches."""
+    B.rans_profile_reset()
+    B.rans_profile_enable("all")
+    try:
+        call()
+        torch.cuda.synchronize()
+        return set(B.rans_profile_read())
+    finally:
+        B.rans_profile_enable(None)
+        B.rans_profile_reset()
+
+
+def _relu(n, zeros, seed=7):
+    g = torch.Generator().manual_seed(seed)
+    x = torch.randn(n, generator=g).abs() + 0.01
+    x *= torch.rand(n, generator=g) >= zeros
+    x[0] = 0
+    return x
+
+
+# streams, symbols of a stream in a chunk, coding waves of 64 streams; the fed coder pays for long streams and while its
+# work-groups find room: a compute unit holds two of them
+@pytest.mark.parametrize("s,rows,waves,fed", [
+    (64, 16, 64, False), (64, 24, 64, True), (64, 32, 256, False), (64, 48, 256, True), (64, 48, 288, True), (64, 32, 288, False),
+    (256, 64, 288, False), (256, 96, 288, True), (1024, 128, 320, False), (1024, 192, 320, True),
+    (64, 128, 512, True), (64, 96, 512, False), (64, 128, 513, False)])
+def test_dense_encoder_form(s, rows, waves, fed):
+    n = waves // -(-s // 64) * s * rows
+    print(f"[case] dense S={s} rows={rows} waves={waves} n={n}", flush=True)
+    x = _relu(n, 0.0)
+    codec = B.Codec(B.make_params(8, 12, n, 1, B.MODE_DENSE, s, s * rows, B.F32), n)
+    xd = x.cuda()
+    names = _launched(lambda: codec.compress(xd))
+    assert ("k_encode_feed" in names) == fed and ("k_encode" in names) != fed
+    ref, _ = oracle.compress(x.numpy(), oracle.make_params(8, 12, n, 1, B.MODE_DENSE, s, s * rows, 0))
+    assert codec.container(int(codec.nbytes.item())) == ref
+
+
+# CSR, where D may be as long as the grid is sized for: 2 n + rows symbols without zeros
+@pytest.mark.parametrize("zeros", [0.0, 0.3, 0.7])
+@pytest.mark.parametrize("s,rows,waves,cols,fed", [
+    (64, 64, 256, 4, True), (64, 64, 288, 16, True), (64, 64, 600, 4, False), (64, 64, 768, 64, False), (1024, 64, 512, 64, False),
+    (256, 128, 288, 300, True), (256, 128, 288, 1500, False), (64, 32, 700, 6000, False)])
+def test_csr_encoder_form(s, rows, waves, cols, fed, zeros):
+    chunk = s * rows
+    n = int(waves // -(-s // 64) * chunk / (2 + 1 / cols)) // cols * cols
+    print(f"[case] csr S={s} rows={rows} waves={waves} K={cols} zeros={zeros} n={n}", flush=True)
+    x = _relu(n, zeros)
+    codec = B.Codec(B.make_params(8, 13, n // cols, cols, B.MODE_CSR, s, chunk, B.F32), n)
+    xd = x.cuda()
+    names = _launched(lambda: codec.compress(xd))
+    assert ("k_encode_feed" in names) == fed and ("k_encode" in names) != fed
+    ref, _ = oracle.compress(x.numpy(), oracle.make_params(8, 13, n // cols, cols, B.MODE_CSR, s, chunk, 0))
+    assert codec.container(int(codec.nbytes.item())) == ref
+
