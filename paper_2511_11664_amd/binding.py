@@ -352,21 +352,26 @@ def compress_with_search(x: torch.Tensor, q_bits: int, freq_bits: int, n_streams
         raise RansError(rc)
     sym = torch.empty(n, dtype=torch.uint8, device=x.device)
     qinfo = torch.empty(4, dtype=torch.float32, device=x.device)
-    ws = torch.empty(ws_bytes + 256, dtype=torch.uint8, device=x.device)
-    rc = rans_quantize(x.reshape(-1), n, pq, sym, qinfo, ws)
+    ws_q = torch.empty(ws_bytes + 256, dtype=torch.uint8, device=x.device)
+    rc = rans_quantize(x.reshape(-1), n, pq, sym, qinfo, ws_q)
     if rc:
         raise RansError(rc)
-    # a non-finite tensor is reported by the encoder, which gets the same extrema: no wait for the status here
-    res = search_reshape(sym, q_bits)
-    p = make_params(q_bits, freq_bits, res.rows, res.cols, MODE_CSR, n_streams, chunk_syms, in_dtype)
-    rc, ws_bytes, max_bytes = rans_workspace_bytes(p, n)
-    if rc:
-        raise RansError(rc)
-    ws = torch.empty(ws_bytes + 256, dtype=torch.uint8, device=x.device)
-    stream = torch.empty(max_bytes + 16, dtype=torch.uint8, device=x.device)
-    size = _host_words(1)
-    rc = rans_encode(sym, n, p, qinfo, stream, size, ws)
-    st = rans_last_status(ws)  # synchronises
-    if rc or st:
-        raise RansError(rc or st)
+    try:
+        # a non-finite tensor is reported by the encoder, which gets the same extrema: no wait for the status here
+        res = search_reshape(sym, q_bits)
+        p = make_params(q_bits, freq_bits, res.rows, res.cols, MODE_CSR, n_streams, chunk_syms, in_dtype)
+        rc, ws_bytes, max_bytes = rans_workspace_bytes(p, n)
+        if rc:
+            raise RansError(rc)
+        ws = torch.empty(ws_bytes + 256, dtype=torch.uint8, device=x.device)
+        stream = torch.empty(max_bytes + 16, dtype=torch.uint8, device=x.device)
+        size = _host_words(1)
+        rc = rans_encode(sym, n, p, qinfo, stream, size, ws)
+        st = rans_last_status(ws)  # synchronises
+        if rc or st:
+            raise RansError(rc or st)
+    except BaseException:
+        # the quantiser has recorded the error in its workspace too: unread, it would be the next call's that gets this memory
+        rans_last_status(ws_q)
+        raise
     return stream[:int(size[0])], p, res
