@@ -141,7 +141,16 @@ inline uint32_t compute_units() {
 }
 
 constexpr uint32_t kDecWideGroupMinChunks = 192;
-constexpr uint32_t kDecLeanMaxWaves = 1024;  // decoding waves (64 streams) up to which the decoder takes its LEAN form
+// Decoding waves (64 streams) up to which the decoder takes its LEAN form, and the symbols of a stream from which: its
+// refill comes every 32 symbols, and its longer start has to pay (decompress calls with it over without it, median of 1 to
+// 512 streams, M = 8 to 13: 24 symbols 1.05, 32 0.97, 64 0.92, 256 0.82, 1024 0.75).
+constexpr uint32_t kDecLeanMaxWaves = 1024, kDecLeanMinRows = 32;
+constexpr uint32_t kDecLeanMinRowsBig = 64;  // M >= 14, with its longer build: 32 and 48 symbols 0.99 in the median, up to 1.10; 64 0.95
+// Chunks of so few streams take it only while a compute unit has at most two work-groups: 128 or more symbols a stream,
+// M = 12, with it over without it, 8 / 12 / 32 streams: 512 chunks 0.92 / 0.91 / 0.82, 640 chunks 1.09 / 0.71 / 0.81, 1024
+// chunks 1.18 / 0.83 / 1.  Both lines are void where the other form's larger LDS would make work-groups wait (M = 15, 1024
+// chunks of a stream: 0.74 to 0.80 from 1 to 1024 symbols).
+constexpr uint32_t kDecLeanFewStreams = 8;
 constexpr uint32_t kExpandOwnSumMaxTiles = 4096;
 // Up to so many rows and tiles k_csr_to_dense does without tile sums: two rounds of 16-byte loads a lane, and no more
 // work-groups than compute units read them.
@@ -541,7 +550,10 @@ int decode_common(const uint8_t *d_stream, size_t stream_bytes, const rans_heade
   // 512 rows 12.4 / 17.6 / 49.7 with the two look-ups, 13.0 / 16.8 / 39.6 with the one.
   const uint64_t n_wg_f = (uint64_t)h.n_chunks * groups_f;
   const uint32_t n_cu_f = compute_units();
-  bool lean = nt == 256 && (uint64_t)h.n_chunks * ((S + 63) / 64) <= kDecLeanMaxWaves;
+  const uint64_t rows_f = (h.p.chunk_syms && h.p.chunk_syms < h.len_d ? h.p.chunk_syms : h.len_d) / S;
+  const bool turns_f = n_wg_f > n_cu_f * (kLdsMax / lds_fast);  // the other form's work-groups would come in turns
+  bool lean = nt == 256 && (uint64_t)h.n_chunks * ((S + 63) / 64) <= kDecLeanMaxWaves &&
+              (turns_f || (rows_f >= (M >= 14 ? kDecLeanMinRowsBig : kDecLeanMinRows) && (S > kDecLeanFewStreams || n_wg_f <= 2 * n_cu_f)));
   uint32_t win_off = 0;
   if (lean) {
     const size_t win_lean = kLeanLine * (size_t)(S < nt ? S : nt);

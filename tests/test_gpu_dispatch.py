@@ -66,3 +66,23 @@ def test_csr_encoder_form(s, rows, waves, cols, fed, zeros):
     ref, _ = oracle.compress(x.numpy(), oracle.make_params(8, 13, n // cols, cols, B.MODE_CSR, s, chunk, 0))
     assert codec.container(int(codec.nbytes.item())) == ref
 
+
+# streams, symbols of a stream, chunks: the form with the short chain is for streams that outlast its refill, while all its
+# work-groups are resident (with a 32 KB table and 64 streams three on a compute unit), and not
+# for a few lanes in many work-groups
+@pytest.mark.parametrize("s,rows,chunks,lean", [
+    (64, 31, 20, False), (64, 32, 20, True), (256, 24, 100, False), (256, 64, 100, True), (64, 64, 768, True), (64, 64, 769, False),
+    (1, 64, 512, True), (8, 40, 600, False), (9, 40, 600, True), (1, 200, 700, False)])
+def test_decoder_form(s, rows, chunks, lean):
+    n = s * rows * chunks
+    print(f"[case] decode S={s} rows={rows} chunks={chunks} n={n}", flush=True)
+    x = _relu(n, 0.3)
+    p = B.make_params(8, 12, n, 1, B.MODE_DENSE, s, s * rows, B.F32)
+    codec = B.Codec(p, n)
+    nbytes = codec.compress(x.cuda())
+    hdr = codec.header(nbytes)
+    out = torch.empty(n, dtype=torch.float32, device="cuda")
+    names = _launched(lambda: codec.decompress(nbytes, hdr, out))
+    assert ("k_decode_lean" in names) == lean and ("k_decode" in names) != lean
+    _, _, y = oracle.decompress(codec.container(nbytes))
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), np.asarray(y, np.float32).view(np.uint32))
