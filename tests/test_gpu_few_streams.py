@@ -59,3 +59,15 @@ def test_table_with_inexact_multipliers():
 def test_large_alphabets(cols, m):
     n = cols * 12
     _compare(_relu(n, cols) * (torch.rand(n, generator=torch.Generator().manual_seed(1)) < 0.5), 8, m, B.MODE_CSR, cols, 32, 0)
+
+
+# tables of 513 to 4096 symbols whose deficit one symbol pays, a few do, or all of the frequent ones, with ties among them
+@pytest.mark.parametrize("cols,n_rows,m,keep", [(784, 4, 12, 0.05), (784, 5, 12, 0.5), (784, 40, 10, 0.5), (600, 3, 11, 0.02),
+                                                (1023, 9, 11, 0.9), (2000, 30, 12, 0.3), (4000, 7, 12, 0.6)])
+@pytest.mark.parametrize("levels", [2, 200])
+def test_who_pays_the_deficit(cols, n_rows, m, keep, levels):
+    n = cols * n_rows
+    g = torch.Generator().manual_seed(n + levels)
+    x = (torch.randint(1, levels, (n,), generator=g).float() * (torch.rand(n, generator=g) < keep)) if levels > 2 else (torch.rand(n, generator=g) < keep).float()
+    x[0], x[1] = 0.0, float(levels - 1)
+    _compare(x, 8, m, B.MODE_CSR, cols, 64, 64 * 16)
