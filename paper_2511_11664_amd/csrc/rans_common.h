@@ -112,9 +112,11 @@ int check_params(const rans_params *p, uint64_t n) {
 //          512: 4096          1.28  1.23  1.24  1.16  1.21  1.17  1.17  1.09  1.03  0.93
 //   dense, 640 waves          1.70  1.61  1.63  1.60  1.53  1.52  1.51  1.38  1.35  1.28
 // CSR tensors are placed as if D were as long as it can be: at 640 and 768 waves a tensor without zeros takes up to 1.7
-// times as long fed and one with 70 % nonzeros 1.5 times, while 30 % nonzeros gain 5 to 10 %.  What a stream gets at
+// times as long fed and one with 70 % nonzeros 1.5 times, while 30 % nonzeros gain 5 to 10 %; only up to 64 streams a chunk
+// of 256 rows and more lose nothing by it (without zeros 1.05 at most, 50 % nonzeros 0.72 to 0.97).  What a stream gets at
 // least is taken from a D with an eighth of the tensor nonzero: the longer start shows in tensors that do not fill a chunk.
-// Alphabets of 1021 to 5120 symbols (one work-group on a unit) at 288 to 512 waves: 1.11 at 128 rows, 0.95 at 512.
+// Alphabets of 1021 to 5120 symbols (one work-group on a unit) at 288 to 512 waves: 1.11 at 128 rows, 0.95 at 512, up to
+// 64 streams 0.98 at 256.
 constexpr uint32_t kFeedSpw = 64;           // streams per work-group of the fed encoder
 constexpr uint32_t kFeedTwoMaxA = 1020;     // alphabets up to this size leave room for a second work-group
 constexpr uint32_t kFeedLdsTabMaxA = 5120;  // and up to this one their 16-byte entries fit the LDS beside two tiles
@@ -125,8 +127,8 @@ inline bool encoder_is_fed(const rans_params &p, uint64_t n, uint32_t A, uint32_
   const uint64_t rows = (len < chunk_len_max ? len : chunk_len_max) / p.n_streams;
   if (waves <= 192) return rows >= 24;
   if (waves <= 256) return rows >= 48;
-  if (waves > 512) return false;
-  if (A > kFeedTwoMaxA && A <= kFeedLdsTabMaxA) return rows >= 512;
+  if (waves > 512) return p.mode == RANS_MODE_CSR && waves <= 768 && groups <= 1 && rows >= 256;
+  if (A > kFeedTwoMaxA && A <= kFeedLdsTabMaxA) return rows >= (groups <= 1 ? 256u : 512u);
   const uint32_t least = groups <= 1 ? 48 : groups <= 4 ? 96 : groups <= 16 ? 192 : 384;
   return rows >= (waves > 384 && least < 128 ? 128 : least);
 }

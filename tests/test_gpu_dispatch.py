@@ -53,7 +53,8 @@ def test_dense_encoder_form(s, rows, waves, fed):
 @pytest.mark.parametrize("zeros", [0.0, 0.3, 0.7])
 @pytest.mark.parametrize("s,rows,waves,cols,fed", [
     (64, 64, 256, 4, True), (64, 64, 288, 16, True), (64, 64, 600, 4, False), (64, 64, 768, 64, False), (1024, 64, 512, 64, False),
-    (256, 128, 288, 300, True), (256, 128, 288, 1500, False), (64, 32, 700, 6000, False)])
+    (256, 128, 288, 300, True), (256, 128, 288, 1500, False), (64, 256, 288, 1500, True), (64, 32, 700, 6000, False),
+    (16, 256, 768, 16, True), (16, 256, 769, 16, False)])
 def test_csr_encoder_form(s, rows, waves, cols, fed, zeros):
     chunk = s * rows
     n = int(waves // -(-s // 64) * chunk / (2 + 1 / cols)) // cols * cols
