@@ -170,11 +170,15 @@ inline uint32_t grid_for(uint64_t n, uint32_t per_block, uint32_t cap) {
 // at 2^20; compress of fp16 30.0 / 27.2, 32.2 / 29.9, 33.1 / 34.4; of fp32 27.9 / 27.1, 29.6 / 29.8, 31.7 / 33.9.
 inline bool csr_by_element(uint64_t n, size_t elem_bytes) { return n <= (1u << 20) / elem_bytes; }
 
-// Vectors of V elements a lane of k_quant_hist takes in a step of its work-group.  A dense tensor that 128 work-groups can
-// take in one step gets as few as that needs: more work-groups end with more additions to the same addresses, 12 ns
-// each, fewer leave the chip idle.  CSR mode's tile counts rely on kQIter.
+// Vectors of V elements a lane of k_quant_hist takes in a step of its work-group.  A dense tensor that a few dozen work-groups
+// can take in one step gets as few as that needs: more work-groups end with more additions to the same addresses, 12 ns
+// each, fewer leave the chip idle.  Where the line lies goes by the work of a step: quantise calls over those with always
+// four vectors, lines of 64 / 96 / 128 work-groups: 500 000 fp32 0.97 / 0.98 / 1.06, 10^6 fp32 0.98 / 0.99 / 1.03, 10^6 fp16
+// 0.89 / 0.89 / 0.93, 1.3 * 10^6 fp16 up to 1.02 / 0.97 / 0.97.  Element loads (unaligned buffers): 8 000 elements 0.95, 30 000
+// 0.98 and 40 000 1.02 with one a step.  CSR mode's tile counts rely on kQIter.
 inline uint32_t quant_vectors(uint64_t n, uint32_t V, bool csr) {
-  const uint64_t it = (n + (uint64_t)QNT * V * 128 - 1) / ((uint64_t)QNT * V * 128);
+  const uint64_t step = (uint64_t)QNT * V * (V == 1 ? 24 : V <= 4 ? 64 : 96);
+  const uint64_t it = (n + step - 1) / step;
   return csr || it > kQIter ? kQIter : it < 1 ? 1u : (uint32_t)it;
 }
 

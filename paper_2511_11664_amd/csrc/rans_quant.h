@@ -866,9 +866,10 @@ __global__ __launch_bounds__(NT) void k_quant_hist(const T *x, uint32_t n, CtlRe
   };
   // a work-group walks tiles blockIdx.x, blockIdx.x + gridDim.x, ... and flushes its histogram once
   for (uint64_t base = (uint64_t)blockIdx.x * tile; base < n; base += (uint64_t)gridDim.x * tile) {
-  // dense: the symbol stores keep the next vector's load behind them anyway, and short code is fetched sooner (a first pass
-  // over 16384 x 4096 fp16 149 -> 145 us); CSR, whose step ends with a wave scan, is 1 us slower without the unrolling
-#pragma unroll(CSR ? kQIter : 1)
+  // dense vectors: the symbol stores keep the next vector's load behind them anyway, and short code is fetched sooner (a
+  // first pass over 16384 x 4096 fp16 149 -> 145 us); CSR, whose step ends with a wave scan, is 1 us slower without the
+  // unrolling, and single elements 3 to 5 %
+#pragma unroll(CSR || !VEC ? kQIter : 1)
   for (int it = 0; it < kQIter; it++) {
     if (!CSR && (uint32_t)it >= n_it) break;
     uint64_t e0 = base + ((uint64_t)it * NT + threadIdx.x) * V;
