@@ -102,19 +102,24 @@ int check_params(const rans_params *p, uint64_t n) {
 // (k_encode_feed), or four coding waves (k_encode).  The fed form has the shorter row and the longer start, and its
 // tiles leave a compute unit room for two work-groups (one, where the table of a large alphabet fills the LDS), so what
 // decides is the symbols per stream (`rows`) and the coding waves (64 streams each) the grid is sized for.  Whole
-// compress calls, time fed over time with k_encode, the slowest of 1 to 16384 streams a chunk and M = 12, 14:
-//   rows                        16    24    32    48    64    96   128   192   256   512
-//   dense, up to 192 waves    1.04  1.01  1.03  0.97  0.97  0.93  0.94  0.86  0.84  0.78
-//   dense, 256 waves          1.07  1.05  1.06  1.00  1.00  0.91  0.91  0.85  0.83  0.77
-//   dense, 512: 64 streams    1.03  0.99  0.98  0.96  0.95  0.91  0.91  0.86  0.86  0.76
-//          512: 256           1.05  1.02  1.07  1.01  1.04  0.96  0.98  0.93  0.92  0.88
-//          512: 1024          1.09  1.06  1.11  1.07  1.09  1.00  1.01  0.95  0.95  0.87
-//          512: 4096          1.28  1.23  1.24  1.16  1.21  1.17  1.17  1.09  1.03  0.93
-//   dense, 640 waves          1.70  1.61  1.63  1.60  1.53  1.52  1.51  1.38  1.35  1.28
+// compress calls, time fed over time with k_encode, the slower of M = 12 and 14, by the streams of a chunk:
+//   rows                         4     8    12    16    24    32    48    64    96   128   192   256   512
+//   dense, up to 192 waves:
+//     1 stream                1.07  1.07  1.04  1.04  1.01  1.03  0.97  0.97  0.93  0.94  0.86  0.84  0.78
+//     64                      0.99  0.97  0.95  0.96  0.93  0.96  0.90  0.92  0.86  0.88  0.82  0.80  0.72
+//     256, 1024               1.01  1.01  0.97  0.98  0.96  1.00  0.93  0.94  0.87  0.87  0.80  0.79  0.72
+//     4096                    1.01  1.03  0.98  1.00  0.98  1.03  0.95  0.94  0.89  0.87  0.80  0.77  0.69
+//   dense, 256 waves: 4096    1.07  1.09  1.02  1.04  1.04  1.02  1.00  0.98  0.91  0.90  0.84  0.81  0.73
+//   dense, 512 waves: 64      0.97  1.00  0.95  1.03  0.99  0.98  0.96  0.95  0.91  0.91  0.86  0.86  0.76
+//     256                     1.02  1.07  1.00  1.05  1.02  1.07  1.01  1.04  0.96  0.98  0.93  0.92  0.88
+//     1024                    1.07  1.14  1.03  1.09  1.06  1.11  1.07  1.09  1.00  1.01  0.95  0.95  0.87
+//     4096                    1.23  1.33  1.19  1.28  1.23  1.24  1.16  1.21  1.17  1.17  1.09  1.03  0.93
+//   dense, 640 waves          1.70  1.66  1.51  1.70  1.61  1.63  1.60  1.53  1.52  1.51  1.38  1.35  1.28
 // CSR tensors are placed as if D were as long as it can be: at 640 and 768 waves a tensor without zeros takes up to 1.7
 // times as long fed and one with 70 % nonzeros 1.5 times, while 30 % nonzeros gain 5 to 10 %; only up to 64 streams a chunk
 // of 256 rows and more lose nothing by it (without zeros 1.05 at most, 50 % nonzeros 0.72 to 0.97).  What a stream gets at
-// least is taken from a D with an eighth of the tensor nonzero: the longer start shows in tensors that do not fill a chunk.
+// least is taken from a D with an eighth of the tensor nonzero: the longer start shows in tensors that do not fill a chunk
+// (5 % nonzeros of 4032 with 256 streams 1.18), and in tables of its own that k_normalize made (5001 symbols 1.12).
 // Alphabets of 1021 to 5120 symbols (one work-group on a unit) at 288 to 512 waves: 1.11 at 128 rows, 0.95 at 512, up to
 // 64 streams 0.98 at 256.
 constexpr uint32_t kFeedSpw = 64;           // streams per work-group of the fed encoder
@@ -123,11 +128,16 @@ constexpr uint32_t kFeedLdsTabMaxA = 5120;  // and up to this one their 16-byte 
 inline bool encoder_is_fed(const rans_params &p, uint64_t n, uint32_t A, uint32_t nc_max, uint64_t chunk_len_max) {
   const uint32_t groups = (p.n_streams + kFeedSpw - 1) / kFeedSpw;
   const uint64_t waves = (uint64_t)nc_max * groups;
-  const uint64_t len = p.mode == RANS_MODE_CSR ? p.rows + n / 4 : n;
+  const bool csr = p.mode == RANS_MODE_CSR;
+  const uint64_t len = csr ? p.rows + n / 4 : n;
   const uint64_t rows = (len < chunk_len_max ? len : chunk_len_max) / p.n_streams;
-  if (waves <= 192) return rows >= 24;
-  if (waves <= 256) return rows >= 48;
-  if (waves > 512) return p.mode == RANS_MODE_CSR && waves <= 768 && groups <= 1 && rows >= 256;
+  if (waves <= 256) {
+    if (waves > 192 && groups > (csr ? 4u : 16u)) return rows >= 48;
+    if (p.n_streams < kFeedSpw) return rows >= 24;
+    if (!csr) return rows >= (groups <= 16 ? 4u : 12u);
+    return rows >= (groups <= 4 && A <= kFeedTwoMaxA ? 8u : 24u);
+  }
+  if (waves > 512) return csr && waves <= 768 && groups <= 1 && rows >= 256;
   if (A > kFeedTwoMaxA && A <= kFeedLdsTabMaxA) return rows >= (groups <= 1 ? 256u : 512u);
   const uint32_t least = groups <= 1 ? 48 : groups <= 4 ? 96 : groups <= 16 ? 192 : 384;
   return rows >= (waves > 384 && least < 128 ? 128 : least);
