@@ -785,19 +785,22 @@ constexpr uint32_t kQuantBlocksCsr = 512;  // CSR mode, where every tile ends wi
 // while this one is worked on made it 10 % slower, by its registers).  Symbols come in one of three ways, chosen per call:
 //   kDivAny    x / s as the compiler divides
 //   kDivFast   FastDiv, the same quotient in five operations
-//   kDivRound  u = fma(x, 1 / s, z), rounded: no quotient and no clamp, where the result is certain (dense mode: in CSR mode,
-//              bound by its barriers, it gives 0.6 us of 28 and costs 4 us of longer code on a first pass).
+//   kDivRound  u = fma(x, 1 / s, z), rounded: no quotient and no clamp, where the result is certain.  For fp16 vectors
+//              in dense mode, whose eight values a load make the instructions count; fp32 is bound by its traffic (16 M
+//              values 31.3 us by kDivFast, 31.6 with this), CSR mode by its barriers.
 // The last needs |x| <= 256 s for all x, as whenever the tensor's range holds a 0.  With r1 = (1 / s)(1 + e), |e| <= 2^-23,
 // u is off x / s + z by 256 * 2^-23 and its own rounding, 2^-16 for |u| < 512; Eq. 6 as defined - the rounded quotient,
 // plus z, rounded - is off by 256 * 2^-24 and 2^-16.  Together below 8 * 10^-5, so u and Eq. 6's sum round to the same integer
 // unless u is within kRoundDoubt = 2^-13 of a half; and that integer is in 0 .. 2^Q - 1, as the exact value is at most
 // 1/2 + 6 * 10^-5 outside (z and s are rounded).  A lane with a doubtful value takes all of its vector by FastDiv: about 2^-12
-// of the values of a continuous distribution, one wave step of 256 values in 16.
-// Measured, FastDiv throughout and always four vectors a step against this: 16384 x 4096 fp16 36.7 -> 34.9 us (5.8 TB/s of
-// tensor and symbols), 395 x 4096 fp16 8.8 -> 7.5 us, 128 x 784 fp32
-// 6.3 -> 4.8 us, 3.3 M symbols counted only 7.7 -> 5.9 us.
+// of the values of a continuous distribution, one wave step of 512 values in 8.  Scales that put many of the few values of
+// fp16 on a half (a range of 255 / 64) would take most steps twice, so a wave in which a lane has met kDoubtMax doubtful
+// vectors does the rest of its tiles by kDivFast.
+// Measured, quantise calls with FastDiv throughout / with this: 16384 x 4096 fp16 58.6 / 57.9 us, with such a scale 58.4 / 59.5
+// (64.2 without the change of sides); 16 M fp16 24.3 / 23.7 and 24.1 / 25.4; 4 M, a single tile, 13.5 / 13.0 and 13.5 / 14.5.
 constexpr int kDivAny = 0, kDivFast = 1, kDivRound = 2;
 constexpr float kRoundDoubt = 0x1p-13f;
+constexpr uint32_t kDoubtMax = 3;
 template <typename T, bool VEC, int NT, bool CSR>
 __global__ __launch_bounds__(NT) void k_quant_hist(const T *x, uint32_t n, CtlRef ctl, uint32_t q_bits,
                                                     uint8_t *sym, uint32_t *cnt, int skip_zero_bin,
@@ -828,7 +831,8 @@ __global__ __launch_bounds__(NT) void k_quant_hist(const T *x, uint32_t n, CtlRe
   FastDiv fd;
   fd.init(s);
   const uint32_t rep = threadIdx.x & (kHistRep - 1);
-  const bool round_only = !CSR && fast && !degenerate && amax <= 256.0f * s;
+  constexpr bool kMayRound = !CSR && VEC && sizeof(T) == 2;
+  const bool round_only = kMayRound && fast && !degenerate && amax <= 256.0f * s;
   const uint32_t tile = NT * V * (CSR ? (uint32_t)kQIter : n_it);
   // CSR: the nonzeros of each tile of kCsrTile symbols are counted on the way.  A work-group's tile of
   // NT * V * kQIter elements is V such tiles and a wave's symbols of one step lie in one of them: the lanes'
@@ -842,8 +846,10 @@ __global__ __launch_bounds__(NT) void k_quant_hist(const T *x, uint32_t n, CtlRe
     atomicAdd(&h[a * kHistRep + rep], 1u);
     if constexpr (CSR) lane_nz += a != 0;
   };
-  auto run = [&](auto div_tag) {
+  // the tiles from the one at `base` on; returns where it stopped (kDivRound: also before the end)
+  auto run = [&](auto div_tag, uint64_t base) -> uint64_t {
   constexpr int DIV = decltype(div_tag)::value;
+  uint32_t doubted = 0;  // this lane's vectors that were done again
   auto q = [&](float v) -> uint32_t {
     const float t = DIV != kDivAny ? fd.div(v) : v / s;
     const float r = rintf(t + zf);
@@ -860,16 +866,18 @@ __global__ __launch_bounds__(NT) void k_quant_hist(const T *x, uint32_t n, CtlRe
         a[k] = (uint32_t)r;
       }
       if (!(far > 0.5f - kRoundDoubt)) return;
+      doubted++;
     }
 #pragma unroll
     for (int k = 0; k < NV; k++) a[k] = q(v[k]);
   };
   // a work-group walks tiles blockIdx.x, blockIdx.x + gridDim.x, ... and flushes its histogram once
-  for (uint64_t base = (uint64_t)blockIdx.x * tile; base < n; base += (uint64_t)gridDim.x * tile) {
-  // dense vectors: the symbol stores keep the next vector's load behind them anyway, and short code is fetched sooner (a
-  // first pass over 16384 x 4096 fp16 149 -> 145 us); CSR, whose step ends with a wave scan, is 1 us slower without the
-  // unrolling, and single elements 3 to 5 %
-#pragma unroll(CSR || !VEC ? kQIter : 1)
+  for (; base < n; base += (uint64_t)gridDim.x * tile) {
+  if (DIV == kDivRound && __any(doubted >= kDoubtMax)) break;  // of the wave: dense mode has no barrier here
+  // fp16 and byte vectors in dense mode: the symbol stores keep the next vector's load behind them anyway, and short code is
+  // fetched sooner (a first pass over 16384 x 4096 fp16 149 -> 145 us); CSR, whose step ends with a wave scan, is 1 us
+  // slower without the unrolling, single elements 3 to 5 %, fp32 1 %
+#pragma unroll(CSR || !VEC || sizeof(T) == 4 ? kQIter : 1)
   for (int it = 0; it < kQIter; it++) {
     if (!CSR && (uint32_t)it >= n_it) break;
     uint64_t e0 = base + ((uint64_t)it * NT + threadIdx.x) * V;
@@ -943,11 +951,17 @@ __global__ __launch_bounds__(NT) void k_quant_hist(const T *x, uint32_t n, CtlRe
     __syncthreads();
   }
   }
+  return base;
   };  // run
-  if constexpr (IS_SYM) run(std::integral_constant<int, kDivAny>{});
-  else if (round_only) run(std::integral_constant<int, kDivRound>{});
-  else if (fast) run(std::integral_constant<int, kDivFast>{});
-  else run(std::integral_constant<int, kDivAny>{});
+  uint64_t from = (uint64_t)blockIdx.x * tile;
+  if constexpr (IS_SYM) {
+    run(std::integral_constant<int, kDivAny>{}, from);
+  } else {
+    if constexpr (kMayRound)
+      if (round_only) from = run(std::integral_constant<int, kDivRound>{}, from);
+    if (fast) run(std::integral_constant<int, kDivFast>{}, from);
+    else run(std::integral_constant<int, kDivAny>{}, from);
+  }
   __syncthreads();
   // The counts go to the global histogram with additions that return nothing: the kernel that reads them
   // starts after this one has ended, which is all the ordering the histogram needs.

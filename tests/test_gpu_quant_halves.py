@@ -1,5 +1,6 @@
-"""Symbols at and around the rounding boundaries of Eq. 6: the quantiser takes a shorter way where the rounded value is
-certain and the exact one elsewhere, and both have to give the oracle's symbols to the last bit."""
+"""Symbols at and around the rounding boundaries of Eq. 6, to the last bit those of the oracle.  fp16 vectors in dense mode
+take a shorter way where the rounded value is certain, the exact one elsewhere and, in a wave that meets many doubtful
+values, from the next tile on; everything else takes the exact way throughout."""
 import numpy as np
 import pytest
 import torch
@@ -26,7 +27,7 @@ def _values(lo, hi, Q, n, seed):
 
 @pytest.mark.parametrize("lo,hi", [(-1.0, 1.0), (0.0, 3.7), (-92.0, 87.3), (-5.1, 0.0), (1e-6, 2.3e-6), (100.0, 101.0),
                                    (0.4999, 128.0), (-3e8, 2e8), (-1e-9, 1e-9), (255.0, 511.0), (256.5, 511.5)])
-@pytest.mark.parametrize("Q,dtype,mode", [(8, "fp32", "dense"), (6, "fp32", "csr"), (8, "fp16", "csr"), (3, "fp16", "dense")])
+@pytest.mark.parametrize("Q,dtype,mode", [(8, "fp32", "dense"), (6, "fp32", "csr"), (8, "fp16", "csr"), (3, "fp16", "dense"), (8, "fp16", "dense"), (6, "fp16", "dense")])
 @pytest.mark.parametrize("n", [4096 * 4 + 7, 1 << 20])
 def test_symbols_at_the_halves(oracle, lo, hi, Q, dtype, mode, n):
     x = _values(lo, hi, Q, n, 5)
@@ -41,4 +42,20 @@ def test_symbols_at_the_halves(oracle, lo, hi, Q, dtype, mode, n):
     sym = torch.empty(n, dtype=torch.uint8, device="cuda")
     codec.quantize(torch.from_numpy(x).cuda(), sym)
     want, _ = oracle.quantize(x, Q)
+    assert np.array_equal(sym.cpu().numpy(), np.asarray(want, np.uint8))
+
+
+# scales that put the few values of binary16 on halves, so that waves change to the exact way: after one tile of many,
+# in tensors that end inside a tile and inside a vector
+@pytest.mark.parametrize("top", [255 / 64, 255 / 32, 4.98046875, 5.1])
+@pytest.mark.parametrize("n", [256 * 32768 * 2 + 32768 * 3 + 8 * 1000 + 5, 32768 * 300 + 4099])
+def test_many_values_on_halves(oracle, top, n):
+    print(f"[case] on halves top={top} n={n}", flush=True)
+    x = torch.randn(n, generator=torch.Generator().manual_seed(n % 1000)).abs().clamp_(max=top).to(torch.float16)
+    x[0], x[1] = top, 0
+    p = B.make_params(8, 12, n, 1, B.MODE_DENSE, 1024, 1 << 18, B.F16)
+    codec = B.Codec(p, n)
+    sym = torch.empty(n, dtype=torch.uint8, device="cuda")
+    codec.quantize(x.cuda(), sym)
+    want, _ = oracle.quantize(x.numpy(), 8)
     assert np.array_equal(sym.cpu().numpy(), np.asarray(want, np.uint8))
