@@ -877,6 +877,7 @@ RsPlan rs_plan(uint64_t n, uint32_t q_bits) {
     };
     uint32_t cur = 0;  // common multiple of the open group, 0: none open
     for (uint32_t k = 0; k < P.cands.n; k++) {
+      if (P.cands.K[k] == 1) continue;  // needs no columns (nor row counts): a tensor of prime size has no other reshape
       const uint32_t K = P.cands.K[k];
       const uint64_t l2 = cur ? (uint64_t)cur / gcd(cur, K) * K : 0;
       if (cur && l2 <= kRsLcmMax) {
@@ -914,7 +915,7 @@ RsPlan rs_plan(uint64_t n, uint32_t q_bits) {
   uint32_t rows = n_words / 128;
   rows = rows < 1 ? 1 : rows > 256 ? 256 : rows;
   P.grid.wg_words = ((n_words + rows - 1) / rows + 3) & ~3u;
-  P.grid.n_rows = P.cands.n ? (n_words + P.grid.wg_words - 1) / P.grid.wg_words : 0;
+  P.grid.n_rows = P.cands.n && P.cands.K[P.cands.n - 1] > 1 ? (n_words + P.grid.wg_words - 1) / P.grid.wg_words : 0;
   const uint32_t pieces = (P.grid.wg_words + kRsPiece - 1) / kRsPiece;
   P.grid.piece = ((P.grid.wg_words + pieces - 1) / pieces + 3) & ~3u;
   // LDS histograms: a counter per lane and bin while they fit 24 KB, then up to eight per bin in 16 KB

@@ -94,15 +94,18 @@ __global__ __launch_bounds__(kWG) void k_rs_mask(const uint8_t *sym, uint32_t n,
 // 32 residues 32 w .. 32 w + 31, reads their bits in one row of L positions after the other - a 32-bit window at any
 // bit position - and adds them up in 32 vertical counters, five bit planes for up to kRsColRows rows: about 20
 // instructions per 32 positions whatever the density, where a walk over the set bits with an LDS addition each took
-// 25 us on 25.7 M symbols with 30 % nonzeros.  A work-group is 32 windows by 32 interleaved rows.
+// 25 us on 25.7 M symbols with 30 % nonzeros.  A work-group is 32 windows by 32 interleaved rows.  Turning the planes into
+// counts is the part that small tensors wait for: one counter at a time it made searches of 20 000 to 10^6 symbols with
+// few divisors and 10 % nonzeros slower than the walk (111 479 symbols, 2 candidates 18.7 -> 22.8 us; four at a time 20.2, 99 999
+// symbols, 4 candidates 21.5 / 21.6 / 19.6).  A tensor without any nonzero still takes up to 5 us longer than with the walk.
 __device__ __forceinline__ void rs_count_cols(const uint32_t *mask, uint32_t n, uint32_t L, uint32_t bx, uint32_t *hl,
-                                              uint32_t *s_c /* 32 * 33 words */) {
+                                              uint32_t *s_c /* 16 * 33 words */) {
   const uint32_t n_words = (n + 31) / 32;
   const uint32_t W = (L + 31) / 32, n_wb = (W + 31) / 32, R = (n + L - 1) / L;
   const uint32_t wx = bx % n_wb, rb = bx / n_wb;
   const uint32_t wl = threadIdx.x & 31u, w = wx * 32 + wl;
   const uint32_t r0 = rb * kRsColBlock + (threadIdx.x >> 5);
-  for (uint32_t i = threadIdx.x; i < 32 * 33; i += kRsWG) s_c[i] = 0;
+  for (uint32_t i = threadIdx.x; i < 16 * 33; i += kRsWG) s_c[i] = 0;
   __syncthreads();
   if (w < W && r0 < R) {
     const uint32_t keep = L - 32 * w >= 32 ? ~0u : (1u << (L - 32 * w)) - 1u;  // the next row's bits are not this window's
@@ -131,18 +134,23 @@ __device__ __forceinline__ void rs_count_cols(const uint32_t *mask, uint32_t n, 
         }
       }
     }
+    // four residues' counters at a time as the bytes of a word (at most kRsColRows each), added up as two pairs of 16-bit
+    // fields: the work-group's 32 rows of counters make at most 32 * kRsColRows
+    static_assert(kRsColRows < 256 && 32 * kRsColRows < 65536, "fields");
 #pragma unroll 2  // short code: straight-line code that runs once is waited for line by line
-    for (uint32_t b = 0; b < 32; b++) {
+    for (uint32_t b = 0; b < 8; b++) {
       uint32_t c = 0;
 #pragma unroll
-      for (int j = 0; j < 5; j++) c |= ((p[j] >> b) & 1u) << j;
-      atomicAdd(&s_c[b * 33 + wl], c);
+      for (int j = 0; j < 5; j++) c |= ((p[j] >> b) & 0x01010101u) << j;
+      atomicAdd(&s_c[(2 * b) * 33 + wl], c & 0x00ff00ffu);             // residues b, b + 16
+      atomicAdd(&s_c[(2 * b + 1) * 33 + wl], (c >> 8) & 0x00ff00ffu);  // b + 8, b + 24
     }
   }
   __syncthreads();
   {
     const uint32_t i = threadIdx.x;  // kRsWG == 32 * 32
-    const uint32_t t = s_c[(i & 31u) * 33 + (i >> 5)], at = wx * 1024 + i;
+    const uint32_t r = i & 31u, two = s_c[(2 * (r & 7u) + ((r >> 3) & 1u)) * 33 + (i >> 5)];
+    const uint32_t t = r & 16u ? two >> 16 : two & 0xffffu, at = wx * 1024 + i;
     if (t && at < L) atomicAdd(&hl[at], t);
   }
 }
@@ -373,7 +381,7 @@ __global__ __launch_bounds__(kRsWG) void k_rs_cost(RsCands cands, uint32_t n, ui
   }
   if (threadIdx.x < 257) s_cnt[threadIdx.x] = 0;
   uint32_t my_c = 0;
-  {
+  if (K > 1) {  // K = 1: all nonzeros are in the one column
     const uint32_t g = grps.of[k], L = grps.L[g], step = ((kRsWG * inv_c) >> 21) * K;
     const uint32_t *hg = hl + grps.off[g];
     if (threadIdx.x < step)
@@ -390,6 +398,7 @@ __global__ __launch_bounds__(kRsWG) void k_rs_cost(RsCands cands, uint32_t n, ui
   {
     if (threadIdx.x < 256) s_v[threadIdx.x] = threadIdx.x ? my_v : 0u;
     if (my_c) atomicAdd(&s_cnt[col], my_c);
+    if (K == 1 && threadIdx.x == 0) s_cnt[0] = nnz;
 #pragma unroll
     for (uint32_t u = 0; u < 3; u++)
       if (my_r[u]) atomicAdd(&s_cnt[my_a[u]], my_r[u]);

@@ -40,6 +40,8 @@ def _costs(sym: torch.Tensor, domain):
     (729 * 8191, 8, 0.5),                # odd: no row count by words, windows at every bit position
     (1012 * 32 * 61 + 32, 8, 0.3),       # just past whole pieces
     (240 * 251 * 169 * 2, 8, 0.35),      # many divisors, several groups
+    (100003, 8, 0.5), (2 * 50021, 6, 0.1),  # K = 1 alone, and one beside it: no columns or rows to count, and hardly any
+    (32 * 1024 * 17 * 31, 8, 0.97),         # counters of a column near the most their fields take
     (32 * 256 * 784 + 784 * 16, 8, 0.25), (5 * (1 << 20) - 4, 4, 0.05), (1 << 23, 8, 1.0),
 ])
 def test_costs_at_the_edges(T, Q, density):
