@@ -63,7 +63,7 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
     const uint32_t qc = (uint32_t)len / cs;  // l_D < 2^32
     nc = qc + ((uint32_t)len - qc * cs != 0);
   }
-  if (k >= nc && blockIdx.x != 0) {  // the grid is sized for the longest D; the first work-group stays for the header
+  if (k >= nc) {  // the grid is sized for the longest D (an empty one never gets here: k_normalize and k_gather write it)
     bail();
     return;
   }
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
   src.init(ctl);
   const uint64_t chunk_len = cs ? cs : len;
   const uint64_t base = (uint64_t)k * chunk_len;
-  const uint64_t n_here = k >= nc ? 0 : (len - base < chunk_len ? len - base : chunk_len);
+  const uint64_t n_here = len - base < chunk_len ? len - base : chunk_len;
   const uint32_t j0 = g * kFeedSpw + lane;
   const uint32_t rows_full = (uint32_t)(n_here / S), rem_row = (uint32_t)(n_here - (uint64_t)rows_full * S);
   const uint32_t rows = rows_full + (rem_row ? 1u : 0u);
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
     }
   };
   uint32_t wa[kFeedPer], wb[kFeedPer];
-  if (wv && n_here) {  // on their way while the table is built
+  if (wv) {  // on their way while the table is built
     fetch(wa, 0);
     fetch(wb, 1);
   }
@@ -171,17 +171,6 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
       }
       __syncthreads();
     }
-  }
-  if (k >= nc) {  // empty D: only the directory's single entry
-    if (threadIdx.x == 0) {
-      uint8_t *dir0 = out + dir_off;
-      st32(dir0, 0u);
-      st32(dir0 + 4, 0u);
-      ctl->total_bytes = payload_off;
-      if (d_stream_bytes) *d_stream_bytes = payload_off;
-    }
-    bail();
-    return;
   }
   typedef __attribute__((address_space(3))) uint16_t lds_u16;
   typedef __attribute__((address_space(3))) uint32_t lds_u32;
