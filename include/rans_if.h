@@ -9,7 +9,10 @@
  *
  * Conventions
  *   - Pointers named d_* are DEVICE pointers owned by the caller; h_* are host
- *     pointers.  The entry points with a workspace argument allocate and free
+ *     pointers.  Two outputs, d_stream_bytes and d_result, are only ever written
+ *     (plain stores; never read back or added to), so they may also be pinned host
+ *     memory that the device can write; the host reads them once the stream has
+ *     been synchronised.  The entry points with a workspace argument allocate and free
  *     nothing: scratch lives in the caller's workspace d_ws, whose size
  *     rans_workspace_bytes() returns.  d_ws must be 256-byte aligned, d_stream
  *     16-byte aligned, tensors aligned to their element size.  A workspace
@@ -117,8 +120,8 @@ int rans_quantize(const void *d_x, uint64_t n_elems, const rans_params *p, uint8
  * Sec. 2.1 Eq. 2 with renormalisation: symbols -> container.
  * d_sym: n_elems quantised symbols (< 2^Q).  d_qinfo: the extrema that go into
  * the header (device).  d_stream / stream_cap: output buffer; the number of
- * bytes written goes to *d_stream_bytes (device, 8-byte aligned; 0 on a data
- * error).  Data errors: RANS_ERR_ALPHABET, RANS_ERR_CAPACITY, RANS_ERR_ARG (a
+ * bytes written goes to *d_stream_bytes (device or pinned host memory, 8-byte
+ * aligned; 0 on a data error).  Data errors: RANS_ERR_ALPHABET, RANS_ERR_CAPACITY, RANS_ERR_ARG (a
  * symbol >= 2^Q), RANS_ERR_NONFINITE (extrema in d_qinfo), RANS_ERR_HIP (see above). */
 int rans_encode(const uint8_t *d_sym, uint64_t n_elems, const rans_params *p,
                 const rans_qinfo *d_qinfo, uint8_t *d_stream, size_t stream_cap,
@@ -175,8 +178,8 @@ int rans_decompress(const uint8_t *d_stream, size_t stream_bytes, const rans_hea
  * T_tot(N) = l_D * H(p(N)) in bits, H the entropy of the one histogram over D = v (+) c (+) r (Eq. 7),
  * in binary64.  The domain is N > sqrt(T), T/N <= 2^Q, N | T; the walk goes from N = T downwards,
  * keeps the cheapest N and stops after the first N that costs more than the one before it.
- * d_sym: the n_elems quantised symbols (< 2^Q).  *d_result (device, 8-byte aligned) receives the
- * result; the costs of ALL reshapes of the domain are computed (cand_* in walk order, the first
+ * d_sym: the n_elems quantised symbols (< 2^Q).  *d_result (device or pinned host memory, 8-byte
+ * aligned) receives the result; the costs of ALL reshapes of the domain are computed (cand_* in walk order, the first
  * n_evaluated of them are the ones the walk looks at).  An empty domain gives rows = T, cols = 1,
  * cost_bits = +inf.  More than RANS_RESHAPE_MAX_CAND reshapes in the domain: RANS_ERR_ARG.
  * Workspace: rans_search_workspace_bytes(). */

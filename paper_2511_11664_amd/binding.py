@@ -213,7 +213,7 @@ def rans_search_workspace_bytes(n_elems: int, q_bits: int):
 
 
 def rans_search_reshape(d_sym, n_elems, q_bits, d_result, d_ws) -> int:
-    """d_result: a device byte tensor of at least sizeof(ReshapeResult) bytes."""
+    """d_result: sizeof(ReshapeResult) bytes of device or pinned host memory, 8-byte aligned; the kernel only writes them."""
     return lib().rans_search_reshape(_p(d_sym), n_elems, q_bits, _p(d_result), _p(d_ws),
                                      d_ws.numel() * d_ws.element_size(), _stream())
 
