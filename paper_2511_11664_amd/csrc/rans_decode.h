@@ -304,8 +304,11 @@ struct FSinkU16 {
   uint16_t *out;
   static constexpr bool kNarrow = true;
   __device__ __forceinline__ uint32_t bits(uint32_t x, float, float, float) const { return x; }
-  // an ordinary store: D is read again by the next two kernels, which find it in the caches (31 MB of D, decode and
-  // expand of a 64 x 512 x 28 x 28 tensor at 6 bits: 58.6 us with non-temporal stores here, 51.2 us with these)
+  // An ordinary store: D is read again by the next two kernels, which find it in the caches.  Whole decompress calls, time
+  // with it over time with non-temporal stores, median over rows of 4 to 256 columns and 512 to 1024 streams, calls one
+  // after the other / each after 1 GB of other writes: D of 2 MB 1 / 1, 4 MB 1 / 0.99, 8 MB 1.02 / 0.99, 11 MB 1.04 / 0.98, 16 MB
+  // 1.02 / 0.96, 32 MB 0.98 / 0.89, 64 MB 0.94 / 0.86.  So it pays most where nothing is in the caches yet; the few per cent
+  // around 11 MB, which fit the L2s and are written out between the kernels, are its price.
   __device__ __forceinline__ static void put(uint16_t *base, uint32_t byte_off, uint32_t b) {
     *(uint16_t *)((uint8_t *)base + byte_off) = (uint16_t)b;
   }
@@ -812,11 +815,10 @@ __host__ __device__ inline ExpandLds expand_lds(uint32_t tile_rows, uint32_t K) 
 // word plus a population count) and eight independent LDS reads - no search through row offsets and no walk from
 // row to row, whose dependent LDS reads dominated an earlier form of this kernel.
 // Checked here: 1 <= v < 2^Q, c < K, c strictly increasing inside a row (a nonzero that is not the first of its
-// row must have a larger column than its predecessor), the tile sums against nnz.  r[i] <= K was checked by
-// k_row_part, which is what keeps a tile's sum below 2^16.
+// row must have a larger column than its predecessor), the tile sums against nnz.  r[i] <= K, which is
+// what keeps a tile's sum below 2^16, has been checked by k_row_part or, without tile sums, is checked here before use.
 // Without tile sums (part is null, up to kExpandAllRows rows in a few tiles) a work-group adds up and checks the
-// counts of all rows before its tile itself: two trips to the caches instead of a launch.  128 x 784 values as
-// 25 088 rows, whole decompress 17.6 -> 17.2 us (kernels 19.7 -> 17.5).
+// counts of all rows before its tile itself: two trips to the caches instead of a launch (see the rule).
 // The loads of r, of the tile sums and - once the tile's first nonzero is known - of the first 16 kWG values and
 // column indices are all issued before the scans that say how many of them the tile really has (reads past the
 // tile's own nonzeros stay inside v and c: they are bounded by nnz).
@@ -1085,8 +1087,8 @@ __global__ __launch_bounds__(kWG) void k_csr_to_dense(const uint16_t *D, const u
   for (uint32_t i = cells4 * 4 + threadIdx.x; i < cells; i += kWG) o[i] = conv(dense[i]);
 }
 
-// Inverse of Eq. 6 over a symbol array.  VEC: sixteen symbols per lane and step (both arrays 16-byte
-// aligned); the tail and unaligned arrays go one symbol at a time.
+// Inverse of Eq. 6 over a symbol array.  VEC: four runs of four symbols per lane and step, kWG runs apart (both
+// arrays 16-byte aligned); the tail and unaligned arrays go one symbol at a time.
 template <typename OutT, bool VEC>
 __global__ __launch_bounds__(kWG) void k_dequant(const uint8_t *sym, uint64_t n, const rans_qinfo *qi, CtlRef ctl,
                                                  OutT *out) {
