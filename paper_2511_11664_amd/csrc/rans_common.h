@@ -120,6 +120,9 @@ int check_params(const rans_params *p, uint64_t n) {
 // of 256 rows and more lose nothing by it (without zeros 1.05 at most, 50 % nonzeros 0.72 to 0.97).  What a stream gets at
 // least is taken from a D with an eighth of the tensor nonzero: the longer start shows in tensors that do not fill a chunk
 // (5 % nonzeros of 4032 with 256 streams 1.18), and in tables of its own that k_normalize made (5001 symbols 1.12).
+// With up to 64 streams a chunk the line is the same from 288 to 512 waves: 64 streams 24 rows 0.97 to 1.01, 32 1.02 at
+// most, 64 0.96, CSR 24 and more 0.82 to 1; 1 and 16 streams 32 rows 1.07, 48 0.99; encode of 927 744 3-bit symbols, 382
+// chunks of 64 x 38, 15.9 -> 14.8 us.
 // Alphabets of 1021 to 5120 symbols (one work-group on a unit) at 288 to 512 waves: 1.11 at 128 rows, 0.95 at 512, up to
 // 64 streams 0.98 at 256.
 constexpr uint32_t kFeedSpw = 64;           // streams per work-group of the fed encoder
@@ -139,7 +142,8 @@ inline bool encoder_is_fed(const rans_params &p, uint64_t n, uint32_t A, uint32_
   }
   if (waves > 512) return csr && waves <= 768 && groups <= 1 && rows >= 256;
   if (A > kFeedTwoMaxA && A <= kFeedLdsTabMaxA) return rows >= (groups <= 1 ? 256u : 512u);
-  const uint32_t least = groups <= 1 ? 48 : groups <= 4 ? 96 : groups <= 16 ? 192 : 384;
+  if (groups <= 1) return rows >= (p.n_streams < kFeedSpw ? 48u : 24u);
+  const uint32_t least = groups <= 4 ? 96 : groups <= 16 ? 192 : 384;
   return rows >= (waves > 384 && least < 128 ? 128 : least);
 }
 

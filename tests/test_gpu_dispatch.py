@@ -35,9 +35,10 @@ def _relu(n, zeros, seed=7):
 # work-groups find room: a compute unit holds two of them
 @pytest.mark.parametrize("s,rows,waves,fed", [
     (64, 3, 64, False), (64, 4, 64, True), (64, 4, 256, True), (16, 23, 64, False), (16, 24, 64, True), (4096, 11, 128, False),
-    (4096, 12, 128, True), (4096, 32, 256, False), (4096, 48, 256, True), (64, 48, 288, True), (64, 32, 288, False),
+    (4096, 12, 128, True), (4096, 32, 256, False), (4096, 48, 256, True), (64, 24, 288, True), (64, 23, 288, False),
     (256, 64, 288, False), (256, 96, 288, True), (1024, 128, 320, False), (1024, 192, 320, True),
-    (64, 128, 512, True), (64, 96, 512, False), (64, 128, 513, False)])
+    (64, 24, 512, True), (64, 23, 512, False), (32, 48, 512, True), (32, 47, 512, False), (256, 128, 512, True),
+    (256, 96, 512, False), (64, 128, 513, False)])
 def test_dense_encoder_form(s, rows, waves, fed):
     n = waves // -(-s // 64) * s * rows
     print(f"[case] dense S={s} rows={rows} waves={waves} n={n}", flush=True)
