@@ -142,80 +142,243 @@ __device__ __forceinline__ uint64_t wait_chunk(const unsigned long long *acc, ui
 // Sixteen bytes at an address that is only 2-byte aligned, moved to or from registers in one access.
 struct __attribute__((packed, aligned(2))) Block16 { uint32_t x, y, z, w; };
 
+// Frequency table of an alphabet of up to kEncBuildMaxA symbols, built by every encoder work-group for itself: the kernels
+// that counted have ended, so the histogram is complete and is read with ordinary loads.
+//
+// What bounds it is one chain of dependent instructions before the first row can be coded, in every work-group: loads, first
+// estimates, sums, corrections, divisions.  A thread has one symbol (two above 256), so the divisions of all symbols run side
+// by side; sums and maxima are 32-bit wave scans, one record per wave goes through LDS, and the corrections of the usual
+// cases - one symbol takes the surplus or pays the deficit - are applied to the running sums in place: two barriers.
+// From the counts to the table, one wave with four symbols a lane and 64-bit scans (no barrier, a thousand instructions) / this:
+// 25 work-groups 2.4 / 1.3 us, 752 of them with 257 symbols 3.2 / 1.8, four on every unit 2.5 / 2.4, where the sixteen waves'
+// instructions count.  Whole compress calls: 100 352 symbols 19.1 -> 16.8 us, 395 x 4096 fp16 27.1 -> 25.4, 25.7 M
+// symbols as CSR 105.8 -> 104.4.
+constexpr uint32_t kEncBuildMaxA = 2 * kWG;
 // What every thread of an encoder work-group knows once the frequency table is in its LDS.
 struct EncTable {
   uint32_t ok;     // 0: an error has been recorded
   uint32_t exact;  // the table holds the division-free entries, else {floor(2^32/f), f, F, 2^M - f}
-  uint32_t n_chunks;
-  uint64_t len_d, dir_off, payload_off;
+  uint64_t dir_off, payload_off;
 };
-// Table build by a whole encoder work-group for itself: counts from the histogram, normalisation by the first wave
-// (meanwhile() is what the work-group does beside it), entries into l_tab (16 bytes a symbol).  sh: 16 words;
-// l_tmp: 12 A bytes that are free until the coding.  Alphabets up to kNormWaveA.
-template <class Meanwhile>
-__device__ __forceinline__ EncTable enc_build_table(const CtlRef &ctl, const NormArgs &na, uint32_t A, uint32_t totalM,
-                                                    uint32_t *l_tab, uint32_t *sh, uint2 *l_tmp, Meanwhile meanwhile) {
-  uint2 *const l_tab8 = l_tmp;  // {floor(2^32/f), f | F << 16}
-  uint32_t *const l_cnt = (uint32_t *)(l_tab8 + A);
-  {  // the counts, partial histograms summed, with all of a lane's loads in flight together
-    constexpr uint32_t kParts = kCntRep + 1;  // n_rep is 0 or kCntRep
-    for (uint32_t a = threadIdx.x; a < A; a += kWG) {
-      uint32_t c[kParts];
+// The histogram's entries of a thread's symbols and the call's status: requested first of all, so that these trips to
+// memory overlap with whatever else the kernel has to fetch.
+struct EncCounts {
+  uint32_t part[2][kCntRep + 1];
+  int status;
+};
+__device__ __forceinline__ EncCounts enc_request_counts(const CtlRef &ctl, const NormArgs &na, uint32_t A) {
+  EncCounts r;
+  r.status = status_at_entry(ctl);
+  const bool two = A > kWG;
+  // always a load, from the last symbol where there is none (enc_build_table takes its count as 0): no branches between them
+  const uint32_t a = (two ? 2u : 1u) * threadIdx.x;
+  const uint32_t at[2] = {a < A ? a : A - 1, a + 1 < A ? a + 1 : A - 1};
+  auto request = [&](uint32_t u) {
+    r.part[u][0] = na.cnt[at[u]];
 #pragma unroll
-      for (uint32_t q = 0; q < kParts; q++) c[q] = q <= na.n_rep ? na.cnt[(size_t)q * A + a] : 0u;
-      uint32_t t = 0;
+    for (uint32_t k = 1; k <= kCntRep; k++) r.part[u][k] = 0;
+    if (na.n_rep) {  // kCntRep
 #pragma unroll
-      for (uint32_t q = 0; q < kParts; q++) t += c[q];
-      l_cnt[a] = t;
+      for (uint32_t k = 1; k <= kCntRep; k++) r.part[u][k] = na.cnt[k * A + at[u]];
     }
-    __syncthreads();
+  };
+  request(0);
+  if (two) request(1);
+  return r;
+}
+// len_d: l_D as the rest of the call knows it, the tensor's size (DENSE) or what the row-count kernel derived from the row
+// ends: a histogram that does not add up to it becomes an error, never a wrong table.  l_tab: 16 bytes a symbol; tmp: 33
+// words of LDS, 16-byte aligned, free until the coding; flag: a word that stays free a little longer.
+template <uint32_t PER>
+__device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const NormArgs &na, const EncCounts &raw, uint32_t A,
+                                                        uint32_t len_d, uint32_t n_chunks, uint32_t *l_tab, uint32_t *tmp,
+                                                        uint32_t *flag) {
+  constexpr uint32_t kWaves = kWG / 64, kSumMask = (1u << 20) - 1;  // the f of 512 symbols sum to less than 2^15 + 2 * 512
+  const uint32_t M = na.p.freq_bits, total = 1u << M;
+  const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6, a0 = PER * threadIdx.x;
+  uint32_t c[PER], f[PER];
+  uint32_t cnt = 0, pk = 0;        // counts; f in the low 20 bits, present symbols above
+  uint32_t key = 0;                // largest f, lowest index: f << 9 | 511 - a
+  uint32_t best = 0, best_a = 0;   // largest count, lowest index
+  bool over = false;
+#pragma unroll
+  for (uint32_t q = 0; q < PER; q++) {
+    uint32_t t = 0;
+#pragma unroll
+    for (uint32_t k = 0; k <= kCntRep; k++) t += raw.part[q][k];
+    c[q] = a0 + q < A ? t : 0u;
+    // the division is made for absent symbols too (and for an empty D, by 1): see enc_forms on branches
+    const uint32_t e = div_small_quot(c[q], M, len_d / 2, len_d ? len_d : 1u);  // at most 2^M
+    f[q] = c[q] ? (e < 1 ? 1u : e) : 0u;
+    over |= c[q] > len_d;
+    cnt += c[q];
+    pk += f[q] + ((uint32_t)(c[q] != 0) << 20);
+    const uint32_t kq = f[q] << 9 | (511u - (a0 + q));
+    key = kq > key ? kq : key;
+    if (c[q] > best) {
+      best = c[q];
+      best_a = a0 + q;
+    }
   }
-  meanwhile();
-  NormArgs nl = na;  // a copy in registers: the argument itself cannot be changed in place
-  nl.lds_cnt = l_cnt;
-  nl.enc_tab = l_tab8;
-  nl.enc_tab4 = (uint4 *)l_tab;
-  nl.quiet = blockIdx.x != 0;
-  nl.entry_checked = 1;
-  // Alphabets above 256 symbols (CSR): the wave would make five to eight symbols' entries per lane, so it stops at
-  // the frequencies and the whole work-group makes the entries, a lane per symbol (c2 as CSR: 2 us less).  With
-  // a byte alphabet the wave does it all: the second step's barriers and its instructions on all sixteen waves
-  // of a compute unit cost more than they save there (c5a: 0.8 us more).
-  const bool split = A > 256;
-  nl.fF = split ? (uint2 *)l_tab : nullptr;
-  if (threadIdx.x < 64) {  // frequencies and their running sums: one wave
-    const NormResult r = normalize_wave(ctl, nl);
-    if (threadIdx.x == 0) {
-      sh[0] = r.ok; sh[1] = split ? 0u : (r.exact ? 0u : 1u); sh[2] = r.n_chunks;
-      *(uint64_t *)(sh + 4) = r.len_d; *(uint64_t *)(sh + 6) = r.dir_off; *(uint64_t *)(sh + 8) = r.payload_off;
+  auto wave_max = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_max_scan(v), 63); };
+  auto wave_sum = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum_scan(v), 63); };
+  const uint32_t pk_inc = wave_incl_sum_scan(pk);
+  {
+    const uint32_t w_cnt = wave_sum(cnt), w_key = wave_max(key), w_best = wave_max(best);
+    const uint32_t w_best_a =
+        (uint32_t)__builtin_amdgcn_readlane((int)best_a, (int)__builtin_ctzll(__ballot(best == w_best)));
+    const bool w_over = __any(over);
+    if (lane == 63) {
+      *(uint4 *)(tmp + 8 * w) = make_uint4(w_cnt, pk_inc, w_key, w_best);
+      tmp[8 * w + 4] = w_best_a | (w_over ? 1u << 16 : 0u);
     }
+  }
+  // another work-group of the running kernel may record an error at any moment: thread 0's look decides for all
+  if (threadIdx.x == 0) {
+    tmp[32] = raw.status != 0;
+    *flag = 0;  // set below if an entry is inexact
   }
   __syncthreads();
-  EncTable t;
-  t.ok = sh[0];
-  t.n_chunks = sh[2];
-  t.len_d = *(const uint64_t *)(sh + 4); t.dir_off = *(const uint64_t *)(sh + 6); t.payload_off = *(const uint64_t *)(sh + 8);
-  t.exact = 0;
-  if (!t.ok) return t;
-  if (split) {  // the table entries: every lane its symbol's (a division each), which overwrite {f, F} in the slot
-    int inexact = 0;
-    for (uint32_t a = threadIdx.x; a < A; a += kWG) {
-      const uint2 e = nl.fF[2 * a];
-      inexact |= emit_entries(nl, a, e.x, e.y, [](uint32_t kk, uint32_t d) { return div_pow2_by(kk, d); });
+  uint32_t len = 0, sum = 0, f_before = 0, top_a = 0, top_c = 0, top_key = 0, any_over = 0;
+  uint4 rec[kWaves];
+  uint32_t rec_a[kWaves];
+#pragma unroll
+  for (uint32_t v = 0; v < kWaves; v++) {  // all on their way before the first is looked at
+    rec[v] = *(const uint4 *)(tmp + 8 * v);
+    rec_a[v] = tmp[8 * v + 4];
+  }
+  const uint32_t failed = tmp[32];
+#pragma unroll
+  for (uint32_t v = 0; v < kWaves; v++) {
+    len += rec[v].x;
+    sum += rec[v].y;
+    f_before += v < w ? rec[v].y & kSumMask : 0u;
+    top_key = rec[v].z > top_key ? rec[v].z : top_key;
+    const bool more = rec[v].w > top_c;
+    top_c = more ? rec[v].w : top_c;
+    top_a = more ? rec_a[v] & 0xffffu : top_a;
+    any_over |= rec_a[v] >> 16;
+  }
+  EncTable t{};
+  t.dir_off = kHdrBytes + (((uint64_t)A * 2 + 7) & ~7ull);
+  t.payload_off = t.dir_off + 8 * ((uint64_t)n_chunks + 1);
+  {
+    const int err = (any_over || len != len_d) ? RANS_ERR_HIP : (sum >> 20) > total ? RANS_ERR_ALPHABET
+                    : t.payload_off > na.cap ? RANS_ERR_CAPACITY : 0;
+    if (__builtin_expect(failed || err, 0)) {  // uniform
+      if (threadIdx.x == 0 && !failed) set_status(ctl, err);
+      return t;
     }
-    if (inexact) atomicOr(&sh[1], 1u);
+  }
+  const int32_t d = (int32_t)total - (int32_t)(sum & kSumMask);
+  uint32_t F = f_before + (pk_inc & kSumMask) - (pk & kSumMask);
+  // one symbol takes the surplus, or pays the whole deficit: everything behind it moves by as much
+  uint32_t star = ~0u;
+  int32_t by = 0;
+  if (len_d && d > 0) {
+    star = top_a;
+    by = d;
+  } else if (d < 0 && (int32_t)(top_key >> 9) - 1 + d >= 0) {
+    star = 511u - (top_key & 511u);
+    by = d;
+  } else if (__builtin_expect(d < 0, 0)) {
+    // Several pay, the largest f down to 1 first (lowest index on ties), then the next largest: the symbols above some v all
+    // go down to 1, and of those equal to v the first ones by index; v is the largest value with sum over f >= v of (f - 1) >=
+    // deficit, found by bisection (uniform; the buffers alternate, so one barrier a sum is enough)
+    const uint32_t deficit = (uint32_t)-d;
+    uint32_t turn = 0;
+    __syncthreads();  // every thread has read the records
+    auto group_sum = [&](uint32_t v, uint32_t *before) {
+      v = wave_sum(v);
+      uint32_t *const at = tmp + 4 * (turn++ & 1);
+      if (lane == 0) at[w] = v;
+      __syncthreads();
+      uint32_t all = 0;
+      *before = 0;
+#pragma unroll
+      for (uint32_t k = 0; k < kWaves; k++) {
+        *before += k < w ? at[k] : 0u;
+        all += at[k];
+      }
+      return all;
+    };
+    uint32_t lo = 2, hi = (top_key >> 9) + 1, above_hi = 0, unused;  // sum from lo on >= deficit > sum from hi on
+    while (hi - lo > 1) {
+      const uint32_t mid = (lo + hi) >> 1;
+      uint32_t mine = 0;
+#pragma unroll
+      for (uint32_t q = 0; q < PER; q++) mine += f[q] >= mid ? f[q] - 1 : 0u;
+      const uint32_t s = group_sum(mine, &unused);
+      if (s >= deficit) {
+        lo = mid;
+      } else {
+        hi = mid;
+        above_hi = s;
+      }
+    }
+    const uint32_t v = lo, rest = deficit - above_hi;  // what the symbols equal to v pay: v - 1 each, in index order
+    uint32_t mine = 0, rank;
+#pragma unroll
+    for (uint32_t q = 0; q < PER; q++) mine += f[q] == v;
+    group_sum(mine, &rank);
+    rank += wave_incl_sum_scan(mine) - mine;
+#pragma unroll
+    for (uint32_t q = 0; q < PER; q++) {
+      const uint32_t paid = rank * (v - 1);
+      if (f[q] > v) {
+        f[q] = 1;
+      } else if (f[q] == v) {
+        rank++;
+        if (paid < rest) f[q] -= rest - paid < v - 1 ? rest - paid : v - 1;
+      }
+    }
+    mine = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < PER; q++) mine += f[q];
+    group_sum(mine, &F);
+    F += wave_incl_sum_scan(mine) - mine;
+  }
+  bool inexact = false;
+  uint32_t m[PER], Fq[PER];
+#pragma unroll
+  for (uint32_t q = 0; q < PER; q++) {
+    const uint32_t a = a0 + q;
+    Fq[q] = F + (star < a ? (uint32_t)by : 0u);
+    F += f[q];
+    f[q] += star == a ? (uint32_t)by : 0u;
+    const EncForms e = enc_forms(M, f[q], Fq[q]);
+    m[q] = e.m;
+    if (a < A) {
+      ((uint4 *)l_tab)[a] = e.free;
+      inexact |= e.inexact;
+      if (blockIdx.x == 0) *(uint16_t *)(na.out + kHdrBytes + 2ull * a) = (uint16_t)f[q];
+    }
+  }
+  if (__any(inexact) && lane == 0) *flag = 1;
+  if (blockIdx.x == 0)
+    for (uint64_t o = kHdrBytes + 2ull * A + 2 * threadIdx.x; o < t.dir_off; o += 2 * kWG) *(uint16_t *)(na.out + o) = 0;
+  __syncthreads();  // the table is complete
+  t.ok = 1;
+  t.exact = *flag == 0;
+  if (__builtin_expect(!t.exact, 0)) {  // uniform
+#pragma unroll
+    for (uint32_t q = 0; q < PER; q++)
+      if (a0 + q < A) ((uint4 *)l_tab)[a0 + q] = make_uint4(m[q], f[q], Fq[q], total - f[q]);
     __syncthreads();
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->enc_exact = sh[1] == 0;
   }
-  t.exact = sh[1] == 0;
-  if (!t.exact) {
-    for (uint32_t a = threadIdx.x; a < A; a += kWG) {
-      const uint2 q = l_tab8[a];
-      ((uint4 *)l_tab)[a] = make_uint4(q.x, q.y & 0xffffu, q.y >> 16, totalM - (q.y & 0xffffu));
-    }
-  }
-  __syncthreads();  // the table is complete; sh and l_tmp may be written again
   return t;
+}
+__device__ __forceinline__ EncTable enc_build_table(const CtlRef &ctl, const NormArgs &na, const EncCounts &raw, uint32_t A,
+                                                    uint32_t len_d, uint32_t n_chunks, uint32_t *l_tab, uint32_t *tmp,
+                                                    uint32_t *flag) {
+  return A <= kWG ? enc_build_table_per<1>(ctl, na, raw, A, len_d, n_chunks, l_tab, tmp, flag)
+                  : enc_build_table_per<2>(ctl, na, raw, A, len_d, n_chunks, l_tab, tmp, flag);
+}
+// Chunks of a D of len symbols (l_D < 2^32: a 32-bit division, far shorter than the 64-bit one).
+__device__ __forceinline__ uint32_t enc_chunks(uint64_t len, uint32_t cs) {
+  if (len == 0 || cs == 0) return len ? 1u : 0u;
+  const uint32_t q = (uint32_t)len / cs;
+  return q + ((uint32_t)len - q * cs != 0);
 }
 
 // Totals of what lies before a work-group's words: every earlier chunk (its size gives the chunk's byte offset) and
@@ -328,26 +491,23 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
       __hip_atomic_fetch_add(chunk_acc + k, 1ull << 40, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   };
-  if (group_has_status(ctl, l_mem)) {  // through the dynamic LDS: this kernel must not have static LDS (see below)
+  const bool builds = TAB == 2 && build_tab;  // the table build looks at the status itself
+  EncCounts counts{};
+  if (builds) {
+    counts = enc_request_counts(ctl, na, A);
+  } else if (group_has_status(ctl, l_mem)) {  // through the dynamic LDS: this kernel must not have static LDS (see below)
     if (FUSE && blockIdx.x == 0 && threadIdx.x == 0 && d_stream_bytes) *d_stream_bytes = 0;
     bail();
     return;
   }
   // The grid is sized for the longest D the tensor could have (in CSR mode the host does not know the number of
   // nonzeros): a work-group whose chunk does not exist leaves before the table build, not after it.  l_D is
-  // known here - the CSR kernels stored it - and with it the number of chunks.
-  // (A dense grid has exactly one work-group per part of a chunk: nothing to leave, and no load to wait for.)
-  if (!std::is_same<Src, SrcDense>::value) {
-    const uint64_t len_pre = ctl->len_d;
-    uint32_t nc_pre = len_pre ? 1u : 0u;
-    if (len_pre && cs) {
-      const uint32_t qc = (uint32_t)len_pre / cs;  // l_D < 2^32
-      nc_pre = qc + ((uint32_t)len_pre - qc * cs != 0);
-    }
-    if (k >= nc_pre && blockIdx.x != 0) {  // the first work-group stays: it writes the header whatever l_D is
-      bail();
-      return;
-    }
+  // known here - the tensor's size, or what the CSR kernels stored - and with it the number of chunks.
+  const uint64_t len = std::is_same<Src, SrcDense>::value ? na.n_elems : ctl->len_d;
+  const uint32_t nc = enc_chunks(len, cs);
+  if (k >= nc && blockIdx.x != 0) {  // the first work-group stays: it writes the header whatever l_D is
+    bail();
+    return;
   }
   const uint32_t sh_lim = 32 - M, totalM = 1u << M;
   // LDS: [guard][word areas][table][reduction scratch][symbol stage].  The areas come first so that a slot
@@ -357,47 +517,39 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
   const uint32_t areas_end = kEncGuard + stride * kWG;  // a multiple of 16
   uint32_t *l_tab = l_mem + areas_end / 4;
   uint32_t *sh = l_tab + (TAB == 2 ? A * 4 : (TAB == 1 ? A * 2 : 0));  // 4 + 8 words for the final reductions
-  // Frequency table (Sec. 3.2's normalisation) and container geometry.  build_tab (alphabets that one wave
-  // can normalise): D's histogram is complete, because the kernels that counted have ended, and every
-  // work-group derives the same table from it for itself, straight into its LDS.  That is about three
-  // microseconds of one wave per work-group; a hand-over from the last counting work-group, or a launch of
-  // its own for the table, costs the call as much or more and needs ordering between work-groups that this
-  // does not.  The first work-group also writes the header and the table of the container.  Otherwise
-  // k_normalize has left tables and geometry in memory.
-  uint32_t nc, exact_tab;
-  uint64_t len, dir_off, payload_off;
-  if (TAB == 2 && build_tab) {
-    auto touch = [&]() {
-      if constexpr (std::is_same<Src, SrcDense>::value) {
-        // While the first wave builds the table the others touch the lines that the coder asks for first (the
-        // last 32 rows of the chunk, which is coded from its end), so that they come from the cache by then.
-        // A wave's 64-byte column shares its 128-byte lines with the neighbouring wave's.
-        if (wide && threadIdx.x >= 64) {
-          const uint64_t cl = cs ? cs : na.n_elems, b0 = (uint64_t)k * cl;
-          if (b0 < na.n_elems) {
-            const uint64_t nh = na.n_elems - b0 < cl ? na.n_elems - b0 : cl, rows = nh / S;
-            const uint32_t ln = threadIdx.x & 63;
-            const uint8_t *colp = src.bytes() + b0 + (g * kWG + (threadIdx.x - ln)) + 16 * (ln & 3);
-            uint32_t acc = 0;
+  // Frequency table (Sec. 3.2's normalisation) and container geometry.  build_tab (alphabets up to kEncBuildMaxA): every
+  // work-group derives the same table from D's histogram for itself, straight into its LDS; a hand-over from the last
+  // counting work-group, or a launch of its own for the table, costs the call as much or more and needs ordering
+  // between work-groups that this does not.  The first work-group also writes the header and the table of the container.
+  // Otherwise k_normalize has left tables and geometry in memory.
+  uint32_t exact_tab;
+  uint64_t dir_off, payload_off;
+  if (builds) {
+    uint32_t touched[2] = {0, 0};
+    if constexpr (std::is_same<Src, SrcDense>::value) {
+      // Beside the table build, touch the lines that the coder asks for first (the last 32 rows of the chunk, which is
+      // coded from its end), so that they come from the cache by then.  A wave's 64-byte column shares its 128-byte
+      // lines with the neighbouring wave's.
+      if (wide && threadIdx.x >= 64 && k < nc && g * kWG + threadIdx.x < S) {
+        const uint32_t cl = cs ? cs : (uint32_t)len, b0 = k * cl, rows = ((uint32_t)len - b0 < cl ? (uint32_t)len - b0 : cl) / S;
+        const uint32_t ln = threadIdx.x & 63;
+        const uint8_t *colp = src.bytes() + b0 + (g * kWG + (threadIdx.x - ln)) + 16 * (ln & 3);
 #pragma unroll
-            for (uint32_t u = 1; u <= 2; u++)
-              if (rows >= 16 * u) acc ^= *(const uint32_t *)(colp + (rows - 16 * u + (ln >> 2)) * S);
-            if (acc == 0x9e3779b9u && wide == 0x7fffffff) l_mem[1] = acc;  // never true: keeps the loads
-          }
-        }
+        for (uint32_t u = 0; u < 2; u++)
+          if (rows >= 16 * (u + 1)) touched[u] = *(const uint32_t *)(colp + (uint64_t)(rows - 16 * (u + 1) + (ln >> 2)) * S);
       }
-    };
-    const EncTable t = enc_build_table(ctl, na, A, totalM, l_tab, sh, (uint2 *)(sh + 16), touch);
+    }
+    const EncTable t = enc_build_table(ctl, na, counts, A, (uint32_t)len, nc, l_tab, sh + 16, sh + 15);
     if (!t.ok) {
       if (FUSE && blockIdx.x == 0 && threadIdx.x == 0 && d_stream_bytes) *d_stream_bytes = 0;
       bail();
       return;
     }
-    nc = t.n_chunks;
-    len = t.len_d; dir_off = t.dir_off; payload_off = t.payload_off;
+    if ((touched[0] ^ touched[1]) == 0x9e3779b9u && wide == 0x7fffffff) l_mem[1] = touched[0];  // never true: keeps the loads
+    dir_off = t.dir_off; payload_off = t.payload_off;
     exact_tab = t.exact;
   } else {
-    nc = ctl->n_chunks; len = ctl->len_d; dir_off = ctl->dir_off; payload_off = ctl->payload_off;
+    dir_off = ctl->dir_off; payload_off = ctl->payload_off;
     exact_tab = TAB == 2 && ctl->enc_exact != 0;
     // TAB == 2 has two forms of the table: the division-free one when every entry of it is exact for
     // this frequency table (the common case), else {floor(2^32/f), f, F, 2^M - f} with a correction step.
@@ -415,6 +567,14 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
     if (TAB != 0) __syncthreads();
   }
+  // The header, which no kernel of the call reads: written by a thread of the first work-group once its totals are out
+  // (before, it would make that work-group the last to start coding).
+  auto header = [&]() {
+    if (builds && blockIdx.x == 0 && threadIdx.x == 64) {
+      if (na.dense) ctl->len_d = len;
+      write_header(ctl, na, len, nc, dir_off, payload_off);
+    }
+  };
   const bool exact = exact_tab != 0;
   if (k >= nc) {
     if (FUSE && nc == 0 && blockIdx.x == 0 && threadIdx.x == 0) {  // empty D: only the directory's single entry
@@ -424,6 +584,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
       ctl->total_bytes = payload_off;
       if (d_stream_bytes) *d_stream_bytes = payload_off;
     }
+    header();
     bail();
     return;
   }
@@ -773,6 +934,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
   const uint32_t ex = block_excl_scan<kWG>(nw, sh, &tot);
   if (!FUSE) {
     if (threadIdx.x == 0 && tot) atomicAdd(&chunk_words[k], tot);
+    header();
     return;
   }
   if constexpr (FUSE) {
@@ -780,6 +942,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
       __hip_atomic_store(wg_pub + blockIdx.x, tot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_fetch_add(chunk_acc + k, (1ull << 40) | tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+    header();
     // The spilled blocks of the whole work-group, taken as one list in stream order and, inside a stream, in
     // read order (the last written first): thread i moves blocks i, i + kWG, ...  Their owners and places come
     // from three small tables in LDS (the stage is no longer needed).  Every thread requests its first kPre

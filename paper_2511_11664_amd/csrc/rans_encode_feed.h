@@ -51,18 +51,18 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
       __hip_atomic_fetch_add(chunk_acc + k, 1ull << 40, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   };
-  if (group_has_status(ctl, l_mem)) {
+  const bool builds = LDS_TAB && build_tab;  // the table build looks at the status itself
+  EncCounts counts{};
+  if (builds) {
+    counts = enc_request_counts(ctl, na, A);
+  } else if (group_has_status(ctl, l_mem)) {
     if (blockIdx.x == 0 && threadIdx.x == 0 && d_stream_bytes) *d_stream_bytes = 0;
     bail();
     return;
   }
   // l_D is known already: the tensor's size, or what the CSR kernels stored
   const uint64_t len = std::is_same<Src, SrcDense>::value ? na.n_elems : ctl->len_d;
-  uint32_t nc = len ? 1u : 0u;
-  if (len && cs) {
-    const uint32_t qc = (uint32_t)len / cs;  // l_D < 2^32
-    nc = qc + ((uint32_t)len - qc * cs != 0);
-  }
+  const uint32_t nc = enc_chunks(len, cs);
   if (k >= nc) {  // the grid is sized for the longest D (an empty one never gets here: k_normalize and k_gather write it)
     bail();
     return;
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
   const uint64_t base = (uint64_t)k * chunk_len;
   const uint64_t n_here = len - base < chunk_len ? len - base : chunk_len;
   const uint32_t j0 = g * kFeedSpw + lane;
-  const uint32_t rows_full = (uint32_t)(n_here / S), rem_row = (uint32_t)(n_here - (uint64_t)rows_full * S);
+  const uint32_t rows_full = (uint32_t)n_here / S, rem_row = (uint32_t)n_here - rows_full * S;  // l_D < 2^32
   const uint32_t rows = rows_full + (rem_row ? 1u : 0u);
   const uint32_t n_tiles = (rows + kFeedRows - 1) / kFeedRows;
   // Coding step p takes row rows - 1 - p; step kFeedRows i + 8 (wv - 1) + u of tile i is feeder wv's u-th.  Lanes
@@ -148,8 +148,8 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
   }
   uint32_t exact_tab;
   uint64_t dir_off, payload_off;
-  if (LDS_TAB && build_tab) {
-    const EncTable t = enc_build_table(ctl, na, A, totalM, l_tab, sh, (uint2 *)l_tile, [] {});
+  if (builds) {
+    const EncTable t = enc_build_table(ctl, na, counts, A, (uint32_t)len, nc, l_tab, l_tile, sh + 15);
     if (!t.ok) {
       if (blockIdx.x == 0 && threadIdx.x == 0 && d_stream_bytes) *d_stream_bytes = 0;
       bail();
@@ -301,6 +301,10 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
   if (threadIdx.x == 0) {
     __hip_atomic_store(wg_pub + blockIdx.x, tot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_fetch_add(chunk_acc + k, (1ull << 40) | tot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (builds && blockIdx.x == 0 && threadIdx.x == kWG - 64) {  // the header, see k_encode
+    if (na.dense) ctl->len_d = len;
+    write_header(ctl, na, len, nc, dir_off, payload_off);
   }
   // what the whole work-group needs of each stream to move its words
   uint32_t *t_n = l_tile, *t_ex = t_n + kFeedSpw, *t_at = t_ex + kFeedSpw, *t_bex = t_at + kFeedSpw, *t_nbg = t_bex + kFeedSpw;

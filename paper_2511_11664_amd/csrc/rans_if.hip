@@ -194,7 +194,7 @@ inline uint32_t *grp_counts_of(const Layout &L, uint8_t *ws) {  // nonzeros per 
 }
 
 NormArgs norm_args(const rans_params &p, const Layout &L, uint8_t *ws, uint64_t n, uint8_t *d_stream, size_t cap) {
-  return NormArgs{(const uint32_t *)(ws + L.cnt), L.cnt_rep, nullptr, (uint32_t *)(ws + L.fq), (uint2 *)(ws + L.enc_tab),
+  return NormArgs{(const uint32_t *)(ws + L.cnt), L.cnt_rep, (uint32_t *)(ws + L.fq), (uint2 *)(ws + L.enc_tab),
                   (uint4 *)(ws + L.enc_tab4), L.A, p, n, p.mode == RANS_MODE_CSR ? 0 : 1, d_stream, (uint64_t)cap};
 }
 
@@ -301,11 +301,11 @@ int launch_encode_tail(const uint8_t *d_sym, uint64_t n, const rans_params &p, c
     }
   }
   // D's histogram is complete here (the kernels that counted end before the next one starts).  Alphabets
-  // that one wave can normalise: every work-group of the encoder builds the table for itself; otherwise, and
+  // up to kEncBuildMaxA: every work-group of the encoder builds the table for itself; otherwise, and
   // when there is nothing to encode, a kernel of its own does.
   NormArgs na_k = norm_args(p, L, ws, n, d_stream, cap);
   if (!(csr && n)) na_k.n_rep = 0;  // only k_csr_rows spreads its counts over partial histograms
-  const int enc_builds = A <= kNormWaveA && L.nc_max != 0;
+  const int enc_builds = A <= kEncBuildMaxA && L.nc_max != 0;
   if (!enc_builds) {
     PROF_LAUNCH(KID_NORMALIZE, k_normalize, dim3(1), dim3(kBig), 0, st, ctl, na_k);
     LAUNCH_CHECK();
@@ -339,7 +339,6 @@ int launch_encode_tail(const uint8_t *d_sym, uint64_t n, const rans_params &p, c
     /* for three tables of kWG words                                                                             */ \
     size_t stage_e = wide_e ? (csr ? (kWG / 64) * 2 * kStageRows2 * 128 + 16 : (kWG / 64) * kStageRows * 64) : 0;   \
     if (stage_e < 3 * kWG * 4) stage_e = 3 * kWG * 4;                                                               \
-    if (enc_builds && stage_e < A * 12) stage_e = A * 12; /* counts and the table's other form, while it is built */ \
     const size_t rest_e = (TABV == 2 ? A * 16 : (TABV == 1 ? A * 8 : 0)) + 64 + stage_e;                            \
     /* slots per stream: what a stream can need (capw), as far as the LDS goes when every work-group of the grid */ \
     /* (up to four per compute unit) is to be resident at once                                                  */ \

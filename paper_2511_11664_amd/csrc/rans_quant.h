@@ -230,7 +230,6 @@ __device__ __forceinline__ uint64_t ld64(const uint8_t *p) { return (uint64_t)ld
 struct NormArgs {
   const uint32_t *cnt;      // histogram of D; n_rep partial histograms of A words each follow it (their sum counts)
   uint32_t n_rep;
-  const uint32_t *lds_cnt;  // the folded counts in LDS, when the calling kernel has put them there (set inside it)
   uint32_t *fq;
   uint2 *enc_tab;
   uint4 *enc_tab4;
@@ -240,30 +239,10 @@ struct NormArgs {
   int dense;
   uint8_t *out;
   uint64_t cap;
-  // The extrema, when the kernel that builds the table has computed them itself (set inside that kernel;
-  // the control block's copy was then written by another of its work-groups and is not read).
-  int mm_given;
-  float x_min, x_max;
-  // Set by a kernel in which every work-group builds the table for itself (the encoder): only the first one
-  // writes the container's header and table and the control block's geometry; the others keep what they
-  // compute to themselves.  0: the caller is the table's only builder and writes everything.
-  int quiet;
-  int entry_checked;  // the caller has looked at the call's status already (set inside the calling kernel)
-  // Set by a kernel whose whole work-group makes the table entries (emit_entries) after one wave has normalised:
-  // the wave then only leaves {f, F} of symbol a in fF[2 a] (the first half of the symbol's 16-byte table slot).
-  uint2 *fF;
-};
-// What the table build leaves in the registers of the wave or work-group that ran it.
-struct NormResult {
-  uint32_t ok;  // 0: an error has been recorded, nothing below is valid
-  uint32_t exact;
-  uint32_t n_chunks;
-  uint64_t len_d, dir_off, payload_off;
 };
 // Count of symbol a: the histogram's entry plus those of the partial histograms behind it.  Plain loads: the
 // histogram was completed by kernels that ended before the one that reads it began.
 __device__ __forceinline__ uint32_t hist_count(const NormArgs &na, uint32_t a) {
-  if (na.lds_cnt) return na.lds_cnt[a];
   uint32_t c = na.cnt[a];
   for (uint32_t k = 1; k <= na.n_rep; k++) c += na.cnt[(size_t)k * na.A + a];
   return c;
@@ -287,30 +266,39 @@ __device__ __forceinline__ void write_header(const CtlRef &ctl, const NormArgs &
   st32(out + 48, p.n_streams);
   st32(out + 52, p.chunk_syms);
   st32(out + 56, (uint32_t)n_chunks);
-  st32(out + 60, __float_as_uint(na.mm_given ? na.x_min : ctl->x_min));
-  st32(out + 64, __float_as_uint(na.mm_given ? na.x_max : ctl->x_max));
+  st32(out + 60, __float_as_uint(ctl->x_min));
+  st32(out + 64, __float_as_uint(ctl->x_max));
   for (uint32_t o = 68; o < kHdrBytes; o += 4) st32(out + o, 0u);
 }
 
-// floor(n / d) for n < 2^48 and 1 <= d < 2^32 when that quotient is below 2^17, without an integer or
-// binary64 division (each a long dependent instruction sequence here).  The binary32 estimate n * (1 / d)
-// carries a relative error below 2^-21 (two conversions, a reciprocal good to one unit in the last place, a
-// product), that is less than 1/16 absolute for such quotients, so its truncation is the quotient or one
-// off; the exact remainder then says which.
-__device__ __forceinline__ uint32_t div_small_quot(uint64_t n, uint32_t d) {
-  const float nf = __builtin_fmaf((float)(uint32_t)(n >> 32), 4294967296.0f, (float)(uint32_t)n);
+// floor((c 2^sh + add) / d) for sh <= 15, add < 2^31 and 1 <= d < 2^32 when that quotient is below 2^17, without an integer or
+// binary64 division (each a long dependent instruction sequence here).  The binary32 estimate of the dividend
+// times the reciprocal of d carries a relative error below 2^-21 (conversions, one fused multiply-add, a reciprocal
+// good to one unit in the last place, a product), that is less than 1/16 absolute for such quotients, so its truncation
+// is the quotient or one off; the exact remainder then says which.
+__device__ __forceinline__ uint32_t div_small_quot(uint32_t c, uint32_t sh, uint32_t add, uint32_t d) {
+  const float nf = __builtin_fmaf((float)c, (float)(1u << sh), (float)add);
   uint32_t q = (uint32_t)(nf * __builtin_amdgcn_rcpf((float)d));
-  const int64_t r = (int64_t)n - (int64_t)((uint64_t)q * d);
+  const int64_t r = (int64_t)(((uint64_t)c << sh) + add) - (int64_t)((uint64_t)q * d);
   q = r < 0 ? q - 1 : (r >= (int64_t)d ? q + 1 : q);
   return q;
 }
-// floor(2^(32+k) / d) for 2^k <= d < 2^(k+1), d < 2^16: long division in base 2^16, whose two digits
-// are quotients of the kind above (the first lies in (2^15, 2^16], the second below 2^16).
-__device__ __forceinline__ uint64_t div_pow2_by(uint32_t k, uint32_t d) {
-  const uint32_t n1 = 1u << (16 + k);
-  const uint32_t q1 = div_small_quot(n1, d);
-  const uint32_t r1 = n1 - q1 * d;  // < d
-  const uint32_t q2 = div_small_quot((uint64_t)r1 << 16, d);
+// floor(2^(32+k) / d) for 2^k <= d < 2^(k+1), d < 2^16, and its remainder: long division in base 2^16, whose two digits
+// are quotients of the kind above (the first lies in (2^15, 2^16], the second below 2^16).  Dividends are below 2^32
+// and the estimates' remainders between -d and 2 d, so 32 bits do.
+__device__ __forceinline__ uint64_t div_pow2_by(uint32_t k, uint32_t d, uint32_t *rem) {
+  const float r = __builtin_amdgcn_rcpf((float)d);
+  auto digit = [&](uint32_t n, uint32_t *left) {
+    uint32_t q = (uint32_t)((float)n * r);
+    int32_t t = (int32_t)(n - q * d);
+    const bool low = t < 0, high = t >= (int32_t)d;
+    q = low ? q - 1 : high ? q + 1 : q;
+    *left = (uint32_t)(low ? t + (int32_t)d : high ? t - (int32_t)d : t);
+    return q;
+  };
+  uint32_t r1;
+  const uint32_t q1 = digit(1u << (16 + k), &r1);
+  const uint32_t q2 = digit(r1 << 16, rem);
   return ((uint64_t)q1 << 16) + q2;
 }
 
@@ -321,7 +309,8 @@ __global__ __launch_bounds__(kWG) void k_selftest_divide(uint32_t *mismatches, u
   uint32_t bad = 0;
   if (i >= 1 && i < 65536) {
     const uint32_t d = (uint32_t)i, k = 31u - (uint32_t)__clz((int)d);
-    bad += div_pow2_by(k, d) != (1ull << (32 + k)) / d;
+    uint32_t rem;
+    bad += div_pow2_by(k, d, &rem) != (1ull << (32 + k)) / d || rem != (1ull << (32 + k)) % d;
   }
   for (uint64_t t = i; t < n_random; t += (uint64_t)gridDim.x * kWG) {
     // a divisor of 1 .. 32 bits, a quotient below 2^17 and a remainder, from a mixing function of t
@@ -335,13 +324,13 @@ __global__ __launch_bounds__(kWG) void k_selftest_divide(uint32_t *mismatches, u
     uint64_t h3 = h2 * 0xd6e8feb86659fd93ull; h3 ^= h3 >> 32;
     const uint32_t r = t % 3 == 0 ? 0u : (t % 3 == 1 ? d - 1 : (uint32_t)(h3 % d));  // both ends of the remainder's range
     const uint64_t n = (uint64_t)q * d + r;
-    if (n < (1ull << 48)) bad += div_small_quot(n, d) != q;
+    const uint32_t sh = 1 + (uint32_t)(h % 15);
+    if (n >> sh < (1ull << 32)) bad += div_small_quot((uint32_t)(n >> sh), sh, (uint32_t)n & ((1u << sh) - 1u), d) != q;
   }
   if (bad) atomicAdd(mismatches, bad);
 }
 
-// Everything stored per symbol: f in the container, the encoder's two table entries.  div(k, d) returns
-// floor(2^(32+k) / d) for 2^k <= d < 2^(k+1), d < 2^16.  Returns whether the division-free entry is inexact.
+// The encoder's two table entries of a symbol.
 //
 // Division-free entry {lim1, mx, Fx | sh << 16, 2^M - f}: the coder renormalises when s > lim1 and
 // then takes q = mulhi(s, mx) >> sh for floor(s / f) in Eq. 2.  At that point s <= lim1 =
@@ -353,25 +342,25 @@ __global__ __launch_bounds__(kWG) void k_selftest_divide(uint32_t *mismatches, u
 //
 // The one division is made for every symbol, whatever its case, and the cases select afterwards: the
 // divisions of a lane's symbols are then independent instruction streams that overlap, where branches
-// around them would run them one after the other.  The fallback entry's floor(2^32 / f) is the same
+// around them would run them one after the other.  The other form's floor(2^32 / f) is the same
 // quotient shifted down by k (floors of successive integer divisions compose).
-template <class Div>
-__device__ __forceinline__ int emit_entries(const NormArgs &na, uint32_t a, uint32_t f, uint32_t F, Div div,
-                                            bool store = true) {
-  const uint32_t M = na.p.freq_bits, total = 1u << M;
+struct EncForms {
+  uint4 free;     // the division-free form
+  uint32_t m;     // floor(2^32 / f) for f >= 2, 2^32 - 1 for f = 1: with it mulhi(s, m) is floor(s / f) or one less
+  bool inexact;   // the division-free form is not exact for every state
+};
+__device__ __forceinline__ EncForms enc_forms(uint32_t M, uint32_t f, uint32_t F) {
   const uint32_t fd = f ? f : 1u;
   const uint32_t k = 31u - (uint32_t)__clz((int)fd);
-  const uint64_t two = 1ull << (32 + k);
-  const uint64_t quo = div(k, fd);  // 2^32 for a power of two, else below 2^32 (f > 2^k)
-  // floor(2^32 / f) for f >= 2, 2^32 - 1 for f = 1: with it mulhi(s, m) is floor(s / f) or one less
-  const uint32_t m = f <= 1 ? 0xffffffffu : (uint32_t)(quo >> k);
-  const uint32_t cmpl = total - f;
+  uint32_t rem;
+  const uint64_t quo = div_pow2_by(k, fd, &rem);  // 2^32 for a power of two, else below 2^32 (f > 2^k)
+  EncForms r;
+  r.m = f <= 1 ? 0xffffffffu : (uint32_t)(quo >> k);
+  const uint32_t cmpl = (1u << M) - f;
   const uint32_t lim1 = (f << (32 - M)) - 1u;
   const bool pow2 = (f & (f - 1)) == 0;  // also f = 0, 1
-  const uint64_t mq = quo + 1;
-  const uint64_t e = mq * fd - two;
-  const int inexact = !pow2 && (uint64_t)lim1 * e >= two;
-  uint32_t mx = pow2 ? 0x80000000u : (uint32_t)mq, sh = pow2 ? k - 1 : k, Fx = F;
+  r.inexact = !pow2 && (__umulhi(lim1, fd - rem) >> k) != 0;  // e = f - the division's remainder
+  uint32_t mx = pow2 ? 0x80000000u : (uint32_t)quo + 1u, sh = pow2 ? k - 1 : k, Fx = F;
   if (f == 1) {
     mx = 0xffffffffu;
     sh = 0;
@@ -380,12 +369,18 @@ __device__ __forceinline__ int emit_entries(const NormArgs &na, uint32_t a, uint
     mx = 0;
     sh = 0;
   }
+  r.free = make_uint4(lim1, mx, Fx | (sh << 16), cmpl);
+  return r;
+}
+// Everything stored per symbol: f in the container, the two table entries.  Returns whether the division-free entry is inexact.
+__device__ __forceinline__ int emit_entries(const NormArgs &na, uint32_t a, uint32_t f, uint32_t F, bool store = true) {
+  const EncForms e = enc_forms(na.p.freq_bits, f, F);
   if (store) {  // a symbol of the alphabet (the caller may pass lanes beyond it, with f = 0)
-    na.enc_tab[a] = make_uint2(m, f | (F << 16));
-    if (!na.quiet) *(uint16_t *)(na.out + kHdrBytes + 2ull * a) = (uint16_t)f;
-    na.enc_tab4[a] = make_uint4(lim1, mx, Fx | (sh << 16), cmpl);
+    na.enc_tab[a] = make_uint2(e.m, f | (F << 16));
+    *(uint16_t *)(na.out + kHdrBytes + 2ull * a) = (uint16_t)f;
+    na.enc_tab4[a] = e.free;
   }
-  return store && inexact;
+  return store && e.inexact;
 }
 
 __device__ void normalize_body(const CtlRef &ctl, const NormArgs &na) {
@@ -425,7 +420,7 @@ __device__ void normalize_body(const CtlRef &ctl, const NormArgs &na) {
     uint32_t c = hist_count(na, a);
     uint32_t f = 0;
     if (c) {
-      const uint32_t q = div_small_quot((uint64_t)c * total + len / 2, (uint32_t)len);  // at most 2^M
+      const uint32_t q = div_small_quot(c, M, (uint32_t)len / 2, (uint32_t)len);  // at most 2^M
       f = q < 1 ? 1u : q;
       uint64_t key = ((uint64_t)c << 32) | (0xffffffffu - a);  // max count, lowest index
       best_cnt = key > best_cnt ? key : best_cnt;
@@ -477,7 +472,7 @@ __device__ void normalize_body(const CtlRef &ctl, const NormArgs &na) {
     uint32_t f = a < A ? fq[a] : 0, tot;
     uint32_t F = carry + block_excl_scan<kBig>(f, sh32, &tot);
     if (a < A) {
-      inexact |= emit_entries(na, a, f, F, [](uint32_t k, uint32_t d) { return div_pow2_by(k, d); });
+      inexact |= emit_entries(na, a, f, F);
     }
     carry += tot;
     __syncthreads();
@@ -532,7 +527,7 @@ __device__ void normalize_block(const CtlRef &ctl, const NormArgs &na) {
   uint64_t sum = 0, best = 0;
 #pragma unroll
   for (int q = 0; q < PER; q++) {
-    const uint32_t e = div_small_quot((uint64_t)c[q] * total + len / 2, len ? (uint32_t)len : 1u);  // at most 2^M
+    const uint32_t e = div_small_quot(c[q], M, (uint32_t)len / 2, len ? (uint32_t)len : 1u);  // at most 2^M
     f[q] = c[q] ? (e < 1 ? 1u : e) : 0u;
     const uint64_t key = ((uint64_t)c[q] << 32) | (0xffffffffu - (a0 + q));  // max count, lowest index
     best = c[q] && key > best ? key : best;
@@ -564,7 +559,7 @@ __device__ void normalize_block(const CtlRef &ctl, const NormArgs &na) {
     };
     // The largest f is that of the largest count.  It pays alone if it can - the usual case, without a sum; otherwise
     // v is below it (present symbols fit 2^M, so the sum over f >= 2 is at least the deficit).
-    const uint32_t f_max = div_small_quot((best >> 32) * total + len / 2, (uint32_t)len);
+    const uint32_t f_max = div_small_quot((uint32_t)(best >> 32), M, (uint32_t)len / 2, (uint32_t)len);
     uint32_t lo = deficit < f_max ? f_max : 2, hi = f_max + 1, above_hi = 0;  // above(lo) >= deficit > above(hi)
     while (hi - lo > 1) {
       const uint32_t mid = (lo + hi) >> 1, t = above(mid);
@@ -608,7 +603,7 @@ __device__ void normalize_block(const CtlRef &ctl, const NormArgs &na) {
   int inexact = 0;
 #pragma unroll
   for (int q = 0; q < PER; q++) {
-    inexact |= emit_entries(na, a0 + q, f[q], F, [](uint32_t k, uint32_t dv) { return div_pow2_by(k, dv); }, a0 + q < A);
+    inexact |= emit_entries(na, a0 + q, f[q], F, a0 + q < A);
     F += f[q];
   }
   inexact = __syncthreads_or(inexact);
@@ -616,147 +611,8 @@ __device__ void normalize_block(const CtlRef &ctl, const NormArgs &na) {
   for (uint64_t o = table_off + 2ull * A + 2 * threadIdx.x; o < dir_off; o += 2 * kBig) *(uint16_t *)(na.out + o) = 0;
 }
 
-// The same as normalize_body for alphabets of up to 64 PER symbols, by ONE wave without a barrier: lane l
-// owns the symbols PER l .. PER l + PER - 1, sums and maxima are wave scans.  Called by the first wave of a
-// work-group (of the encoder, where every work-group builds the table for itself, or of k_normalize).  About
-// a thousand instructions of one wave; sharing the symbols out over the four waves of an encoder work-group
-// was measured and is no faster, since the barriers and the four-fold instruction issue eat the gain.
-constexpr uint32_t kNormWaveA = 512;
-template <int PER>
-__device__ __forceinline__ NormResult normalize_wave_per(const CtlRef &ctl, const NormArgs &na) {
-  const uint32_t lane = threadIdx.x & 63;
-  const uint32_t A = na.A;
-  const rans_params &p = na.p;
-  const uint32_t M = p.freq_bits, total = 1u << M;
-  NormResult res{};
-  if (!na.entry_checked && __ballot(status_at_entry(ctl) != 0) != 0) return res;  // one decision for the wave
-  auto total64 = [](uint64_t v) { return lane63_64(wave_incl_scan64(v, [](uint64_t a, uint64_t b) { return a + b; })); };
-  auto max64 = [](uint64_t v) { return lane63_64(wave_incl_scan64(v, [](uint64_t a, uint64_t b) { return a > b ? a : b; })); };
-  uint32_t c[PER];
-#pragma unroll
-  for (int q = 0; q < PER; q++) {
-    const uint32_t a = PER * lane + q;
-    c[q] = a < A ? hist_count(na, a) : 0;
-  }
-  uint64_t lp = 0;  // l_D in the low 40 bits, the number of present symbols above
-#pragma unroll
-  for (int q = 0; q < PER; q++) lp += (uint64_t)c[q] + ((uint64_t)(c[q] != 0) << 40);
-  lp = total64(lp);
-  const uint64_t len = lp & ((1ull << 40) - 1), present = lp >> 40;
-  // l_D as the rest of the call knows it: the tensor's size (DENSE), or - CSR mode - what the row-count kernel
-  // derived from the row ends.  A histogram that does not add up to it becomes an error, never a wrong table.
-  const uint64_t len_d = na.dense ? na.n_elems : ctl->len_d;
-  if (na.dense && !na.quiet && lane == 0) ctl->len_d = len_d;
-  if (present > total || len != len_d) {
-    if (lane == 0) set_status(ctl, len != len_d ? RANS_ERR_HIP : RANS_ERR_ALPHABET);
-    return res;
-  }
-  // first estimate, its sum, the symbol with the largest count
-  uint32_t f[PER];
-  uint64_t sum = 0, best = 0;
-#pragma unroll
-  for (int q = 0; q < PER; q++) {
-    // the division is made for absent symbols too (and for an empty D, by 1): see emit_entries on branches
-    const uint32_t e = div_small_quot((uint64_t)c[q] * total + len / 2, len ? (uint32_t)len : 1u);  // at most 2^M
-    f[q] = c[q] ? (e < 1 ? 1u : e) : 0u;
-    const uint64_t key = ((uint64_t)c[q] << 32) | (0xffffffffu - (PER * lane + q));  // max count, lowest index
-    best = c[q] && key > best ? key : best;
-    sum += f[q];
-  }
-  sum = total64(sum);
-  best = max64(best);
-  int64_t d = (int64_t)total - (int64_t)sum;
-  auto adjust = [&](uint32_t a_star, int64_t by) {  // f[a_star] += by, in the lane that owns it
-#pragma unroll
-    for (int q = 0; q < PER; q++)
-      if (PER * lane + q == a_star) f[q] = (uint32_t)((int64_t)f[q] + by);
-  };
-  if (len && d > 0) {
-    adjust(0xffffffffu - (uint32_t)best, d);
-    d = 0;
-  }
-  while (d < 0) {  // uniform: d is identical in every lane
-    uint64_t kb = 0;
-#pragma unroll
-    for (int q = 0; q < PER; q++) {
-      const uint64_t key = ((uint64_t)f[q] << 32) | (0xffffffffu - (PER * lane + q));
-      kb = PER * lane + q < A && key > kb ? key : kb;
-    }
-    kb = max64(kb);
-    int64_t take = (int64_t)(kb >> 32) - 1;
-    if (take > -d) take = -d;
-    adjust(0xffffffffu - (uint32_t)kb, -take);
-    d += take;
-  }
-  // container geometry
-  // l_D < 2^32 (at most 3 * 2^30): a 32-bit division, far shorter than the 64-bit one
-  uint64_t n_chunks = len_d == 0 ? 0 : 1;
-  if (len_d && p.chunk_syms) {
-    const uint32_t qc = (uint32_t)len_d / p.chunk_syms;
-    n_chunks = qc + ((uint32_t)len_d - qc * p.chunk_syms != 0);
-  }
-  const uint64_t table_off = kHdrBytes;
-  const uint64_t dir_off = table_off + (((uint64_t)A * 2 + 7) & ~7ull);
-  const uint64_t payload_off = dir_off + 8 * (n_chunks + 1);
-  if (payload_off > na.cap) {
-    if (lane == 0) set_status(ctl, RANS_ERR_CAPACITY);
-    return res;
-  }
-  if (!na.quiet && lane == 0) write_header(ctl, na, len_d, n_chunks, dir_off, payload_off);
-  // cumulative sum, encoder tables, stored table
-  uint32_t mine = 0;
-#pragma unroll
-  for (int q = 0; q < PER; q++) mine += f[q];
-  uint32_t F = wave_incl_sum_scan(mine) - mine;
-  if (na.fF) {  // the entries are made by the caller's whole work-group
-#pragma unroll
-    for (int q = 0; q < PER; q++) {
-      const uint32_t a = PER * lane + q;
-      if (a < A) na.fF[2 * a] = make_uint2(f[q], F);
-      F += f[q];
-    }
-    if (!na.quiet)
-      for (uint64_t o = table_off + 2ull * A + 2 * lane; o < dir_off; o += 2 * 64) *(uint16_t *)(na.out + o) = 0;
-    res.ok = 1;
-    res.n_chunks = (uint32_t)n_chunks;
-    res.len_d = len_d;
-    res.dir_off = dir_off;
-    res.payload_off = payload_off;
-    return res;
-  }
-  int inexact = 0;
-#pragma unroll
-  for (int q = 0; q < PER; q++) {
-    const uint32_t a = PER * lane + q;
-    inexact |= emit_entries(na, a, f[q], F, [](uint32_t k, uint32_t d) { return div_pow2_by(k, d); }, a < A);
-    F += f[q];
-  }
-  const bool any_inexact = __ballot(inexact) != 0;
-  if (!na.quiet) {
-    if (lane == 0) ctl->enc_exact = any_inexact ? 0u : 1u;
-    for (uint64_t o = table_off + 2ull * A + 2 * lane; o < dir_off; o += 2 * 64) *(uint16_t *)(na.out + o) = 0;
-  }
-  res.ok = 1;
-  res.exact = any_inexact ? 0u : 1u;
-  res.n_chunks = (uint32_t)n_chunks;
-  res.len_d = len_d;
-  res.dir_off = dir_off;
-  res.payload_off = payload_off;
-  return res;
-}
-
-__device__ __forceinline__ NormResult normalize_wave(const CtlRef &ctl, const NormArgs &na) {
-  // as few symbols per lane as the alphabet allows (CSR with K = 2^Q has 2^Q + 1 symbols)
-  if (na.A <= 256) return normalize_wave_per<4>(ctl, na);
-  if (na.A <= 320) return normalize_wave_per<5>(ctl, na);
-  if (na.A <= 384) return normalize_wave_per<6>(ctl, na);
-  return normalize_wave_per<8>(ctl, na);
-}
-
 __global__ __launch_bounds__(kBig) void k_normalize(CtlRef ctl, NormArgs na) {
-  if (na.A <= kNormWaveA) {
-    if (threadIdx.x < 64) normalize_wave(ctl, na);
-  } else if (na.A <= kBig) {  // as few symbols a thread as hold them all: each is a division and its stores, one after the other
+  if (na.A <= kBig) {  // as few symbols a thread as hold them all: each is a division and its stores, one after the other
     normalize_block<1>(ctl, na);
   } else if (na.A <= 2 * kBig) {
     normalize_block<2>(ctl, na);
