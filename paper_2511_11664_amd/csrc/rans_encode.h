@@ -189,7 +189,11 @@ __device__ __forceinline__ EncCounts enc_request_counts(const CtlRef &ctl, const
 // len_d: l_D as the rest of the call knows it, the tensor's size (DENSE) or what the row-count kernel derived from the row
 // ends: a histogram that does not add up to it becomes an error, never a wrong table.  l_tab: 16 bytes a symbol; tmp: 33
 // words of LDS, 16-byte aligned, free until the coding; flag: a word that stays free a little longer.
-template <uint32_t PER>
+// The division-free entry as k_encode_feed's coder takes it: {lim, mx, F, 2^M - f | sh << 24}.
+__device__ __forceinline__ uint4 enc_fed_form(const uint4 &e) {
+  return make_uint4(e.x, e.y, e.z & 0xffffu, e.w | (e.z >> 16 << 24));
+}
+template <uint32_t PER, bool FED>
 __device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const NormArgs &na, const EncCounts &raw, uint32_t A,
                                                         uint32_t len_d, uint32_t n_chunks, uint32_t *l_tab, uint32_t *tmp,
                                                         uint32_t *flag) {
@@ -349,7 +353,7 @@ __device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const
     const EncForms e = enc_forms(M, f[q], Fq[q]);
     m[q] = e.m;
     if (a < A) {
-      ((uint4 *)l_tab)[a] = e.free;
+      ((uint4 *)l_tab)[a] = FED ? enc_fed_form(e.free) : e.free;
       inexact |= e.inexact;
       if (blockIdx.x == 0) *(uint16_t *)(na.out + kHdrBytes + 2ull * a) = (uint16_t)f[q];
     }
@@ -368,11 +372,12 @@ __device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const
   }
   return t;
 }
+template <bool FED>
 __device__ __forceinline__ EncTable enc_build_table(const CtlRef &ctl, const NormArgs &na, const EncCounts &raw, uint32_t A,
                                                     uint32_t len_d, uint32_t n_chunks, uint32_t *l_tab, uint32_t *tmp,
                                                     uint32_t *flag) {
-  return A <= kWG ? enc_build_table_per<1>(ctl, na, raw, A, len_d, n_chunks, l_tab, tmp, flag)
-                  : enc_build_table_per<2>(ctl, na, raw, A, len_d, n_chunks, l_tab, tmp, flag);
+  return A <= kWG ? enc_build_table_per<1, FED>(ctl, na, raw, A, len_d, n_chunks, l_tab, tmp, flag)
+                  : enc_build_table_per<2, FED>(ctl, na, raw, A, len_d, n_chunks, l_tab, tmp, flag);
 }
 // Chunks of a D of len symbols (l_D < 2^32: a 32-bit division, far shorter than the 64-bit one).
 __device__ __forceinline__ uint32_t enc_chunks(uint64_t len, uint32_t cs) {
@@ -539,7 +544,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
           if (rows >= 16 * (u + 1)) touched[u] = *(const uint32_t *)(colp + (uint64_t)(rows - 16 * (u + 1) + (ln >> 2)) * S);
       }
     }
-    const EncTable t = enc_build_table(ctl, na, counts, A, (uint32_t)len, nc, l_tab, sh + 16, sh + 15);
+    const EncTable t = enc_build_table<false>(ctl, na, counts, A, (uint32_t)len, nc, l_tab, sh + 16, sh + 15);
     if (!t.ok) {
       if (FUSE && blockIdx.x == 0 && threadIdx.x == 0 && d_stream_bytes) *d_stream_bytes = 0;
       bail();

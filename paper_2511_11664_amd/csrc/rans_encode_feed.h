@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
   typedef const __attribute__((address_space(1))) uint8_t *gptr;
   struct __attribute__((packed, aligned(1))) U32 { uint32_t x; };
   typedef const __attribute__((address_space(1))) U32 *gptr32;
-  auto fetch = [&](uint32_t *d, uint32_t tile) {
+  auto fetch = [&](uint32_t *d, uint32_t tile) __attribute__((always_inline)) {
     const uint32_t p = tile * kFeedRows + (wv - 1) * kFeedPer;
     if constexpr (std::is_same<Src, SrcDense>::value) {  // a chunk has at most 2^30 symbols here
       const int32_t i0 = ((int32_t)rows - 1 - (int32_t)p) * (int32_t)S + (int32_t)jc, last = (int32_t)n_here - 1;
@@ -141,15 +141,26 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
       }
     }
   };
-  uint32_t wa[kFeedPer], wb[kFeedPer];
+  // Two tiles' symbols are requested at a time, when the two before have arrived: across the branches of fetch() and feed() the
+  // compiler cannot tell how old a request is, so a wave that waits for one waits for all of them.  Requested a tile at a time,
+  // every tile of a dense tensor took a trip to memory.  CSR: a tile at a time, two in turn; its fetch() and feed() are long and
+  // two more copies of each cost more than the trips (one chunk of 32 streams 307 us, 321 with two tiles at a time).
+  constexpr bool DENSE = std::is_same<Src, SrcDense>::value;
+  uint32_t w0[kFeedPer], wa[2][kFeedPer], wb[2][kFeedPer];
+  auto fetch_two = [&](uint32_t (&w)[2][kFeedPer], uint32_t tile) __attribute__((always_inline)) {  // past the end: valid addresses, never fed
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    fetch(w[0], tile);
+    fetch(w[1], tile + 1);
+  };
   if (wv) {  // on their way while the table is built
-    fetch(wa, 0);
-    fetch(wb, 1);
+    fetch(w0, 0);
+    fetch(wa[0], 1);
+    if (DENSE) fetch(wa[1], 2);
   }
   uint32_t exact_tab;
   uint64_t dir_off, payload_off;
   if (builds) {
-    const EncTable t = enc_build_table(ctl, na, counts, A, (uint32_t)len, nc, l_tab, l_tile, sh + 15);
+    const EncTable t = enc_build_table<true>(ctl, na, counts, A, (uint32_t)len, nc, l_tab, l_tile, sh + 15);
     if (!t.ok) {
       if (blockIdx.x == 0 && threadIdx.x == 0 && d_stream_bytes) *d_stream_bytes = 0;
       bail();
@@ -163,7 +174,7 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
     if (LDS_TAB) {
       for (uint32_t a = threadIdx.x; a < A; a += kWG) {
         if (exact_tab) {
-          ((uint4 *)l_tab)[a] = g_tab4[a];
+          ((uint4 *)l_tab)[a] = enc_fed_form(g_tab4[a]);
         } else {
           const uint2 q = g_tab[a];
           ((uint4 *)l_tab)[a] = make_uint4(q.x, q.y & 0xffffu, q.y >> 16, totalM - (q.y & 0xffffu));
@@ -202,18 +213,12 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
     wp = top - 2 - 2 * r;
   };
   auto entry_of = [&](uint32_t a, bool exact) -> uint4 {  // in the form the coder takes
-    uint4 e;
-    if (LDS_TAB) {
-      e = ((const uint4 *)l_tab)[a];
-    } else if (exact) {
-      e = g_tab4[a];
-    } else {
-      const uint2 q = g_tab[a];
-      e = make_uint4(q.x, q.y & 0xffffu, q.y >> 16, totalM - (q.y & 0xffffu));
-    }
-    return exact ? make_uint4(e.x, e.y, e.z & 0xffffu, e.w | (e.z >> 16 << 24)) : e;
+    if (LDS_TAB) return ((const uint4 *)l_tab)[a];
+    if (exact) return enc_fed_form(g_tab4[a]);
+    const uint2 q = g_tab[a];
+    return make_uint4(q.x, q.y & 0xffffu, q.y >> 16, totalM - (q.y & 0xffffu));
   };
-  auto feed = [&](const uint32_t *d, uint32_t tile, auto exact_tag) {
+  auto feed = [&](const uint32_t *d, uint32_t tile, auto exact_tag) __attribute__((always_inline)) {
     constexpr bool EXACT = decltype(exact_tag)::value;
     const uint32_t p = tile * kFeedRows + (wv - 1) * kFeedPer;
     uint4 *to = (uint4 *)l_tile + (tile & 1) * (kFeedRows * kFeedSpw) + ((wv - 1) * kFeedPer) * kFeedSpw + lane;
@@ -252,7 +257,7 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
         s = s + e.z + (MUL24 ? __umul24(q, e.w) : q * e.w);
       }
     };
-    auto code_tile = [&](uint32_t tile) {
+    auto code_tile = [&](uint32_t tile) __attribute__((always_inline)) {
       const uint4 *tp = (const uint4 *)l_tile + (tile & 1) * (kFeedRows * kFeedSpw) + lane;
       uint4 e[2][8];
 #pragma unroll
@@ -268,26 +273,30 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
         if (__any(wp < colb + 2 * 7)) spill();  // at least eight free slots at the start of every batch
       }
     };
-    if (wv) feed(wa, 0, exact_tag);
+    if (wv) feed(w0, 0, exact_tag);
     else __builtin_amdgcn_s_setprio(3);  // nothing may delay the one wave that everything waits for
     lds_barrier();
-    // two tiles a turn, so that the waiting symbols never move between registers
-    for (uint32_t t = 0; t < n_tiles; t += 2) {
-      if (wv == 0) {
-        code_tile(t);
-      } else {
-        fetch(wa, t + 2);  // past the end: valid addresses, never fed
-        if (t + 1 < n_tiles) feed(wb, t + 1, exact_tag);
-      }
+    // two or four tiles a turn, so that the waiting symbols never move between registers
+    auto step = [&](uint32_t t, const uint32_t *w) __attribute__((always_inline)) {
+      if (wv == 0) code_tile(t);
+      else if (t + 1 < n_tiles) feed(w, t + 1, exact_tag);
       lds_barrier();
-      if (t + 1 >= n_tiles) break;
-      if (wv == 0) {
-        code_tile(t + 1);
-      } else {
-        fetch(wb, t + 3);
-        if (t + 2 < n_tiles) feed(wa, t + 2, exact_tag);
+      return t + 1 < n_tiles;
+    };
+    if constexpr (DENSE) {
+      for (uint32_t t = 0;; t += 4) {
+        if (wv) fetch_two(wb, t + 3);
+        if (!step(t, wa[0]) || !step(t + 1, wa[1])) break;
+        if (wv) fetch_two(wa, t + 5);
+        if (!step(t + 2, wb[0]) || !step(t + 3, wb[1])) break;
       }
-      lds_barrier();
+    } else {
+      for (uint32_t t = 0;; t += 2) {
+        if (wv) fetch(w0, t + 2);  // past the end: valid addresses, never fed
+        if (!step(t, wa[0])) break;
+        if (wv) fetch(wa[0], t + 3);
+        if (!step(t + 1, w0)) break;
+      }
     }
     if (wv == 0) __builtin_amdgcn_s_setprio(0);
   };
