@@ -578,7 +578,9 @@ __global__ __launch_bounds__(NT) void k_decode_fast(const uint8_t *in, uint64_t 
       else return *(lds_u16 *)(uintptr_t)((rd_scaled & 31u) | colb);
     };
     auto wread_next = [&](uint32_t rd) -> uint32_t {  // LEAN: the word after word rd; the line's first word follows its last one again
-      return *(lds_u16 *)(uintptr_t)(((rd & (2 * kBlkWords - 1)) << 1) + colb + 2);
+      uint32_t n = rd & (2 * kBlkWords - 1);
+      asm("" : "+v"(n));  // one instruction for the shift and the addition, where the mask behind the shift would make it two
+      return *(lds_u16 *)(uintptr_t)((n << 1) + colb + 2);
     };
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) u32x4 lds_u128;
@@ -681,6 +683,8 @@ __global__ __launch_bounds__(NT) void k_decode_fast(const uint8_t *in, uint64_t 
     };
     uint64_t e_ahead = LEAN ? slot_entry(s) : 0;
     uint32_t wnext2 = 0, s_top = s >> M;  // LEAN: the word after wnext, the state without its slot
+    // LEAN and WIDE: the table address that wnext leads to, should the state take it up: its low M <= 16 bits are the slot then
+    uint32_t w_at = (wnext << 3) & (mask << 3);
     auto lean_step = [&]() {
       const uint32_t ex = (uint32_t)e_ahead, ey = (uint32_t)(e_ahead >> 32);
       uint32_t fx, bias;
@@ -696,13 +700,22 @@ __global__ __launch_bounds__(NT) void k_decode_fast(const uint8_t *in, uint64_t 
       }
       const uint32_t v = (MUL24 ? __umul24(fx, s_top) : fx * s_top) + bias;
       const bool low = v < kL;
-      s = low ? (v << 16) | wnext : v;
-      e_ahead = slot_entry(s);
-      __builtin_amdgcn_sched_barrier(0);  // the request goes out before anything else
-      s_top = s >> M;
-      wnext = low ? wnext2 : wnext;
+      if constexpr (WIDE) {  // both addresses are there when it is known which one it is
+        const uint32_t v_at = (v << 3) & (mask << 3);
+        e_ahead = *(lds_u64 *)(uintptr_t)(low ? w_at : v_at);
+        __builtin_amdgcn_sched_barrier(0);  // the request goes out before anything else
+        s = low ? (v << 16) | wnext : v;
+      } else {
+        s = low ? (v << 16) | wnext : v;
+        e_ahead = slot_entry(s);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       rd9 += low ? 1u : 0u;
+      asm("" : "+v"(rd9));  // one addition with carry a step
+      wnext = low ? wnext2 : wnext;
       wnext2 = wread_next(rd9);
+      s_top = s >> M;
+      if constexpr (WIDE) w_at = (wnext << 3) & (mask << 3);
       sink.put(ob, oi, ey);
       oi += oi_step;
       __builtin_amdgcn_sched_barrier(0);
