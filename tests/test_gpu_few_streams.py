@@ -38,6 +38,14 @@ def test_tile_edges(rows, s, rem):
         _compare(_relu(n, rows), 6, 12, B.MODE_CSR, 5, s, 0)
 
 
+# dense chunks of four to nine tiles: the feeding waves request two tiles at a time, four make a turn
+@pytest.mark.parametrize("rows", [95, 96, 97, 119, 120, 121, 144, 145, 168, 169, 192, 193, 217])
+@pytest.mark.parametrize("s,rem,cs", [(64, 0, 0), (33, 1, 0), (70, 69, 70 * 96)])
+def test_turns_of_four_tiles(rows, s, rem, cs):
+    n = rows * s + rem
+    _compare(_relu(n, rows), 8, 12, B.MODE_DENSE, n, s, cs)
+
+
 # word areas that run full again and again, one stream, and chunks whose last one is short
 @pytest.mark.parametrize("n,q,m,mode,cols,s,cs", [
     (30011, 8, 12, 0, 1, 3, 0), (30011, 8, 14, 0, 1, 1, 0), (50000, 8, 12, 1, 50, 2, 0), (40000, 8, 12, 1, 8, 64, 64 * 300),
