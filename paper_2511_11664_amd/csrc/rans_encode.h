@@ -498,18 +498,24 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
   };
   const bool builds = TAB == 2 && build_tab;  // the table build looks at the status itself
   EncCounts counts{};
-  if (builds) {
-    counts = enc_request_counts(ctl, na, A);
-  } else if (group_has_status(ctl, l_mem)) {  // through the dynamic LDS: this kernel must not have static LDS (see below)
-    if (FUSE && blockIdx.x == 0 && threadIdx.x == 0 && d_stream_bytes) *d_stream_bytes = 0;
-    bail();
-    return;
-  }
+  if (builds) counts = enc_request_counts(ctl, na, A);
+  const bool failed = !builds && group_has_status(ctl, l_mem);  // through the dynamic LDS: this kernel must not have static LDS (see below)
   // The grid is sized for the longest D the tensor could have (in CSR mode the host does not know the number of
   // nonzeros): a work-group whose chunk does not exist leaves before the table build, not after it.  l_D is
   // known here - the tensor's size, or what the CSR kernels stored - and with it the number of chunks.
   const uint64_t len = std::is_same<Src, SrcDense>::value ? na.n_elems : ctl->len_d;
   const uint32_t nc = enc_chunks(len, cs);
+  // Without a container the size is 0: the first work-group says so, which sees every error of the kernels before this one,
+  // and the last one that has a chunk, which would have written the size.  It may find at its start what an earlier one
+  // has recorded since: all are not resident at once.
+  auto give_up = [&]() {
+    if (FUSE && threadIdx.x == 0 && d_stream_bytes && (blockIdx.x == 0 || (k == nc - 1 && g == groups - 1))) *d_stream_bytes = 0;
+    bail();
+  };
+  if (failed) {
+    give_up();
+    return;
+  }
   if (k >= nc && blockIdx.x != 0) {  // the first work-group stays: it writes the header whatever l_D is
     bail();
     return;
@@ -549,8 +555,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
     const EncTable t = enc_build_table<false>(ctl, na, counts, A, (uint32_t)len, nc, l_tab, sh + 16, sh + 15);
     if (!t.ok) {
-      if (FUSE && blockIdx.x == 0 && threadIdx.x == 0 && d_stream_bytes) *d_stream_bytes = 0;
-      bail();
+      give_up();
       return;
     }
     if ((touched[0] ^ touched[1]) == 0x9e3779b9u && wide == 0x7fffffff) l_mem[1] = touched[0];  // never true: keeps the loads
@@ -607,7 +612,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
   typedef __attribute__((address_space(3))) uint32_t lds_u32;
   if ((uint32_t)(uintptr_t)(lds_u16 *)l_mem != 0) {  // cannot happen without static LDS; the slot arithmetic relies on it
     if (threadIdx.x == 0) set_status(ctl, RANS_ERR_HIP);
-    bail();
+    give_up();
     return;
   }
   uint32_t s = kL;
@@ -1114,12 +1119,12 @@ __global__ __launch_bounds__(kWG) void k_gather(CtlRef ctl, uint16_t *scratch, u
   __shared__ uint32_t sh[kWG / 64];
   __shared__ uint64_t sh64[kWG / 64];
   __shared__ uint16_t tile[kGatherTile];
-  if (group_has_status(ctl)) {
-    if (FUSED_SCAN && blockIdx.x == 0 && threadIdx.x == 0 && d_stream_bytes) *d_stream_bytes = 0;
-    return;
-  }
   const uint32_t k = blockIdx.x / groups, g = blockIdx.x % groups;
   const uint32_t nc = ctl->n_chunks;
+  if (group_has_status(ctl)) {  // of a kernel before, or of an earlier work-group of this one; see k_encode on the size
+    if (FUSED_SCAN && threadIdx.x == 0 && d_stream_bytes && (blockIdx.x == 0 || (k == nc - 1 && g == 0))) *d_stream_bytes = 0;
+    return;
+  }
   if (FUSED_SCAN && nc == 0 && blockIdx.x == 0) {  // empty D: only the directory's single entry
     if (threadIdx.x == 0) {
       uint8_t *dir0 = out + ctl->dir_off;

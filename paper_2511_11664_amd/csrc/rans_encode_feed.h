@@ -55,16 +55,19 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
   };
   const bool builds = LDS_TAB && build_tab;  // the table build looks at the status itself
   EncCounts counts{};
-  if (builds) {
-    counts = enc_request_counts(ctl, na, A);
-  } else if (group_has_status(ctl, l_mem)) {
-    if (blockIdx.x == 0 && threadIdx.x == 0 && d_stream_bytes) *d_stream_bytes = 0;
-    bail();
-    return;
-  }
+  if (builds) counts = enc_request_counts(ctl, na, A);
+  const bool failed = !builds && group_has_status(ctl, l_mem);
   // l_D is known already: the tensor's size, or what the CSR kernels stored
   const uint64_t len = std::is_same<Src, SrcDense>::value ? na.n_elems : ctl->len_d;
   const uint32_t nc = enc_chunks(len, cs);
+  auto give_up = [&]() {  // the size of a container that there is not, see k_encode
+    if (threadIdx.x == 0 && d_stream_bytes && (blockIdx.x == 0 || (k == nc - 1 && g == groups - 1))) *d_stream_bytes = 0;
+    bail();
+  };
+  if (failed) {
+    give_up();
+    return;
+  }
   if (k >= nc) {  // the grid is sized for the longest D (an empty one never gets here: k_normalize and k_gather write it)
     bail();
     return;
@@ -164,8 +167,7 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
   if (builds) {
     const EncTable t = enc_build_table<true>(ctl, na, counts, A, (uint32_t)len, nc, l_tab, l_tile, sh + 15);
     if (!t.ok) {
-      if (blockIdx.x == 0 && threadIdx.x == 0 && d_stream_bytes) *d_stream_bytes = 0;
-      bail();
+      give_up();
       return;
     }
     dir_off = t.dir_off; payload_off = t.payload_off;
@@ -189,7 +191,7 @@ __global__ __launch_bounds__(kWG) void k_encode_feed(Src src, const uint2 *g_tab
   typedef __attribute__((address_space(3))) uint32_t lds_u32;
   if ((uint32_t)(uintptr_t)(lds_u16 *)l_mem != 0) {  // cannot happen without static LDS; the slot arithmetic relies on it
     if (threadIdx.x == 0) set_status(ctl, RANS_ERR_HIP);
-    bail();
+    give_up();
     return;
   }
   const bool live = threadIdx.x < kFeedSpw && j0 < S;
