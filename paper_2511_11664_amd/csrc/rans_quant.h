@@ -326,6 +326,13 @@ __global__ __launch_bounds__(kWG) void k_selftest_divide(uint32_t *mismatches, u
     const uint64_t n = (uint64_t)q * d + r;
     const uint32_t sh = 1 + (uint32_t)(h % 15);
     if (n >> sh < (1ull << 32)) bad += div_small_quot((uint32_t)(n >> sh), sh, (uint32_t)n & ((1u << sh) - 1u), d) != q;
+    // the normalisation's own: counts c of the l_D = d symbols, half of d on top; ends, anything between, both sides of a quotient's edge
+    const uint64_t edge = ((h3 & ((1u << sh) - 1u)) + 1) * d - d / 2;  // where c 2^sh + d / 2 reaches a multiple of d
+    const uint64_t at = edge >> sh;
+    uint32_t c = t % 8 == 0 ? 0u : t % 8 == 1 ? 1u : t % 8 == 2 ? d : t % 8 == 3 ? d - 1
+                 : t % 8 == 4 ? (uint32_t)(h3 >> 32) : (uint32_t)(at + t % 8 - 6);
+    c = c > d ? c % d : c;
+    bad += div_small_quot(c, sh, d / 2, d) != (uint32_t)((((uint64_t)c << sh) + d / 2) / d);
   }
   if (bad) atomicAdd(mismatches, bad);
 }
