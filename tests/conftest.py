@@ -17,3 +17,22 @@ def oracle():
     import oracle as _o
     _o.lib()
     return _o
+
+
+@pytest.fixture
+def launched_kernels():
+    """Names of the kernels that a call launches."""
+    import torch
+    from paper_2511_11664_amd import binding as B
+
+    def launched(call):
+        B.rans_profile_reset()
+        B.rans_profile_enable("all")
+        try:
+            call()
+            torch.cuda.synchronize()
+            return set(B.rans_profile_read())
+        finally:
+            B.rans_profile_enable(None)
+            B.rans_profile_reset()
+    return launched

@@ -9,18 +9,6 @@ from paper_2511_11664_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 
-def _launched(call):
-    B.rans_profile_reset()
-    B.rans_profile_enable("all")
-    try:
-        call()
-        torch.cuda.synchronize()
-        return set(B.rans_profile_read())
-    finally:
-        B.rans_profile_enable(None)
-        B.rans_profile_reset()
-
-
 # encoder, elements, row length, mode, streams, chunk: work-groups of the encoder that places its words itself (building its
 # table, and with k_normalize's), of the fed one likewise, and of the gather kernel behind grids above 16384
 @pytest.mark.parametrize("kernel,n,cols,mode,s,chunk", [
@@ -30,7 +18,7 @@ def _launched(call):
     ("k_encode_feed", 6000000, 16, B.MODE_CSR, 64, 64 * 256),
     ("k_encode_feed", 6000000, 750, B.MODE_CSR, 64, 64 * 256),
     ("k_gather", 66 * 65536, 65536, B.MODE_DENSE, 65536, 65536)])
-def test_size_is_zero_when_later_groups_find_the_error(kernel, n, cols, mode, s, chunk):
+def test_size_is_zero_when_later_groups_find_the_error(kernel, n, cols, mode, s, chunk, launched_kernels):
     g = torch.Generator().manual_seed(n + cols)
     x = torch.randint(1, 256, (n,), generator=g).float()  # no zeros but one: D is as long as the grid is sized for
     x[0] = 0
@@ -47,7 +35,7 @@ def test_size_is_zero_when_later_groups_find_the_error(kernel, n, cols, mode, s,
         for _ in range(3):
             size.fill_(0x7777)
             print(f"[case] {kernel} n={n} K={cols} mode={mode} S={s} room={room}", flush=True)
-            names = _launched(lambda: B.rans_compress(xd, n, p, small, size, codec.ws))
+            names = launched_kernels(lambda: B.rans_compress(xd, n, p, small, size, codec.ws))
             assert kernel in names
             assert B.rans_last_status(codec.ws) == B.ERR_CAPACITY
             assert int(size.item()) == 0

@@ -38,7 +38,7 @@ def test_tile_edges(rows, s, rem):
         _compare(_relu(n, rows), 6, 12, B.MODE_CSR, 5, s, 0)
 
 
-# dense chunks of four to nine tiles: the feeding waves request two tiles at a time, four make a turn
+# dense chunks of four to ten tiles: the feeding waves request two tiles at a time, four make a turn
 @pytest.mark.parametrize("rows", [95, 96, 97, 119, 120, 121, 144, 145, 168, 169, 192, 193, 217])
 @pytest.mark.parametrize("s,rem,cs", [(64, 0, 0), (33, 1, 0), (70, 69, 70 * 96)])
 def test_turns_of_four_tiles(rows, s, rem, cs):

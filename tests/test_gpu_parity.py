@@ -275,7 +275,7 @@ def _inexact_entries(container: bytes, A: int, M: int) -> int:
 
 
 def test_both_table_forms_and_the_alphabet_switches():
-    """The encoder builds its table itself for alphabets up to 512 symbols (one wave up to 256, wave plus work-group
+    """The encoder builds its table itself for alphabets up to 512 symbols (a symbol a thread up to 256, two
     above), k_normalize above that; a frequency table with a multiplier that is not exact makes the coder use its other
     table form.  Every combination has to give the oracle's bytes."""
     n = 60000

@@ -24,22 +24,36 @@ def _tensor(kind, levels, n, seed):
     return x[torch.randperm(n, generator=g)]
 
 
+def _compare(x, q, m, cols, s, cs, kernel, launched_kernels):
+    n, mode = x.numel(), B.MODE_CSR if cols else B.MODE_DENSE
+    print(f"[case] Q={q} K={cols} M={m} S={s} n={n}", flush=True)
+    codec = B.Codec(B.make_params(q, m, n // (cols or n), cols or n, mode, s, cs, B.F32), n)
+    xd = x.cuda()
+    assert {"k_encode", "k_encode_feed"} & launched_kernels(lambda: codec.compress(xd, check=False)) == {kernel}
+    status = B.rans_last_status(codec.ws)
+    try:
+        ref, _ = oracle.compress(x.numpy(), oracle.make_params(q, m, n // (cols or n), cols or n, mode, s, cs, 0))
+    except oracle.OracleError as e:
+        assert status == e.code and int(codec.nbytes.item()) == 0
+        return
+    assert status == 0 and codec.container(int(codec.nbytes.item())) == ref
+
+
 # M from the fewest slots the present symbols fit up; 2^6 slots are too few for most of the 8-bit tensors
 @pytest.mark.parametrize("kind", ["flat", "steep", "steps", "few"])
 @pytest.mark.parametrize("q,cols", [(1, 0), (3, 0), (8, 0), (6, 63), (8, 255), (8, 256), (8, 301), (8, 511)])
-def test_small_tables(kind, q, cols):
-    n = (cols or 97) * 41
-    x = _tensor(kind, 1 << q, n, q + cols)
-    mode = B.MODE_CSR if cols else B.MODE_DENSE
+def test_small_tables(kind, q, cols, launched_kernels):
+    x = _tensor(kind, 1 << q, (cols or 97) * 41, q + cols)
+    other = "k_encode" if cols else "k_encode_feed"
     for m in (6, 8, 9, 10, 12, 15):
-        for s, cs in ((64, 64 * 40), (300, 0)):  # the fed encoder and, with so few symbols a stream, the other one
-            print(f"[case] {kind} Q={q} K={cols} M={m} S={s}", flush=True)
-            codec = B.Codec(B.make_params(q, m, n // (cols or n), cols or n, mode, s, cs, B.F32), n)
-            try:
-                ref, _ = oracle.compress(x.numpy(), oracle.make_params(q, m, n // (cols or n), cols or n, mode, s, cs, 0))
-            except oracle.OracleError as e:
-                with pytest.raises(B.RansError) as got:
-                    codec.compress(x.cuda())
-                assert got.value.code == e.code
-                continue
-            assert codec.container(codec.compress(x.cuda())) == ref
+        for s, cs, kernel in ((64, 64 * 40, "k_encode_feed"), (300, 0, other), (1088, 0, "k_encode")):
+            _compare(x, q, m, cols, s, cs, kernel, launched_kernels)
+
+
+# k_encode on dense chunks long enough for the lines that it requests beside the table build (16 and 32 rows), ragged at the end
+@pytest.mark.parametrize("kind", ["flat", "steep", "steps", "few"])
+@pytest.mark.parametrize("s,rows,chunks", [(1088, 11, 3), (4096, 31, 4), (4096, 33, 4), (64, 40, 513)])
+def test_small_tables_beside_touched_lines(kind, s, rows, chunks, launched_kernels):
+    x = _tensor(kind, 256, s * rows * chunks - 5, rows)
+    for m in (8, 9, 12):
+        _compare(x, 8, m, 0, s, s * rows, "k_encode", launched_kernels)
