@@ -214,7 +214,8 @@ const char *rans_strerror(int code);
  * Eq. 2) against the integer division they stand for: floor(2^(32+k) / d) for
  * every d in 1 .. 65535 with 2^k <= d < 2^(k+1), floor(n / d) for n_random
  * pseudo-random pairs with a quotient below 2^17, and as many first estimates
- * floor((c 2^m + l / 2) / l), c <= l < 2^32, m = 1 .. 15.  *d_mismatches (device, 4
+ * floor((c 2^m + l / 2) / l), c <= l < 2^32, m = 1 .. 15; then the table build on
+ * histograms that add up to l_D and on such that do not.  *d_mismatches (device, 4
  * bytes, written by the call) receives the number of disagreements: 0 on a
  * correct build.  Enqueued on `stream`. */
 int rans_selftest_divide(uint32_t *d_mismatches, uint64_t n_random, void *stream);

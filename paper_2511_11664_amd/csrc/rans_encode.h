@@ -186,13 +186,14 @@ __device__ __forceinline__ EncCounts enc_request_counts(const CtlRef &ctl, const
   if (two) request(1);
   return r;
 }
-// len_d: l_D as the rest of the call knows it, the tensor's size (DENSE) or what the row-count kernel derived from the row
-// ends: a histogram that does not add up to it becomes an error, never a wrong table.  l_tab: 16 bytes a symbol; tmp: 33
-// words of LDS, 16-byte aligned, free until the coding; flag: a word that stays free a little longer.
 // The division-free entry as k_encode_feed's coder takes it: {lim, mx, F, 2^M - f | sh << 24}.
 __device__ __forceinline__ uint4 enc_fed_form(const uint4 &e) {
   return make_uint4(e.x, e.y, e.z & 0xffffu, e.w | (e.z >> 16 << 24));
 }
+// len_d: l_D as the rest of the call knows it, the tensor's size (DENSE) or what the row-count kernel derived from the row
+// ends: a histogram that does not add up to it becomes an error, never a wrong table.  The sum is exact: 512 counts of 32
+// bits as two sums of 16-bit halves.  l_tab: 16 bytes a symbol; tmp: 33 words of LDS, 16-byte aligned, free until the
+// coding; flag: a word that stays free a little longer.
 template <uint32_t PER, bool FED>
 __device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const NormArgs &na, const EncCounts &raw, uint32_t A,
                                                         uint32_t len_d, uint32_t n_chunks, uint32_t *l_tab, uint32_t *tmp,
@@ -201,10 +202,10 @@ __device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const
   const uint32_t M = na.p.freq_bits, total = 1u << M;
   const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6, a0 = PER * threadIdx.x;
   uint32_t c[PER], f[PER];
-  uint32_t cnt = 0, pk = 0;        // counts; f in the low 20 bits, present symbols above
+  uint32_t cnt_lo = 0, cnt_hi = 0; // the halves of the counts
+  uint32_t pk = 0;                 // f in the low 20 bits, present symbols above
   uint32_t key = 0;                // largest f, lowest index: f << 9 | 511 - a
   uint32_t best = 0, best_a = 0;   // largest count, lowest index
-  bool over = false;
 #pragma unroll
   for (uint32_t q = 0; q < PER; q++) {
     uint32_t t = 0;
@@ -214,8 +215,8 @@ __device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const
     // the division is made for absent symbols too (and for an empty D, by 1): see enc_forms on branches
     const uint32_t e = div_small_quot(c[q], M, len_d / 2, len_d ? len_d : 1u);  // at most 2^M
     f[q] = c[q] ? (e < 1 ? 1u : e) : 0u;
-    over |= c[q] > len_d;
-    cnt += c[q];
+    cnt_lo += c[q] & 0xffffu;
+    cnt_hi += c[q] >> 16;
     pk += f[q] + ((uint32_t)(c[q] != 0) << 20);
     const uint32_t kq = f[q] << 9 | (511u - (a0 + q));
     key = kq > key ? kq : key;
@@ -228,13 +229,12 @@ __device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const
   auto wave_sum = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum_scan(v), 63); };
   const uint32_t pk_inc = wave_incl_sum_scan(pk);
   {
-    const uint32_t w_cnt = wave_sum(cnt), w_key = wave_max(key), w_best = wave_max(best);
+    const uint32_t w_lo = wave_sum(cnt_lo), w_hi = wave_sum(cnt_hi), w_key = wave_max(key), w_best = wave_max(best);
     const uint32_t w_best_a =
         (uint32_t)__builtin_amdgcn_readlane((int)best_a, (int)__builtin_ctzll(__ballot(best == w_best)));
-    const bool w_over = __any(over);
     if (lane == 63) {
-      *(uint4 *)(tmp + 8 * w) = make_uint4(w_cnt, pk_inc, w_key, w_best);
-      tmp[8 * w + 4] = w_best_a | (w_over ? 1u << 16 : 0u);
+      *(uint4 *)(tmp + 8 * w) = make_uint4(w_lo, pk_inc, w_key, w_best);
+      *(uint2 *)(tmp + 8 * w + 4) = make_uint2(w_best_a, w_hi);
     }
   }
   // another work-group of the running kernel may record an error at any moment: thread 0's look decides for all
@@ -243,31 +243,31 @@ __device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const
     *flag = 0;  // set below if an entry is inexact
   }
   __syncthreads();
-  uint32_t len = 0, sum = 0, f_before = 0, top_a = 0, top_c = 0, top_key = 0, any_over = 0;
+  uint32_t len_lo = 0, len_hi = 0, sum = 0, f_before = 0, top_a = 0, top_c = 0, top_key = 0;
   uint4 rec[kWaves];
-  uint32_t rec_a[kWaves];
+  uint2 rec_a[kWaves];
 #pragma unroll
   for (uint32_t v = 0; v < kWaves; v++) {  // all on their way before the first is looked at
     rec[v] = *(const uint4 *)(tmp + 8 * v);
-    rec_a[v] = tmp[8 * v + 4];
+    rec_a[v] = *(const uint2 *)(tmp + 8 * v + 4);
   }
   const uint32_t failed = tmp[32];
 #pragma unroll
   for (uint32_t v = 0; v < kWaves; v++) {
-    len += rec[v].x;
+    len_lo += rec[v].x;
+    len_hi += rec_a[v].y;
     sum += rec[v].y;
     f_before += v < w ? rec[v].y & kSumMask : 0u;
     top_key = rec[v].z > top_key ? rec[v].z : top_key;
     const bool more = rec[v].w > top_c;
     top_c = more ? rec[v].w : top_c;
-    top_a = more ? rec_a[v] & 0xffffu : top_a;
-    any_over |= rec_a[v] >> 16;
+    top_a = more ? rec_a[v].x : top_a;
   }
   EncTable t{};
   t.dir_off = kHdrBytes + (((uint64_t)A * 2 + 7) & ~7ull);
   t.payload_off = t.dir_off + 8 * ((uint64_t)n_chunks + 1);
   {
-    const int err = (any_over || len != len_d) ? RANS_ERR_HIP : (sum >> 20) > total ? RANS_ERR_ALPHABET
+    const int err = ((uint64_t)len_hi << 16) + len_lo != len_d ? RANS_ERR_HIP : (sum >> 20) > total ? RANS_ERR_ALPHABET
                     : t.payload_off > na.cap ? RANS_ERR_CAPACITY : 0;
     if (__builtin_expect(failed || err, 0)) {  // uniform
       if (threadIdx.x == 0 && !failed) set_status(ctl, err);
@@ -378,6 +378,43 @@ __device__ __forceinline__ EncTable enc_build_table(const CtlRef &ctl, const Nor
                                                     uint32_t *flag) {
   return A <= kWG ? enc_build_table_per<1, FED>(ctl, na, raw, A, len_d, n_chunks, l_tab, tmp, flag)
                   : enc_build_table_per<2, FED>(ctl, na, raw, A, len_d, n_chunks, l_tab, tmp, flag);
+}
+// Runs the table build by one work-group on histograms that add up to l_D and on such that miss it by 1, 2^32 or 2^33, and
+// adds those it takes wrongly to *mismatches (see rans_selftest_divide).
+__global__ __launch_bounds__(kWG) void k_selftest_table(uint32_t *mismatches) {
+  __shared__ __align__(16) uint32_t cnt[kEncBuildMaxA], l_tab[4 * kEncBuildMaxA], tmp[36], flag;
+  __shared__ __align__(16) uint8_t out[kHdrBytes + 2 * kEncBuildMaxA + 8];
+  __shared__ Ctl c;
+  const uint32_t len_d = 3u << 30, M = 12;
+  uint32_t bad = 0;
+  for (uint32_t i = 0; i < 15; i++) {
+    const uint32_t A = i < 5 ? 256 : i < 10 ? 257 : 512;
+    const uint64_t off[5] = {0, 1, ~0ull, 1ull << 32, 1ull << 33};
+    const uint64_t all = len_d + off[i % 5];
+    for (uint32_t a = threadIdx.x; a < A; a += kWG) cnt[a] = (uint32_t)(all / A) + (a < all % A);
+    if (threadIdx.x == 0) {
+      c.status = 0;
+      c.status_seq = 1;
+      c.sticky = 0;
+    }
+    __syncthreads();
+    const CtlRef ctl{&c, 1};
+    NormArgs na{};
+    na.cnt = cnt;
+    na.A = A;
+    na.p.freq_bits = M;
+    na.out = out;
+    na.cap = ~0ull;
+    const EncTable t = enc_build_table<false>(ctl, na, enc_request_counts(ctl, na, A), A, len_d, 1, l_tab, tmp, &flag);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      uint32_t sum = 0;
+      for (uint32_t a = 0; a < A; a++) sum += *(const uint16_t *)(out + kHdrBytes + 2 * a);
+      bad += i % 5 ? t.ok != 0 || c.status != RANS_ERR_HIP : t.ok != 1 || c.status != 0 || sum != 1u << M;
+    }
+    __syncthreads();
+  }
+  if (bad) atomicAdd(mismatches, bad);
 }
 // Chunks of a D of len symbols (l_D < 2^32: a 32-bit division, far shorter than the 64-bit one).
 __device__ __forceinline__ uint32_t enc_chunks(uint64_t len, uint32_t cs) {
@@ -527,7 +564,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
   const uint32_t stride = enc_area_stride(rw);
   const uint32_t areas_end = kEncGuard + stride * kWG;  // a multiple of 16
   uint32_t *l_tab = l_mem + areas_end / 4;
-  uint32_t *sh = l_tab + (TAB == 2 ? A * 4 : (TAB == 1 ? A * 2 : 0));  // 4 + 8 words for the final reductions
+  uint32_t *sh = l_tab + (TAB == 2 ? A * 4 : (TAB == 1 ? A * 2 : 0));  // 16 words: 4 + 8 for the final reductions, the last one enc_build_table's flag
   // Frequency table (Sec. 3.2's normalisation) and container geometry.  build_tab (alphabets up to kEncBuildMaxA): every
   // work-group derives the same table from D's histogram for itself, straight into its LDS; a hand-over from the last
   // counting work-group, or a launch of its own for the table, costs the call as much or more and needs ordering

@@ -1122,6 +1122,8 @@ int rans_selftest_divide(uint32_t *d_mismatches, uint64_t n_random, void *stream
   g = g < 256 ? 256 : (g > 4096 ? 4096 : g);  // at least the 65536 divisors of the first check
   hipLaunchKernelGGL(k_selftest_divide, dim3((uint32_t)g), dim3(kWG), 0, st, d_mismatches, n_random);
   LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_selftest_table, dim3(1), dim3(kWG), 0, st, d_mismatches);
+  LAUNCH_CHECK();
   return RANS_OK;
 }
 

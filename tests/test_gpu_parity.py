@@ -307,7 +307,8 @@ def test_both_table_forms_and_the_alphabet_switches():
 def test_table_divisions_equal_integer_division():
     """The frequency-table kernels divide through a reciprocal estimate and an exact remainder check; on the device
     that runs them: every divisor of the encoder's multipliers (Eq. 2), 2^24 quotients below 2^17, and 2^24 first
-    estimates of Sec. 3.2's normalisation with their half of l_D on top, against integer division."""
+    estimates of Sec. 3.2's normalisation with their half of l_D on top, against integer division; and the table build
+    refuses histograms that miss l_D by 1, 2^32 or 2^33."""
     bad = torch.full((1,), 123, dtype=torch.int32, device="cuda")
     print("[case] division self-test", flush=True)
     assert B.rans_selftest_divide(bad, 1 << 24) == 0
