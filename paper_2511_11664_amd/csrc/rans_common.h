@@ -304,6 +304,7 @@ __device__ __forceinline__ float key2f(uint32_t k) {
   X = OP(X, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)X, 0x142, 0xa, 0xf, false)); /* row_bcast:15 into rows 1, 3 */ \
   X = OP(X, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)X, 0x143, 0xc, 0xf, false)); /* row_bcast:31 into rows 2, 3 */
 __device__ __forceinline__ uint32_t op_add32(uint32_t a, uint32_t b) { return a + b; }
+__device__ __forceinline__ uint32_t add_sat32(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
 __device__ __forceinline__ uint32_t op_max32(uint32_t a, uint32_t b) { return a > b ? a : b; }
 __device__ __forceinline__ uint32_t wave_incl_sum_scan(uint32_t x) {
   RANS_DPP_STEPS(x, op_add32)
@@ -311,6 +312,10 @@ __device__ __forceinline__ uint32_t wave_incl_sum_scan(uint32_t x) {
 }
 __device__ __forceinline__ uint32_t wave_incl_max_scan(uint32_t x) {
   RANS_DPP_STEPS(x, op_max32)
+  return x;
+}
+__device__ __forceinline__ uint32_t wave_incl_sat_scan(uint32_t x) {  // sums that stop at 2^32 - 1
+  RANS_DPP_STEPS(x, add_sat32)
   return x;
 }
 #undef RANS_DPP_STEPS

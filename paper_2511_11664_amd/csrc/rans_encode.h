@@ -191,9 +191,9 @@ __device__ __forceinline__ uint4 enc_fed_form(const uint4 &e) {
   return make_uint4(e.x, e.y, e.z & 0xffffu, e.w | (e.z >> 16 << 24));
 }
 // len_d: l_D as the rest of the call knows it, the tensor's size (DENSE) or what the row-count kernel derived from the row
-// ends: a histogram that does not add up to it becomes an error, never a wrong table.  The sum is exact: 512 counts of 32
-// bits as two sums of 16-bit halves.  l_tab: 16 bytes a symbol; tmp: 33 words of LDS, 16-byte aligned, free until the
-// coding; flag: a word that stays free a little longer.
+// ends: a histogram that does not add up to it becomes an error, never a wrong table.  The sum stops at 2^32 - 1, above any
+// l_D, so that none is taken for another one.  l_tab: 16 bytes a symbol; tmp: 33 words of LDS, 16-byte aligned, free until
+// the coding; flag: a word that stays free a little longer.
 template <uint32_t PER, bool FED>
 __device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const NormArgs &na, const EncCounts &raw, uint32_t A,
                                                         uint32_t len_d, uint32_t n_chunks, uint32_t *l_tab, uint32_t *tmp,
@@ -202,8 +202,7 @@ __device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const
   const uint32_t M = na.p.freq_bits, total = 1u << M;
   const uint32_t lane = threadIdx.x & 63, w = threadIdx.x >> 6, a0 = PER * threadIdx.x;
   uint32_t c[PER], f[PER];
-  uint32_t cnt_lo = 0, cnt_hi = 0; // the halves of the counts
-  uint32_t pk = 0;                 // f in the low 20 bits, present symbols above
+  uint32_t cnt = 0, pk = 0;        // counts; f in the low 20 bits, present symbols above
   uint32_t key = 0;                // largest f, lowest index: f << 9 | 511 - a
   uint32_t best = 0, best_a = 0;   // largest count, lowest index
 #pragma unroll
@@ -215,8 +214,7 @@ __device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const
     // the division is made for absent symbols too (and for an empty D, by 1): see enc_forms on branches
     const uint32_t e = div_small_quot(c[q], M, len_d / 2, len_d ? len_d : 1u);  // at most 2^M
     f[q] = c[q] ? (e < 1 ? 1u : e) : 0u;
-    cnt_lo += c[q] & 0xffffu;
-    cnt_hi += c[q] >> 16;
+    cnt = add_sat32(cnt, c[q]);
     pk += f[q] + ((uint32_t)(c[q] != 0) << 20);
     const uint32_t kq = f[q] << 9 | (511u - (a0 + q));
     key = kq > key ? kq : key;
@@ -229,12 +227,12 @@ __device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const
   auto wave_sum = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum_scan(v), 63); };
   const uint32_t pk_inc = wave_incl_sum_scan(pk);
   {
-    const uint32_t w_lo = wave_sum(cnt_lo), w_hi = wave_sum(cnt_hi), w_key = wave_max(key), w_best = wave_max(best);
+    const uint32_t w_cnt = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sat_scan(cnt), 63), w_key = wave_max(key), w_best = wave_max(best);
     const uint32_t w_best_a =
         (uint32_t)__builtin_amdgcn_readlane((int)best_a, (int)__builtin_ctzll(__ballot(best == w_best)));
     if (lane == 63) {
-      *(uint4 *)(tmp + 8 * w) = make_uint4(w_lo, pk_inc, w_key, w_best);
-      *(uint2 *)(tmp + 8 * w + 4) = make_uint2(w_best_a, w_hi);
+      *(uint4 *)(tmp + 8 * w) = make_uint4(w_cnt, pk_inc, w_key, w_best);
+      tmp[8 * w + 4] = w_best_a;
     }
   }
   // another work-group of the running kernel may record an error at any moment: thread 0's look decides for all
@@ -243,31 +241,30 @@ __device__ __forceinline__ EncTable enc_build_table_per(const CtlRef &ctl, const
     *flag = 0;  // set below if an entry is inexact
   }
   __syncthreads();
-  uint32_t len_lo = 0, len_hi = 0, sum = 0, f_before = 0, top_a = 0, top_c = 0, top_key = 0;
+  uint32_t len = 0, sum = 0, f_before = 0, top_a = 0, top_c = 0, top_key = 0;
   uint4 rec[kWaves];
-  uint2 rec_a[kWaves];
+  uint32_t rec_a[kWaves];
 #pragma unroll
   for (uint32_t v = 0; v < kWaves; v++) {  // all on their way before the first is looked at
     rec[v] = *(const uint4 *)(tmp + 8 * v);
-    rec_a[v] = *(const uint2 *)(tmp + 8 * v + 4);
+    rec_a[v] = tmp[8 * v + 4];
   }
   const uint32_t failed = tmp[32];
 #pragma unroll
   for (uint32_t v = 0; v < kWaves; v++) {
-    len_lo += rec[v].x;
-    len_hi += rec_a[v].y;
+    len = add_sat32(len, rec[v].x);
     sum += rec[v].y;
     f_before += v < w ? rec[v].y & kSumMask : 0u;
     top_key = rec[v].z > top_key ? rec[v].z : top_key;
     const bool more = rec[v].w > top_c;
     top_c = more ? rec[v].w : top_c;
-    top_a = more ? rec_a[v].x : top_a;
+    top_a = more ? rec_a[v] : top_a;
   }
   EncTable t{};
   t.dir_off = kHdrBytes + (((uint64_t)A * 2 + 7) & ~7ull);
   t.payload_off = t.dir_off + 8 * ((uint64_t)n_chunks + 1);
   {
-    const int err = ((uint64_t)len_hi << 16) + len_lo != len_d ? RANS_ERR_HIP : (sum >> 20) > total ? RANS_ERR_ALPHABET
+    const int err = len != len_d ? RANS_ERR_HIP : (sum >> 20) > total ? RANS_ERR_ALPHABET
                     : t.payload_off > na.cap ? RANS_ERR_CAPACITY : 0;
     if (__builtin_expect(failed || err, 0)) {  // uniform
       if (threadIdx.x == 0 && !failed) set_status(ctl, err);
@@ -387,11 +384,13 @@ __global__ __launch_bounds__(kWG) void k_selftest_table(uint32_t *mismatches) {
   __shared__ Ctl c;
   const uint32_t len_d = 3u << 30, M = 12;
   uint32_t bad = 0;
-  for (uint32_t i = 0; i < 15; i++) {
-    const uint32_t A = i < 5 ? 256 : i < 10 ? 257 : 512;
+  for (uint32_t i = 0; i < 30; i++) {
+    const uint32_t A = i % 15 < 5 ? 256 : i % 15 < 10 ? 257 : 512;
     const uint64_t off[5] = {0, 1, ~0ull, 1ull << 32, 1ull << 33};
     const uint64_t all = len_d + off[i % 5];
-    for (uint32_t a = threadIdx.x; a < A; a += kWG) cnt[a] = (uint32_t)(all / A) + (a < all % A);
+    // evenly, or nearly all of it in as many symbols as have to share it
+    for (uint32_t a = threadIdx.x; a < A; a += kWG)
+      cnt[a] = i < 15 ? (uint32_t)(all / A) + (a < all % A) : a < 4 ? (uint32_t)((all - 1) / 4) : a == 4 ? (uint32_t)(all - (all - 1) / 4 * 4) : 0u;
     if (threadIdx.x == 0) {
       c.status = 0;
       c.status_seq = 1;
