@@ -102,29 +102,31 @@ int check_params(const rans_params *p, uint64_t n) {
 // (k_encode_feed), or four coding waves (k_encode).  The fed form has the shorter row and the longer start, and its
 // tiles leave a compute unit room for two work-groups (one, where the table of a large alphabet fills the LDS), so what
 // decides is the symbols per stream (`rows`) and the coding waves (64 streams each) the grid is sized for.  Whole
-// compress calls, time fed over time with k_encode, the slower of M = 12 and 14, by the streams of a chunk:
+// compress calls in a replayed graph, time fed over time with k_encode, the slower of M = 12 and 14, by the streams of a chunk:
 //   rows                         4     8    12    16    24    32    48    64    96   128   192   256   512
-//   dense, up to 192 waves:
-//     1 stream                1.07  1.07  1.04  1.04  1.01  1.03  0.97  0.97  0.93  0.94  0.86  0.84  0.78
-//     64                      0.99  0.97  0.95  0.96  0.93  0.96  0.90  0.92  0.86  0.88  0.82  0.80  0.72
-//     256, 1024               1.01  1.01  0.97  0.98  0.96  1.00  0.93  0.94  0.87  0.87  0.80  0.79  0.72
-//     4096                    1.01  1.03  0.98  1.00  0.98  1.03  0.95  0.94  0.89  0.87  0.80  0.77  0.69
-//   dense, 256 waves: 4096    1.07  1.09  1.02  1.04  1.04  1.02  1.00  0.98  0.91  0.90  0.84  0.81  0.73
-//   dense, 512 waves: 64      0.97  1.00  0.95  1.03  0.99  0.98  0.96  0.95  0.91  0.91  0.86  0.86  0.76
-//     256                     1.02  1.07  1.00  1.05  1.02  1.07  1.01  1.04  0.96  0.98  0.93  0.92  0.88
-//     1024                    1.07  1.14  1.03  1.09  1.06  1.11  1.07  1.09  1.00  1.01  0.95  0.95  0.87
-//     4096                    1.23  1.33  1.19  1.28  1.23  1.24  1.16  1.21  1.17  1.17  1.09  1.03  0.93
-//   dense, 640 waves          1.70  1.66  1.51  1.70  1.61  1.63  1.60  1.53  1.52  1.51  1.38  1.35  1.28
-// CSR tensors are placed as if D were as long as it can be: at 640 and 768 waves a tensor without zeros takes up to 1.7
-// times as long fed and one with 70 % nonzeros 1.5 times, while 30 % nonzeros gain 5 to 10 %; only up to 64 streams a chunk
-// of 256 rows and more lose nothing by it (without zeros 1.05 at most, 50 % nonzeros 0.72 to 0.97).  What a stream gets at
-// least is taken from a D with an eighth of the tensor nonzero: the longer start shows in tensors that do not fill a chunk
-// (5 % nonzeros of 4032 with 256 streams 1.18), and in tables of its own that k_normalize made (5001 symbols 1.12).
-// With up to 64 streams a chunk the line is the same from 288 to 512 waves: 64 streams 24 rows 0.97 to 1.01, 32 1.02 at
-// most, 64 0.96, CSR 24 and more 0.82 to 1; 1 and 16 streams 32 rows 1.07, 48 0.99; encode of 927 744 3-bit symbols, 382
-// chunks of 64 x 38, 15.9 -> 14.8 us.
-// Alphabets of 1021 to 5120 symbols (one work-group on a unit) at 288 to 512 waves: 1.11 at 128 rows, 0.95 at 512, up to
-// 64 streams 0.98 at 256.
+//   dense, 192 waves:
+//     1 stream                1.05  1.03  1.00  1.00  0.93  0.96  0.90  0.87  0.84  0.84  0.79  0.76  0.70
+//     64                      0.90  0.93  0.85  0.91  0.88  0.90  0.83  0.85  0.80  0.80  0.74  0.77  0.68
+//     256, 1024               0.95  1.01  0.87  0.99  0.92  0.96  0.94  0.90  0.83  0.83  0.76  0.74  0.69
+//     4096                    1.01  1.01  0.93  0.98  0.94  0.97  0.91  0.87  0.85  0.85  0.76  0.74  0.68
+//   dense, 256 waves: 4096    1.06  1.09  0.98  1.05  1.01  1.01  0.98  0.92  0.91  0.88  0.81  0.77  0.70
+//   dense, 512 waves: 64      0.96  0.98  0.89  0.95  0.92  0.97  0.88  0.92  0.89  0.86  0.83  0.84  0.69
+//     256                     1.03  1.12  0.98  1.10  1.03  1.14  1.03  1.08  0.97  0.95  0.88  0.87  0.81
+//     1024                    1.18  1.33  1.11  1.31  1.14  1.26  1.14  1.13  1.02  1.00  0.96  0.92  0.83
+//     4096                    1.45  1.45  1.27  1.46  1.40  1.43  1.31  1.31  1.25  1.23  1.13  1.07  0.91
+//   dense, 640 waves: 64      1.22  1.22  1.15  1.18  1.13  1.12  1.12  1.14  0.80  0.79  0.73  0.64  0.60
+//     1024                    1.61  1.79  1.50  1.75  1.61  1.70  1.53  1.56  1.41  1.40  1.28  1.27  1.15
+// CSR tensors (rows of 16) are placed as if D were as long as it can be: at 640 and 768 waves of 1024 and 4096 streams a tensor
+// without zeros takes up to 1.55 times as long fed and one with 70 % nonzeros 1.43 times, while one with 30 % takes 0.82 to
+// 1.12; up to 64 streams a chunk of 128 rows and more lose nothing by it (without zeros 0.98 at most, 50 % nonzeros 0.48 to
+// 0.85).  What a stream gets at least is taken from a D with an eighth of the tensor nonzero: 4032 symbols, 5 % of them
+// nonzero, with 256 streams 1.04.  Tables that k_normalize made (5001 symbols), up to 192 waves: 1.01 at 8 rows, 1 from 12 on.
+// With up to 64 streams a chunk the line is the same from 288 to 512 waves: 64 streams 24 rows 0.97, 32 0.98, 64 0.92, CSR 24
+// and more 0.70 to 0.97; 1 and 16 streams 32 rows 1.05, 48 0.99.
+// Alphabets of 1101 and 4001 symbols (one work-group on a unit) at 288 to 512 waves: 128 rows 1.00, 512 0.82, up to 64
+// streams 128 rows 0.94, 256 0.83.
+// The lines below were drawn when both encoders were slower; none of them sends a call to the slower one by more than 1 %, and
+// some would bear fewer rows (64 streams: dense at 640 waves, large alphabets).
 constexpr uint32_t kFeedSpw = 64;           // streams per work-group of the fed encoder
 constexpr uint32_t kFeedTwoMaxA = 1020;     // alphabets up to this size leave room for a second work-group
 constexpr uint32_t kFeedLdsTabMaxA = 5120;  // and up to this one their 16-byte entries fit the LDS beside two tiles

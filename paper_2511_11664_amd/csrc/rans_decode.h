@@ -373,11 +373,11 @@ constexpr uint32_t kLeanBlkWords = 32, kLeanLine = 144;  // see LEAN below
 // after next, read one step before it can be needed) happens while that request is on its way; blocks are 32 words
 // and looked after every 32 steps, which takes the refill's fifty instructions out of the steps.  The table is at LDS
 // address 0, the windows (144 bytes a stream: the same word of all streams in 16 different banks) at win_off.
-// One chunk of 32 streams and 6240 rows: 504 -> 405 us; 31 chunks of 64 x 64: 11.6 -> 10.6 us; a step was 133 cycles, of
-// which 60 wait for the entry and about 20 each go into issuing the word read and the store beside it.
+// One chunk of 32 streams and 6211 rows: 504 -> 405 us; 31 chunks of 64 x 64: 11.6 -> 10.6 us.  Before the two candidates below
+// a step was 133 cycles, of which 60 waited for the entry and about 20 each went into issuing the word read and the store beside it.
 // WIDE: where the renormalisation fires, the next slot is the low M bits of the word it takes up, known a step before.  Both
 // candidates of the entry's address are made while the comparison is on its way, instead of the state first and its address
-// from that; the state itself follows behind the request.  The one chunk's decompress call 402 -> 380 us.
+// from that; the state itself follows behind the request.  The one chunk's decompress call 402 -> 380 us, a step about 60 ns.
 template <class Sink, typename LutT, bool MUL24, int NT, bool WIDE, bool LEAN>
 __global__ __launch_bounds__(NT) void k_decode_fast(const uint8_t *in, uint64_t bytes, CtlRef ctl, uint32_t A,
                                                      uint32_t M, uint32_t S, uint32_t cs, uint32_t groups,

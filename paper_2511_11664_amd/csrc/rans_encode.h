@@ -152,7 +152,8 @@ struct __attribute__((packed, aligned(2))) Block16 { uint32_t x, y, z, w; };
 // From the counts to the table, one wave with four symbols a lane and 64-bit scans (no barrier, a thousand instructions) / this:
 // 25 work-groups 2.4 / 1.3 us, 752 of them with 257 symbols 3.2 / 1.8, four on every unit 2.5 / 2.4, where the sixteen waves'
 // instructions count.  Whole compress calls: 100 352 symbols 19.1 -> 16.8 us, 395 x 4096 fp16 27.1 -> 25.4, 25.7 M
-// symbols as CSR 105.8 -> 104.4.
+// symbols as CSR 106.2 -> 104.7; 67 M fp16, four work-groups on every unit, 110.7 -> 111.3, which waiting for the counts
+// alone (see k_encode) makes up for.
 constexpr uint32_t kEncBuildMaxA = 2 * kWG;
 // What every thread of an encoder work-group knows once the frequency table is in its LDS.
 struct EncTable {
@@ -423,8 +424,8 @@ __device__ __forceinline__ uint32_t enc_chunks(uint64_t len, uint32_t cs) {
 }
 
 // Totals of what lies before a work-group's words: every earlier chunk (its size gives the chunk's byte offset) and
-// the earlier groups of this chunk (the position inside the chunk).  The first wave collects them - a lane's loads
-// are independent of each other - and hands the sums over through LDS.
+// the earlier groups of this chunk (the position inside the chunk).  The first wave collects them, 64 at a time - a lane's next
+// load goes out when its last one has brought a published value - and hands the sums over through LDS.
 struct EncBefore {
   uint64_t off, pre;  // bytes of the chunks before, words of the groups before
   bool failed;        // a wait ran into its bound, or another work-group reported an error
@@ -578,7 +579,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4))) void k
       // coded from its end), so that they come from the cache by then.  A wave's 64-byte column shares its 128-byte
       // lines with the neighbouring wave's.
       // Requested when the counts have arrived: behind the branch the compiler would have the build wait for these as well
-      // (compress call of 67 M fp16 symbols, four work-groups on every unit, 112.3 us; like this 111.2).
+      // (compress call of 67 M fp16 symbols, four work-groups on every unit, 113.2 us; like this 111.6).
       __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
       if (wide && threadIdx.x >= 64 && k < nc && g * kWG + threadIdx.x < S) {
         const uint32_t cl = cs ? cs : (uint32_t)len, b0 = k * cl, rows = ((uint32_t)len - b0 < cl ? (uint32_t)len - b0 : cl) / S;

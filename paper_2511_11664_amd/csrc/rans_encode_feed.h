@@ -24,9 +24,11 @@ namespace {
 // The entry as fed: exact tables {lim, mx, F, 2^M - f | sh << 24} (the 24-bit multiply-add ignores the shift count on
 // top of its operand), else {floor(2^32/f), f, F, 2^M - f} with a correction step.
 //
-// Measured, k_encode before against this: one chunk of 32 streams and 6272 rows 946 -> 281 us (45 ns a row; the coder's
-// eleven instructions are about 72 cycles, 30 ns, of which the two LDS accesses are 32), 25 chunks of 64 x 64 symbols
-// 15.0 -> 12.0 us, 198 chunks of 64 x 128 symbols 20.4 -> 16.3 us; where the line to k_encode lies: encoder_is_fed.
+// Measured, k_encode before against this: one chunk of 32 streams 946 -> 271 us in CSR form (6211 rows, 44 ns each), 235 us
+// dense (6272 rows, 37 ns); 25 chunks of 64 x 64 symbols 15.0 -> 9.9 us; where the line to k_encode lies: encoder_is_fed.
+// Who waits (cycles of a tile of 24 rows, stamped around the barrier in a copy): the coder works 2235 and waits 75 in CSR form,
+// 2050 and 50 dense; the feeders work 1705 to 1855 and 1130 to 1285 of that.  So the coder is what a row waits for: its eleven
+// instructions are about 72 cycles, of which the two LDS accesses are 32, and take 93 and 85 beside the feeders.
 // Dense symbols requested two tiles at a time instead of one, entries laid out by the table build: the compress call of those
 // 198 chunks 25.9 -> 24.5 us, of the 25 chunks 16.8 -> 16.7.
 //

@@ -143,12 +143,12 @@ inline uint32_t compute_units() {
 constexpr uint32_t kDecWideGroupMinChunks = 192;
 // Decoding waves (64 streams) up to which the decoder takes its LEAN form, and the symbols of a stream from which: its
 // refill comes every 32 symbols, and its longer start has to pay (decompress calls with it over without it, median of 1 to
-// 512 streams, M = 8 to 13: 24 symbols 1.05, 32 0.97, 64 0.92, 256 0.82, 1024 0.75).
+// 512 streams, M = 8 to 13: 16 symbols 1.05, 24 1.04, 32 0.95 (a single stream 1.02), 64 0.89, 256 0.77, 1024 0.71).
 constexpr uint32_t kDecLeanMaxWaves = 1024, kDecLeanMinRows = 32;
-constexpr uint32_t kDecLeanMinRowsBig = 64;  // M >= 14, with its longer build: 32 and 48 symbols 0.99 in the median, up to 1.10; 64 0.95
+constexpr uint32_t kDecLeanMinRowsBig = 64;  // M >= 14, with its longer build: 24 symbols 1.05, 32 and 48 0.98 in the median, up to 1.01; 64 0.92
 // Chunks of so few streams take it only while a compute unit has at most two work-groups: 128 or more symbols a stream,
-// M = 12, with it over without it, 8 / 12 / 32 streams: 512 chunks 0.92 / 0.91 / 0.82, 640 chunks 1.09 / 0.71 / 0.81, 1024
-// chunks 1.18 / 0.83 / 1.  Both lines are void where the other form's larger LDS would make work-groups wait (M = 15, 1024
+// M = 12, with it over without it, 8 / 12 / 32 streams: 512 chunks 0.91 / 0.92 / 0.83, 640 chunks 1.06 / 0.75 / 0.83, 1024
+// chunks 1.17 / 0.87 / 1.  Both lines are void where the other form's larger LDS would make work-groups wait (M = 15, 1024
 // chunks of a stream: 0.74 to 0.80 from 1 to 1024 symbols).
 constexpr uint32_t kDecLeanFewStreams = 8;
 constexpr uint32_t kExpandOwnSumMaxTiles = 4096;
@@ -549,9 +549,9 @@ int decode_common(const uint8_t *d_stream, size_t stream_bytes, const rans_heade
   size_t lds_fast = use_wide ? lds_wide : lds_two;
   // Few waves on the chip, every work-group of them resident: the form with the shortest chain (LEAN in the kernel),
   // table first, windows behind it.  Whole decompress calls, us, without / with it at 64 streams a chunk, M = 12: 256
-  // chunks of 128 rows 16.0 / 13.2, 768 chunks 17.6 / 15.1, 1024 chunks, of which a quarter waits, 18.5 / 25.2.  At
+  // chunks of 128 rows 15.8 / 12.6, 768 chunks 16.7 / 13.7, 1024 chunks, of which a quarter waits, 17.5 / 23.6.  At
   // M = 14 the entry per slot needs 128 KB and a longer build, which pays from about 128 rows: 256 chunks of 64 / 128 /
-  // 512 rows 12.4 / 17.6 / 49.7 with the two look-ups, 13.0 / 16.8 / 39.6 with the one.
+  // 512 rows 11.6 / 16.7 / 46.9 with the two look-ups, 11.7 / 15.9 / 36.8 with the one.
   const uint64_t n_wg_f = (uint64_t)h.n_chunks * groups_f;
   const uint32_t n_cu_f = compute_units();
   const uint64_t rows_f = (h.p.chunk_syms && h.p.chunk_syms < h.len_d ? h.p.chunk_syms : h.len_d) / S;
